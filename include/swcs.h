@@ -157,11 +157,19 @@ int swcs_set_sigma_method(swcs_ctx* ctx, int method);
  * another 12.5 bytes per record fit as well, the gradient terms are summed
  * through per-operator bins (LDS sums, then one device-scope add per
  * operator and bin chunk) instead of one device-scope add per record.  AUTO
- * (default) takes JOIN when no table budget is set, there are at most 2^31
- * records (beyond that the table was faster at 52 spin-orbitals) and they fit
- * within half of the free device memory and the word, else TABLE; a JOIN pass
- * whose hash group overflows its LDS table is redone by TABLE.  Forced JOIN that
- * does not fit returns SWCS_E_CAPACITY.  Both agree up to summation order.
+ * (default), with no table budget set, forms large states' gradients from the
+ * three-body density matrix of the stored determinants instead: pairs that
+ * share N_e - 3 electrons, found by a sort of alive * C(N_e, 3) records, then
+ * a dense contraction with the integrals (3 to 32 electrons; from 3e7 join
+ * records, more beyond 20 orbitals; not where a sample of the state shows more
+ * such pairs than join records; up to 1.3 GB at 26 orbitals plus 16 bytes a
+ * record, within half of the free device memory).  It serves screened subsets
+ * that would otherwise count their query keys as well.  Where it does not
+ * apply, AUTO takes JOIN when there are at most 2^31 records (beyond that the
+ * table was faster at 52 spin-orbitals) and they fit within half of the free
+ * device memory and the word, else TABLE; a JOIN pass whose hash group
+ * overflows its LDS table is redone by TABLE.  Forced JOIN that does not fit
+ * returns SWCS_E_CAPACITY.  All agree up to summation order.
  * Returns SWCS_E_INVALID for an unknown method. */
 enum { SWCS_POOL_AUTO = 0, SWCS_POOL_TABLE = 1, SWCS_POOL_JOIN = 2 };
 int swcs_set_pool_method(swcs_ctx* ctx, int method);
@@ -267,6 +275,8 @@ int swcs_pool_gradients(swcs_ctx* ctx, const int32_t* subset, int64_t n_subset, 
  * into batches also counts the new keys of its first batch (one more
  * synchronization) and restarts with fewer batches when the query set is
  * under half the estimate.
+ * A call that would count takes the density matrix instead where AUTO does
+ * (swcs_set_pool_method), with two synchronizations.
  * A bound-sized table is not checked on the host: if an insert found it full
  * (more than 4,096 probes at load <= 1/2), every entry of d_g is NaN.
  * Returns SWCS_E_OOM if even 4,096 batches do not fit the table memory. */
@@ -310,11 +320,12 @@ int swcs_compact(swcs_ctx* ctx, int64_t* stored);
 
 /* The last pool-gradient pass: *keys the key count its accumulation table
  * was sized for (after a full-pool pass: the distinct determinants sigma was
- * formed on), *table_slots the slots of one table (0 for a sort-and-join
- * pass, which has none), *batches the key-hash batches, *passes how many
- * times the pass ran (a pass whose table filled is repeated), *screened 1
- * for a subset pass.  Any pointer may be NULL; SWCS_E_STATE before the
- * first pass. */
+ * formed on; after a density-matrix pass: its records, the determinants'
+ * subsets of N_e - 3 electrons), *table_slots the slots of one table (0 for a
+ * sort-and-join or density-matrix pass, which has none), *batches the key-hash
+ * batches, *passes how many times the pass ran (a pass whose table filled is
+ * repeated), *screened 1 for a subset pass.  Any pointer may be NULL;
+ * SWCS_E_STATE before the first pass. */
 int swcs_pool_stats(swcs_ctx* ctx, double* keys, int64_t* table_slots, int32_t* batches,
                     int32_t* passes, int32_t* screened);
 

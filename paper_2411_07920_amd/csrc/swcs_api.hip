@@ -12,6 +12,7 @@
 #include "../../include/swcs.h"
 #include "conn_ops.h"
 #include "gate_ops.h"
+#include "rdm_ops.h"
 #include "swcs_internal.h"
 
 using namespace swcs;
@@ -172,7 +173,7 @@ struct swcs_ctx {
   DevBuf gacc, selected, ncut_state, qfilt;
   DevBuf partial, partial2, sigma, mu, work, seg_states, acc_tab, gbuf, subset_buf, scalars,
       exp_keys, exp_amps, exp_tmp_k, exp_tmp_v, sort_scratch, ctr_r, occ, sel_scratch, mlp_partial, mse_partial, hp_key, hp_val, hp_tk, hp_tv, diag, join_src,
-      join_w, join_j, join_bins;
+      join_w, join_j, join_bins, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs;
   int sigma_method = SWCS_SIGMA_AUTO;
   int pool_method = SWCS_POOL_AUTO;
   double ext_count = 0.0, ext_alive = 0.0;  // distinct external keys of the last full pool pass
@@ -192,7 +193,8 @@ struct swcs_ctx {
                      &partial, &partial2, &sigma, &mu, &work, &seg_states, &acc_tab, &gbuf,
                      &subset_buf, &scalars, &exp_keys, &exp_amps, &exp_tmp_k, &exp_tmp_v,
                      &sort_scratch, &ctr_r, &occ, &sel_scratch, &mlp_partial, &mse_partial,
-                     &hp_key, &hp_val, &hp_tk, &hp_tv, &diag, &qfilt, &join_src};
+                     &hp_key, &hp_val, &hp_tk, &hp_tv, &diag, &qfilt, &join_src, &join_w, &join_j,
+                     &join_bins, &rdm_g3, &rdm_g2, &rdm_vtab, &rdm_part, &rdm_bs};
     for (DevBuf* b : all) f(*b);
     for (auto& b : ckpt) f(b);
   }
@@ -326,7 +328,8 @@ size_t avail_bytes(swcs_ctx* c) {
 // when the state needs the memory, and allocated again on their next use.
 void release_scratch(swcs_ctx* c) {
   DevBuf* bufs[] = {&c->acc_tab, &c->hp_key, &c->hp_val, &c->hp_tk, &c->hp_tv, &c->sort_scratch,
-                    &c->exp_keys, &c->exp_amps, &c->exp_tmp_k, &c->exp_tmp_v, &c->qfilt, &c->join_src};
+                    &c->exp_keys, &c->exp_amps, &c->exp_tmp_k, &c->exp_tmp_v, &c->qfilt, &c->join_src, &c->join_w,
+                    &c->join_j, &c->rdm_g3, &c->rdm_part};
   for (DevBuf* b : bufs) b->release();
 }
 
@@ -1467,6 +1470,148 @@ static int norm2_enqueue(swcs_ctx* c, u64 n) {
   return SWCS_OK;
 }
 
+// Records per sort of the density-matrix pass (2 GB and as much again for the
+// sort); a state with more is taken in hash classes of its subsets.
+constexpr u64 kRdmMaxRecords = 1ULL << 28;
+// About this many determinants are looked at before the pass is taken.
+constexpr u64 kRdmSample = 1024;
+// Largest number of pairs (determinants within a triple excitation, counted
+// once per subset they share) per record of the join: a pair costs one
+// device-scope add, 18 G/s measured, a join record 14-22 G/s.  The pass is
+// slower than the join only where the state fills its sector so far that
+// every determinant has more neighbours than connections.
+constexpr double kRdmPairLimit = 1.0;
+
+// Join records (alive (C + 1)) from which AUTO takes the density matrix.  Its
+// cost on a small state is the contraction, n^7: 3.4 ms in all at 26 orbitals,
+// as long as a join of 6e7 records; below about 3e7 records (2 ms) the pass
+// has no lead at any n because of its fifteen small launches.
+static double rdm_min_records(int n) { return std::max(3.0e7, 0.0075 * std::pow((double)n, 7.0)); }
+
+// Pool gradients of the `count` operators d_subset (NULL: the whole pool) into
+// d_out from the three-body density matrix (k_rdm.hip).  Returns 1 when the
+// pass does not apply: another method or a table budget is set, fewer than
+// three electrons, a small state, too little memory, or so many pairs of
+// determinants within a triple excitation that the join or the table does
+// less work.  Synchronizes (the pair count decides).
+static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, int64_t count, const double* norm2,
+                         double* d_out) {
+  if (c->pool_method != SWCS_POOL_AUTO || c->table_budget > 0) return 1;
+  const int ne = c->na + c->nb;
+  if (ne < 3 || ne > kRdmMaxElectrons) return 1;
+  const double R_join = (double)h.alive * (double)(c->exc.total + 1);
+  if (R_join < rdm_min_records(c->n)) return 1;
+  // pairs of a state that is spread evenly over its sector: a state is at least
+  // this crowded, so a full sector needs no sample
+  {
+    const double a = c->na, b = c->nb, va = c->n - c->na, vb = c->n - c->nb;
+    auto c2 = [](double m) { return 0.5 * m * (m - 1.0); };
+    auto c3 = [](double m) { return m * (m - 1.0) * (m - 2.0) / 6.0; };
+    const double t1 = a * va + b * vb, t2 = c2(a) * c2(va) + c2(b) * c2(vb) + a * b * va * vb;
+    const double t3 = c3(a) * c3(va) + c3(b) * c3(vb) + c2(a) * c2(va) * b * vb + c2(b) * c2(vb) * a * va;
+    const double share = (double)h.alive / (double)c->sector;
+    if (0.5 * (double)h.alive * share * (t3 + (ne - 2.0) * t2 + c2(ne - 1.0) * t1) > kRdmPairLimit * R_join) return 1;
+  }
+  const u64 n = h.n, ntri = (u64)ne * (u64)(ne - 1) * (u64)(ne - 2) / 6, total = h.alive * ntri;
+  auto bits_for = [](u64 v) {
+    int b = 1;
+    while (b < 64 && (v >> b) != 0) ++b;
+    return b;
+  };
+  RdmFmt fm;
+  fm.bt = bits_for(ntri - 1);
+  fm.hb = std::min(48, 64 - fm.bt - bits_for(n - 1));
+  int nbatch = 1;
+  while (nbatch < 256 && total / (u64)nbatch > kRdmMaxRecords) nbatch *= 2;
+  // room for an uneven split of the subsets over the hash classes
+  const u64 cap = nbatch == 1 ? total : total / (u64)nbatch + total / (u64)nbatch / 8 + 65536;
+  const int sort_bits = cap < (1ULL << 19) ? 16 : 24;
+  if (fm.hb < sort_bits + 8 || total / (u64)nbatch > kRdmMaxRecords) return 1;
+  const u64 scr = radix_sort_scratch_elems(cap);
+  const size_t g3 = rdm_gamma_elems(c->n), part = rdm_part_elems(c->n), two = rdm_two_elems(c->n),
+               vt = rdm_vtab_elems(c->n);
+  const double need = 8.0 * ((double)g3 + (double)part + (double)two + (double)vt + 2.0 * (double)cap + (double)scr);
+  const double have = (double)(avail_bytes(c) + c->hp_key.bytes + c->hp_tk.bytes + c->sort_scratch.bytes +
+                               c->rdm_g3.bytes + c->rdm_part.bytes + c->rdm_g2.bytes + c->rdm_vtab.bytes);
+  if (need > 0.5 * have) return 1;
+  HIP_TRY(c, c->rdm_g3.ensure(g3 * 8), "alloc density matrix");
+  HIP_TRY(c, c->rdm_part.ensure(part * 8), "alloc density matrix");
+  HIP_TRY(c, c->rdm_g2.ensure(two * 8), "alloc density matrix");
+  HIP_TRY(c, c->rdm_vtab.ensure(vt * 8), "alloc density matrix");
+  HIP_TRY(c, c->rdm_bs.ensure((size_t)2 * c->n * c->n * 8), "alloc density matrix");
+  HIP_TRY(c, c->hp_key.ensure(cap * 8), "alloc subset records");
+  HIP_TRY(c, c->hp_tk.ensure(cap * 8), "alloc subset records");
+  HIP_TRY(c, c->sort_scratch.ensure(scr * 8), "alloc sort scratch");
+  double* gam = c->rdm_g3.as<double>();
+  u64* cursor = c->scalars.as<u64>() + 32;
+  // Decide by the pairs among a sample of the determinants, one in `share`.
+  {
+    double share = 8.0;
+    while (share < 1024.0 && ((double)h.alive / share > 2.0 * (double)kRdmSample ||
+                              (double)total / share > 0.5 * (double)cap)) share *= 2.0;
+    HIP_TRY(c, launch_fill_u32(cursor, 0u, 2, c->stream), "zero cursor");
+    HIP_TRY(c, launch_rdm_emit(c->st, n, ne, fm, 1, 0, (u64)share - 1, c->hp_key.as<u64>(), cap, cursor,
+                               grid_blocks(c, n, 32), c->stream), "subset records");
+    u64 R = 0;
+    HIP_TRY(c, hipMemcpyAsync(&R, cursor, 8, hipMemcpyDeviceToHost, c->stream), "copy");
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+    if (R > cap) {
+      HIP_TRY(c, launch_clear_flag(c->st.ctr, kFlagOverflow, c->stream), "clear flag");
+      return 1;
+    }
+    double pairs = 0.0;
+    if (R > 0) {
+      // records that share a bucket's sort bits by chance are no pairs; their
+      // expected number is taken off (16 bits keep it known to a percent of
+      // the limit for up to 2^22 records)
+      const int bits = R < (1ULL << 22) ? 16 : 24;
+      u64* sorted = c->hp_key.as<u64>();
+      HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, bits, c->sort_scratch.as<u64>(), scr, c->stream,
+                                 &sorted), "subset sort");
+      const int cgrid = grid_blocks(c, R, 256);
+      HIP_TRY(c, c->partial2.ensure((size_t)cgrid * 8), "alloc partials");
+      HIP_TRY(c, launch_rdm_count(sorted, R, bits, c->partial2.as<double>(), cgrid, c->stream), "pair count");
+      HIP_TRY(c, launch_reduce_partials(c->partial2.as<double>(), cgrid, cgrid, 1, c->scalars.as<double>() + 26,
+                                        c->stream), "pair count");
+      HIP_TRY(c, hipMemcpyAsync(&pairs, c->scalars.as<double>() + 26, 8, hipMemcpyDeviceToHost, c->stream), "copy");
+      HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+      pairs = std::max(0.0, pairs - 0.5 * (double)R * (double)R / (double)(1ULL << bits));
+    }
+    if (pairs * share * share > kRdmPairLimit * R_join) return 1;
+  }
+  HIP_TRY(c, launch_rdm_clear(c->n, gam, c->stream), "zero density matrix");
+  for (int b = 0; b < nbatch; ++b) {
+    HIP_TRY(c, launch_fill_u32(cursor, 0u, 2, c->stream), "zero cursor");
+    HIP_TRY(c, launch_rdm_emit(c->st, n, ne, fm, nbatch, b, 0, c->hp_key.as<u64>(), cap, cursor,
+                               grid_blocks(c, n, nbatch > 1 ? 4 : 32), c->stream), "subset records");
+    u64 R = total;
+    if (nbatch > 1) {
+      HIP_TRY(c, hipMemcpyAsync(&R, cursor, 8, hipMemcpyDeviceToHost, c->stream), "copy");
+      HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+      if (R > cap) {  // a class far above its share (many entries on few subsets)
+        HIP_TRY(c, launch_clear_flag(c->st.ctr, kFlagOverflow, c->stream), "clear flag");
+        return 1;
+      }
+    }
+    u64* sorted = c->hp_key.as<u64>();
+    HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, sort_bits, c->sort_scratch.as<u64>(), scr, c->stream,
+                               &sorted), "subset sort");
+    const u64 tiles = (R + 1023) / 1024;
+    HIP_TRY(c, launch_rdm_pairs(c->st, n, c->n, ne, fm, sort_bits, sorted, R, gam,
+                                (int)std::min<u64>(std::max<u64>(tiles, 1), (u64)c->num_cu * 16), c->stream), "pairs");
+  }
+  HIP_TRY(c, launch_rdm_diag(c->st, n, c->n, gam, (int)std::min<u64>((n + 7) / 8, (u64)c->num_cu), c->stream),
+          "diagonal");
+  HIP_TRY(c, launch_rdm_gradients(ints_view(c), c->eri.as<double>(), c->na, c->nb, gam, c->rdm_g2.as<double>(), c->rdm_vtab.as<double>(),
+                                  c->rdm_part.as<double>(), c->rdm_bs.as<double>(), c->ops.as<OpDesc>(), d_subset,
+                                  count, norm2, d_out, c->stream), "contraction");
+  c->ps_keys = (double)total;
+  c->ps_slots = 0;
+  c->ps_batches = nbatch;
+  c->ps_passes = 1;
+  return SWCS_OK;
+}
+
 // The screened query table is sized from a bound on its key count (no host
 // round trip) when that table stays below this size and no table budget is
 // set, otherwise from an exact count.
@@ -1480,11 +1625,23 @@ constexpr double kQueryBoundBytes = 512.0 * 1024 * 1024;
 // query table has to be sized by an exact count.
 static int mark_subset(swcs_ctx* c, const int* d_subset, int64_t n_subset);
 
-static int screened_gradients(swcs_ctx* c, u64 n, u64 alive, const int* d_subset, int64_t n_subset,
+static int screened_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, int64_t n_subset,
                               const double* norm2, double* d_out, bool may_sync) {
+  const u64 n = h.n, alive = h.alive;
+  const bool op_major = n_subset <= c->exc.total;
+  const double bound = std::min<double>((double)c->sector,
+                                        (double)alive * (double)(op_major ? n_subset : c->exc.total));
+  // a pass that would count its query keys synchronizes anyway; the density
+  // matrix of the state then gives any subset at the price of the whole pool
+  if (2.0 * bound * sizeof(AccSlot) > kQueryBoundBytes) {
+    int r = rdm_gradients(c, h, d_subset, n_subset, norm2, d_out);
+    if (r <= 0) {
+      c->ps_screened = 1;
+      return r;
+    }
+  }
   // a state too large for the join makes its scratch dead weight
   if (!join_fits_state(c, alive)) release_join_scratch(c);
-  const bool op_major = n_subset <= c->exc.total;
   const unsigned char* d_sel = nullptr;
   if (!op_major) {
     // the determinant-major passes test the operator flags and accumulate
@@ -1493,8 +1650,6 @@ static int screened_gradients(swcs_ctx* c, u64 n, u64 alive, const int* d_subset
     if (r) return r;
     d_sel = c->selected.as<unsigned char>();
   }
-  const double bound = std::min<double>((double)c->sector,
-                                        (double)alive * (double)(op_major ? n_subset : c->exc.total));
   u64 nq;
   bool counted = false, sampled = false;
   if (c->table_budget == 0 && 2.0 * bound * sizeof(AccSlot) <= kQueryBoundBytes) {
@@ -1686,7 +1841,7 @@ int swcs_pool_gradients_device(swcs_ctx* c, const int32_t* d_subset, int64_t n_s
   HIP_TRY(c, launch_sanitize_subset(d_subset, n_subset, c->K_pool, c->subset_buf.as<int>(), c->stream), "subset");
   const int* sub = c->subset_buf.as<int>();
   const double* norm2 = c->scalars.as<double>() + 2;
-  r = screened_gradients(c, h.n, h.alive, sub, n_subset, norm2, d_g, false);
+  r = screened_gradients(c, h, sub, n_subset, norm2, d_g, false);
   if (r) return r;
   HIP_TRY(c, launch_nan_invalid(d_subset, n_subset, c->K_pool, d_g, c->stream), "flag invalid");
   return SWCS_OK;
@@ -1824,8 +1979,16 @@ int swcs_pool_gradients(swcs_ctx* c, const int32_t* subset, int64_t n_subset, do
     d_subset = c->subset_buf.as<int>();
   }
   if (subset && 2 * n_subset < c->K_pool) {
-    r = screened_gradients(c, n, h.alive, d_subset, n_subset, norm2, c->gbuf.as<double>(), true);
+    r = screened_gradients(c, h, d_subset, n_subset, norm2, c->gbuf.as<double>(), true);
     if (r) return r;
+    HIP_TRY(c, hipMemcpyAsync(g_out, c->gbuf.p, (size_t)count * 8, hipMemcpyDeviceToHost, c->stream), "copy g");
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+    return SWCS_OK;
+  }
+  r = rdm_gradients(c, h, d_subset, count, norm2, c->gbuf.as<double>());
+  if (r <= 0) {
+    if (r) return r;
+    c->ps_screened = 0;
     HIP_TRY(c, hipMemcpyAsync(g_out, c->gbuf.p, (size_t)count * 8, hipMemcpyDeviceToHost, c->stream), "copy g");
     HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
     return SWCS_OK;

@@ -420,6 +420,23 @@ hipError_t launch_join_reduce(const DeviceState& st, const u64* recs, u64 R, con
                               JoinTerms terms, double* inserted, int grid, hipStream_t stream);
 // Sums the binned terms into g[K] (nothing when terms.lb < 0).
 hipError_t launch_join_terms(JoinTerms terms, double* gacc, long long K, hipStream_t stream);
+// Pool gradients from the three-body density matrix (k_rdm.hip; sizes in
+// doubles).
+struct RdmFmt;
+size_t rdm_gamma_elems(int n);
+size_t rdm_two_elems(int n);
+size_t rdm_vtab_elems(int n);
+size_t rdm_part_elems(int n);
+hipError_t launch_rdm_emit(const DeviceState& st, u64 n, int ne, RdmFmt fm, int nbatch, int batch, u64 smask,
+                           u64* recs, u64 cap, u64* cursor, int grid, hipStream_t stream);
+hipError_t launch_rdm_clear(int n_spatial, double* g3, hipStream_t stream);
+hipError_t launch_rdm_count(const u64* recs, u64 R, int sort_bits, double* partial, int grid, hipStream_t stream);
+hipError_t launch_rdm_pairs(const DeviceState& st, u64 n, int n_spatial, int ne, RdmFmt fm, int sort_bits,
+                            const u64* recs, u64 R, double* g3, int grid, hipStream_t stream);
+hipError_t launch_rdm_diag(const DeviceState& st, u64 n, int n_spatial, double* g3, int grid, hipStream_t stream);
+hipError_t launch_rdm_gradients(const Ints& I, const double* eri, int na, int nb, double* g3, double* g2, double* vtab, double* part, double* bs,
+                                const OpDesc* ops, const int* subset, long long count, const double* norm2,
+                                double* out, hipStream_t stream);
 hipError_t launch_sigma_push(const DeviceState& st, const Ints& I, const ExcSpace& E, u64 n,
                              AccSlot* tab, u64 tmask, int nbatch, int batch, double* inserted,
                              int grid, hipStream_t stream);
