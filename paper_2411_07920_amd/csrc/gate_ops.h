@@ -211,6 +211,19 @@ __device__ inline void ncut_pick(NcutState& st, int d) {
   }
 }
 
+// The same selection of a state in HBM (k_state.hip): 12-bit digits of |c|.
+// Zeroed before its first use; every selection leaves hist, ncand and ticket
+// zero again.
+struct NcutSelect {
+  unsigned skip;    // 1: keep everything (fewer than ncut alive, or chain stopped)
+  unsigned k;       // rank still to find inside the current prefix
+  unsigned prefix;  // leading bits of |c| found so far
+  unsigned ncand;   // entries with the whole prefix
+  unsigned ticket;  // blocks of the current launch that are done
+  unsigned pad[3];
+  unsigned hist[2][4096];
+};
+
 // ---------------------------------------------------------------- stores
 struct GlobalStore {
   u64* keys;

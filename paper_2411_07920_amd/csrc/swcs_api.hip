@@ -170,7 +170,7 @@ struct swcs_ctx {
   size_t ev_used = 0;
 
   // scratch
-  DevBuf gacc, selected, ncut_state, qfilt;
+  DevBuf gacc, selected, ncut_state, ncut_cand, qfilt;
   DevBuf partial, partial2, sigma, mu, work, seg_states, acc_tab, gbuf, subset_buf, scalars,
       exp_keys, exp_amps, exp_tmp_k, exp_tmp_v, sort_scratch, ctr_r, occ, sel_scratch, mlp_partial, mse_partial, hp_key, hp_val, hp_tk, hp_tv, diag, join_src,
       join_w, join_j, join_bins, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs;
@@ -188,7 +188,7 @@ struct swcs_ctx {
   u64 state_version = 1, diag_version = 0, norm_version = 0;
 
   template <class F> void for_each_buf(F&& f) {
-    DevBuf* all[] = {&h, &eri, &eri8, &J, &K, &fock, &ops, &opmap, &gacc, &selected, &ncut_state, &filt, &keys, &amps, &hash, &ctr, &ckpt_n, &ckpt_ptrs,
+    DevBuf* all[] = {&h, &eri, &eri8, &J, &K, &fock, &ops, &opmap, &gacc, &selected, &ncut_state, &ncut_cand, &filt, &keys, &amps, &hash, &ctr, &ckpt_n, &ckpt_ptrs,
                      &gate_tab, &gate_n_in, &gate_n_act,
                      &partial, &partial2, &sigma, &mu, &work, &seg_states, &acc_tab, &gbuf,
                      &subset_buf, &scalars, &exp_keys, &exp_amps, &exp_tmp_k, &exp_tmp_v,
@@ -538,6 +538,15 @@ int upload_ckpt_table(swcs_ctx* c, int nck) {
   return SWCS_OK;
 }
 
+// Buffers of the N_CUT selection for `states` arrays of at most n entries; the
+// select states are zeroed.
+int ncut_reserve(swcs_ctx* c, int states, u64 n) {
+  HIP_TRY(c, c->ncut_state.ensure((size_t)states * ncut_select_bytes()), "alloc ncut state");
+  HIP_TRY(c, c->ncut_cand.ensure((size_t)states * n * 4), "alloc ncut candidates");
+  HIP_TRY(c, launch_fill_u32(c->ncut_state.p, 0u, (u64)states * ncut_select_bytes() / 4, c->stream), "zero ncut state");
+  return SWCS_OK;
+}
+
 // Apply gates [0, M) of (ops, c, s) to the current state, with checkpoints
 // every `seg` gates when ckpt is requested.  A state that starts with at
 // most lds_chain_capacity() entries runs in one single-workgroup launch
@@ -601,6 +610,10 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     HIP_TRY(c, launch_store_counters(c->st.ctr, h, c->stream), "counters");
   }
   for (int attempt = 0; attempt < 64; ++attempt) {
+    if (ncut) {
+      int r = ncut_reserve(c, 1, c->st.cap);
+      if (r) return r;
+    }
     for (int64_t g = g0; g < M; ++g) {
       if (ckpt && g % c->seg == 0) {
         const int j = (int)(g / c->seg);
@@ -624,8 +637,8 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
       if (g == 0 && eps > 0.0)
         HIP_TRY(c, launch_prune_all(c->st, eps, grid_blocks(c, c->st.cap / 2, 256), c->stream), "prune");
       if (ncut)
-        HIP_TRY(c, launch_ncut(c->st.amps, c->st.keys, 0, c->st.ctr, c->ncut_state.as<NcutState>(), ncut,
-                               grid_blocks(c, c->st.cap / 2, 256), c->stream), "ncut");
+        HIP_TRY(c, launch_ncut(c->st.amps, 0, c->st.keys, 0, c->st.ctr, c->ncut_state.p, c->ncut_cand.as<unsigned>(), 0,
+                               ncut, c->st.cap, 1, c->stream), "ncut");
     }
     hipError_t e;
     Counters h = read_counters(c, &e);
@@ -1033,7 +1046,6 @@ static int apply_common(swcs_ctx* c, ChainSpec& sp, double eps, int64_t ncut, in
     if (e != hipSuccess) return hip_fail(c, e, "read counters");
     n_start = h0.n;
   }
-  HIP_TRY(c, c->ncut_state.ensure(sizeof(NcutState)), "alloc ncut state");
   int r = run_chain(c, sp.ops.data(), sp.cs.data(), sp.sn.data(), M, eps, (unsigned)ncut, from_reference,
                     n_start, &h, sp.kind.data(), sp.gen.data());
   if (r) return r;
@@ -2131,6 +2143,10 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
     HIP_TRY(c, c->partial2.ensure((size_t)M * grid * 8), "alloc partials");
     HIP_TRY(c, c->work.ensure(n * 8), "alloc working amplitudes");
     HIP_TRY(c, c->ctr_r.ensure((size_t)2 * seg * sizeof(u64)), "alloc log counters");
+    if (c->a_ncut) {
+      r = ncut_reserve(c, 1, n);
+      if (r) return r;
+    }
     double* W = c->work.as<double>();
     u64* lc = c->ctr_r.as<u64>();   // pair records per gate of the segment
     u64* sc = lc + seg;             // star records per gate
@@ -2150,8 +2166,8 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
                                         c->a_ncut ? 0.0 : c->a_eps, plog_of(t), lc + t,
                                         gate_grid(c, n, kReplayTile), c->stream), "replay");
         if (c->a_ncut)
-          HIP_TRY(c, launch_ncut(W, c->st.keys, n, nullptr, c->ncut_state.as<NcutState>(), (unsigned)c->a_ncut,
-                                 grid, c->stream), "ncut");
+          HIP_TRY(c, launch_ncut(W, 0, c->st.keys, n, nullptr, c->ncut_state.p, c->ncut_cand.as<unsigned>(), 0,
+                                 (unsigned)c->a_ncut, n, 1, c->stream), "ncut");
       }
       for (int t = len - 1; t >= 0; --t) {
         const int64_t g = g_lo + t;

@@ -347,9 +347,13 @@ hipError_t launch_prune_all(const DeviceState& st, double eps, int grid, hipStre
 hipError_t launch_hash_build_dev(const DeviceState& st, int grid, hipStream_t stream);
 hipError_t launch_filter_build(const DeviceState& st, u64 n, int grid, hipStream_t stream);
 hipError_t launch_reset_reference(const DeviceState& st, u64 ref, hipStream_t stream);
-struct NcutState;
-hipError_t launch_ncut(double* amps, const u64* keys, u64 n_host, Counters* ctr, NcutState* st,
-                       unsigned ncut, int grid, hipStream_t stream);
+// N_CUT selection on `states` amplitude arrays amps + y * stride of the same
+// keys: select holds ncut_select_bytes() per state, zeroed before the first
+// use; cand room for one index per entry (cand_stride apart).  n_most bounds
+// the stored entries for the launch grid.
+size_t ncut_select_bytes();
+hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Counters* ctr, void* select,
+                       unsigned* cand, u64 cand_stride, unsigned ncut, u64 n_most, int states, hipStream_t stream);
 int lds_chain_capacity();
 hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, int g0, int M, double eps,
                             int prune_first, double* const* ckpt, u64* ckpt_n, int seg,
