@@ -259,13 +259,12 @@ k_gen_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restri
     }
     if (gate_n_act && na) atomicAdd((unsigned long long*)gate_n_act, (unsigned long long)na);
     if (d != 0) atomicAdd((unsigned long long*)&ctr->dalive, (unsigned long long)d);
-    __threadfence();
+    device_atomics_done();
     const unsigned tk = atomicAdd(&ctr->ticket, 1u);
     is_last = (tk == gridDim.x - 1);
   }
   __syncthreads();
   if (is_last && threadIdx.x == 0) {
-    __threadfence();
     const u64 app = atomicAdd(&ctr->app, 0ULL);
     const long long da = (long long)atomicAdd((unsigned long long*)&ctr->dalive, 0ULL);
     const u64 alive = ctr->alive;
@@ -274,7 +273,6 @@ k_gen_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restri
     ctr->alive = (u64)((long long)alive + da);
     ctr->app = 0;
     ctr->dalive = 0;
-    __threadfence();
     ctr->ticket = 0;
   }
 }

@@ -174,13 +174,12 @@ k_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__
     for (int w = 0; w < kGateThreads / 64; ++w) d += s_wsum[w];
     if (gate_n_act && nact) atomicAdd((unsigned long long*)gate_n_act, (unsigned long long)nact);
     if (d != 0) atomicAdd((unsigned long long*)&ctr->dalive, (unsigned long long)d);
-    __threadfence();
+    device_atomics_done();
     const unsigned tk = atomicAdd(&ctr->ticket, 1u);
     is_last = (tk == gridDim.x - 1);
   }
   __syncthreads();
   if (is_last && threadIdx.x == 0) {
-    __threadfence();
     const u64 app = atomicAdd(&ctr->app, 0ULL);
     const long long da = (long long)atomicAdd((unsigned long long*)&ctr->dalive, 0ULL);
     const u64 alive = ctr->alive;
@@ -189,7 +188,6 @@ k_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__
     ctr->alive = (u64)((long long)alive + da);
     ctr->app = 0;
     ctr->dalive = 0;
-    __threadfence();
     ctr->ticket = 0;
   }
 }
@@ -321,7 +319,7 @@ __device__ inline unsigned ncut_prefix(u64 hi) { return (unsigned)(hi >> 39); }
 // needed: a device-scope fence writes the L2 back, and one in every wavefront
 // made each of these launches 40 us.
 __device__ inline bool ncut_last_block(unsigned* ticket, bool* s_last) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  device_atomics_done();
   __syncthreads();
   if (threadIdx.x == 0)
     *s_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;

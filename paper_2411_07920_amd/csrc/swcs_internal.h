@@ -153,6 +153,13 @@ struct Counters {
   u64 stop_gate;
 };
 
+// Waits until this wavefront's device-scope atomics (and its other memory
+// operations) are done.  Before a ticket that announces only such atomics this
+// is all the order the last block needs; a device-scope fence would also write
+// the L2 back, which cost each gate launch several microseconds and a launch of
+// many blocks tens.
+__device__ inline void device_atomics_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // kFlagOverflow: an append or table insert found no room (a bug guard: the
 // host sizes buffers so it cannot happen).  kFlagStopped: a gate found too
 // little capacity and did nothing; later gates of the chain skip too.
