@@ -298,8 +298,10 @@ def algorithmic_bytes(kname, wl, r):
     C = 2 * na * nv + 2 * comb(na, 2) * comb(nv, 2) + na * na * nv * nv
     if kname in ("chain_lds",):
         return 8.0 * n_in.sum()                      # whole chain per launch
-    if kname in ("gate", "gate_replay", "adjoint_rec"):
+    if kname == "gate":
         return 8.0 * n_in.sum() / M                  # one gate per launch
+    if kname in ("gate_replay", "adjoint_rec"):      # a launch covers several gates of the chain
+        return 8.0 * n_in.sum() / r["kernels"][kname]["launches_per_step"]
     if kname in ("adjoint_lds", "adjoint_replay_lds"):
         return 8.0 * n_in.sum()                      # reverse sweep / all segment replays
     if kname == "sigma_proj":

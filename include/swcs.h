@@ -351,8 +351,8 @@ enum {
   SWCS_K_SIGMA_PUSH = 4,    /* external sigma vector accumulation               */
   SWCS_K_POOL_CONTRACT = 5, /* pool-gradient contraction                        */
   SWCS_K_ADJOINT_LDS = 6,   /* reverse adjoint sweep in one LDS-resident workgroup */
-  SWCS_K_GATE_REPLAY = 7,   /* one replayed gate with pair logging (adjoint)    */
-  SWCS_K_ADJOINT_REC = 8,   /* one reverse step over logged pairs (adjoint)     */
+  SWCS_K_GATE_REPLAY = 7,   /* one replayed gate of each segment, pairs logged (adjoint) */
+  SWCS_K_ADJOINT_REC = 8,   /* reverse steps over logged pairs, one or a run of gates (adjoint) */
   SWCS_K_SIGMA_PUSH_INTO = 9, /* external sigma on the screened query set        */
   SWCS_K_CONTRACT_OPS = 10,  /* operator-major contraction of a small subset     */
   SWCS_K_HOLEPAIR = 11,      /* sigma_P pair evaluation inside hole-pair groups  */

@@ -57,6 +57,56 @@ struct StarRec {
   double xc, x1, x2;
 };
 
+// Logs of the gates g0 .. of a group of checkpoint segments (seg gates each, M
+// gates in all, from segment seg0): per gate, log_bytes with room for n
+// PairRecs and, where the chain has overlapping generators (kinds set), n
+// StarRecs behind them; counts[g - g0] and star_counts[g - g0] say how many.
+struct ReplayGroup {
+  char* logs;
+  size_t log_bytes;
+  u64* counts;
+  u64* star_counts;
+  const int* kinds;  // per gate of the chain: 1 = overlapping generator (NULL: none)
+  u64 n;
+  int seg, seg0, g0, M;
+  // gate `step` of the group's segment y, -1 past its end
+  __device__ int gate(int step, int y) const {
+    const int g = (seg0 + y) * seg + step;
+    return step < seg && g < M ? g : -1;
+  }
+  __device__ bool star(int g) const { return kinds && kinds[g]; }
+  __host__ __device__ PairRec* pairs(int g) const { return (PairRec*)(logs + (size_t)(g - g0) * log_bytes); }
+  __host__ __device__ StarRec* stars(int g) const { return (StarRec*)(pairs(g) + n); }
+};
+
+// Reverse step of one logged star: contributes mu . (G U x_old) over the
+// members to dE/dtheta (U = exp(theta G)), and mu <- U^T mu = exp(-theta G) mu
+// restricted to the members alive before the gate.
+template <class Mu>
+__device__ inline double adjoint_star(const StarRec& s, Mu& mu, const GenGate& g) {
+  const double al = (double)s.al, be = (double)s.be;
+  const bool aC = !is_dead(s.xc), a1 = !is_dead(s.x1), a2 = !is_dead(s.x2);
+  const double xc = aC ? s.xc : 0.0, x1 = a1 ? s.x1 : 0.0, x2 = a2 ? s.x2 : 0.0;
+  const double u = (al * x1 + be * x2) * g.rt;
+  const double nc = g.c2 * xc - g.s2 * u;
+  const double nu = g.s2 * xc + g.c2 * u;
+  const double du = nu - u;
+  const double n1 = x1 + al * (g.rt * du);
+  const double n2 = x2 + be * (g.rt * du);
+  const double mc = s.iC != 0xffffffffu ? mu.get(s.iC) : 0.0;
+  const double m1 = s.i1 != 0xffffffffu ? mu.get(s.i1) : 0.0;
+  const double m2 = s.i2 != 0xffffffffu ? mu.get(s.i2) : 0.0;
+  const double acc = mc * (-(al * n1 + be * n2)) + m1 * (al * nc) + m2 * (be * nc);
+  const double v = (al * m1 + be * m2) * g.rt;
+  const double bc = g.c2 * mc + g.s2 * v;
+  const double bv = -g.s2 * mc + g.c2 * v;
+  const double dv = bv - v;
+  if (s.iC != 0xffffffffu) mu.set(s.iC, aC ? bc : 0.0);
+  if (s.i1 != 0xffffffffu) mu.set(s.i1, a1 ? m1 + al * (g.rt * dv) : 0.0);
+  if (s.i2 != 0xffffffffu) mu.set(s.i2, a2 ? m2 + be * (g.rt * dv) : 0.0);
+  return acc;
+}
+
 // Store: key(i), amp(i), set_amp(i, v), find(key) -> index or -1.
 template <class Store>
 __device__ inline GateOut gate_entry(Store& S, u64 i, const OpDesc& op, double c, double sn,

@@ -277,15 +277,23 @@ k_gen_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restri
   }
 }
 
-// Replay inside the adjoint's recomputation: the forward update on a working
-// copy of the amplitudes over the final keys (every reachable key is stored,
-// so nothing is appended), logging one PairRec per updated pair and one
-// StarRec per updated star.
+// Replay inside the adjoint's recomputation, one gate of every segment of a
+// group (blockIdx.y) as k_gate_replay: the forward update on the segment's
+// working copy over the final keys (every reachable key is stored, so nothing
+// is appended), logging one PairRec per updated pair and one StarRec per
+// updated star.
 __global__ void __launch_bounds__(kGenThreads)
-k_gen_replay(const u64* __restrict__ keys, double* __restrict__ amps, const HashSlot* __restrict__ hash,
-             u64 hmask, u64 n, GenGate g, double eps, PairRec* __restrict__ plog, u64* __restrict__ pcount,
-             StarRec* __restrict__ slog, u64* __restrict__ scount, unsigned* __restrict__ flags) {
-  GlobalStore S{(u64*)keys, amps, (HashSlot*)hash, hmask};
+k_gen_replay(const u64* __restrict__ keys, double* __restrict__ work, const HashSlot* __restrict__ hash, u64 hmask,
+             u64 n, const GenGate* __restrict__ gens, double eps, ReplayGroup G, int step,
+             unsigned* __restrict__ flags) {
+  const int gi = G.gate(step, (int)blockIdx.y);
+  if (gi < 0 || !G.star(gi)) return;  // uniform
+  const GenGate g = gens[gi];
+  PairRec* __restrict__ plog = G.pairs(gi);
+  StarRec* __restrict__ slog = G.stars(gi);
+  u64* pcount = G.counts + (gi - G.g0);
+  u64* scount = G.star_counts + (gi - G.g0);
+  GlobalStore S{(u64*)keys, work + (u64)blockIdx.y * n, (HashSlot*)hash, hmask};
   const u64 stride = (u64)gridDim.x * kGenThreads;
   for (u64 base = (u64)blockIdx.x * kGenThreads; base < n; base += stride) {
     const u64 i = base + threadIdx.x;
@@ -301,39 +309,17 @@ k_gen_replay(const u64* __restrict__ keys, double* __restrict__ amps, const Hash
   }
 }
 
-// Reverse step of the logged stars: dE/dtheta += mu . (G U x_old) over the
-// members (U = exp(theta G)), and mu <- U^T mu = exp(-theta G) mu restricted
-// to the members alive before the gate.  Block sums are added to
-// partial[blockIdx.x] (written by the pairs' reverse step of the same gate).
+// Reverse step of the logged stars of one gate (see adjoint_star); block sums
+// are added to partial[blockIdx.x] (written by the pairs' reverse step of the
+// same gate).
 __global__ void __launch_bounds__(256)
 k_adjoint_star(const StarRec* __restrict__ slog, const u64* __restrict__ scount, double* __restrict__ mu,
                GenGate g, double* __restrict__ partial) {
+  GlobalMu m{mu};
   const u64 cnt = *scount;
   double acc = 0.0;
   const u64 stride = (u64)gridDim.x * blockDim.x;
-  for (u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x; r < cnt; r += stride) {
-    const StarRec s = slog[r];
-    const double al = (double)s.al, be = (double)s.be;
-    const bool aC = !is_dead(s.xc), a1 = !is_dead(s.x1), a2 = !is_dead(s.x2);
-    const double xc = aC ? s.xc : 0.0, x1 = a1 ? s.x1 : 0.0, x2 = a2 ? s.x2 : 0.0;
-    const double u = (al * x1 + be * x2) * g.rt;
-    const double nc = g.c2 * xc - g.s2 * u;
-    const double nu = g.s2 * xc + g.c2 * u;
-    const double du = nu - u;
-    const double n1 = x1 + al * (g.rt * du);
-    const double n2 = x2 + be * (g.rt * du);
-    const double mc = s.iC != 0xffffffffu ? mu[s.iC] : 0.0;
-    const double m1 = s.i1 != 0xffffffffu ? mu[s.i1] : 0.0;
-    const double m2 = s.i2 != 0xffffffffu ? mu[s.i2] : 0.0;
-    acc += mc * (-(al * n1 + be * n2)) + m1 * (al * nc) + m2 * (be * nc);
-    const double v = (al * m1 + be * m2) * g.rt;
-    const double bc = g.c2 * mc + g.s2 * v;
-    const double bv = -g.s2 * mc + g.c2 * v;
-    const double dv = bv - v;
-    if (s.iC != 0xffffffffu) mu[s.iC] = aC ? bc : 0.0;
-    if (s.i1 != 0xffffffffu) mu[s.i1] = a1 ? m1 + al * (g.rt * dv) : 0.0;
-    if (s.i2 != 0xffffffffu) mu[s.i2] = a2 ? m2 + be * (g.rt * dv) : 0.0;
-  }
+  for (u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x; r < cnt; r += stride) acc += adjoint_star(slog[r], m, g);
   __shared__ double sacc[256];
   sacc[threadIdx.x] = acc;
   __syncthreads();
@@ -351,11 +337,10 @@ hipError_t launch_gen_gate(const DeviceState& st, const GenGate& g, double eps, 
   return hipGetLastError();
 }
 
-hipError_t launch_gen_replay(const DeviceState& st, double* amps, u64 n, const GenGate& g, double eps,
-                             PairRec* plog, u64* pcount, StarRec* slog, u64* scount, int grid,
-                             hipStream_t stream) {
-  hipLaunchKernelGGL(k_gen_replay, dim3(grid), dim3(kGenThreads), 0, stream, st.keys, amps, st.hash,
-                     st.hmask, n, g, eps, plog, pcount, slog, scount, &st.ctr->flags);
+hipError_t launch_gen_replay(const DeviceState& st, double* work, u64 n, const GenGate* gens, double eps,
+                             const ReplayGroup& G, int step, int segs, int grid, hipStream_t stream) {
+  hipLaunchKernelGGL(k_gen_replay, dim3(grid, segs), dim3(kGenThreads), 0, stream, st.keys, work, st.hash,
+                     st.hmask, n, gens, eps, G, step, &st.ctr->flags);
   return hipGetLastError();
 }
 

@@ -161,6 +161,7 @@ struct swcs_ctx {
   std::vector<GateDesc> gate_tab_host;  // source of the last gate-table upload
   DevBuf gate_tab;    // GateDesc per gate of the last apply call
   DevBuf gate_n_in;   // u64 per gate of the last apply call
+  DevBuf gen_tab;     // GenGate and kind per gate, for adjoint replays of overlapping generators
   DevBuf gate_n_act;  // u64 per gate: stored entries the gate's operator acts on
   int64_t last_M = 0;
 
@@ -189,7 +190,7 @@ struct swcs_ctx {
 
   template <class F> void for_each_buf(F&& f) {
     DevBuf* all[] = {&h, &eri, &eri8, &J, &K, &fock, &ops, &opmap, &gacc, &selected, &ncut_state, &ncut_cand, &filt, &keys, &amps, &hash, &ctr, &ckpt_n, &ckpt_ptrs,
-                     &gate_tab, &gate_n_in, &gate_n_act,
+                     &gate_tab, &gen_tab, &gate_n_in, &gate_n_act,
                      &partial, &partial2, &sigma, &mu, &work, &seg_states, &acc_tab, &gbuf,
                      &subset_buf, &scalars, &exp_keys, &exp_amps, &exp_tmp_k, &exp_tmp_v,
                      &sort_scratch, &ctr_r, &occ, &sel_scratch, &mlp_partial, &mse_partial,
@@ -329,7 +330,7 @@ size_t avail_bytes(swcs_ctx* c) {
 void release_scratch(swcs_ctx* c) {
   DevBuf* bufs[] = {&c->acc_tab, &c->hp_key, &c->hp_val, &c->hp_tk, &c->hp_tv, &c->sort_scratch,
                     &c->exp_keys, &c->exp_amps, &c->exp_tmp_k, &c->exp_tmp_v, &c->qfilt, &c->join_src, &c->join_w,
-                    &c->join_j, &c->rdm_g3, &c->rdm_part};
+                    &c->join_j, &c->rdm_g3, &c->rdm_part, &c->seg_states, &c->work};
   for (DevBuf* b : bufs) b->release();
 }
 
@@ -2082,6 +2083,14 @@ int swcs_pool_gradients(swcs_ctx* c, const int32_t* subset, int64_t n_subset, do
   }
 }
 
+// Segments replayed side by side: as many as fit these bytes of logs and
+// working copies, at least one (a large state's gate fills the device by
+// itself, so there is nothing to gain from holding more).
+constexpr size_t kReplayGroupBytes = (size_t)4 << 30;
+// Records of a gate that one workgroup walks back (eight per thread); from
+// there a launch of many blocks is faster.
+constexpr u64 kWalkMaxRecords = 8192;
+
 int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   if (!c) return SWCS_E_INVALID;
   if (!c->ansatz_valid) return fail(c, SWCS_E_STATE, "no ansatz applied from the reference");
@@ -2111,16 +2120,10 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   HIP_TRY(c, c->gbuf.ensure((size_t)M * 8), "alloc dE");
   const bool lds = !c->a_has_star && n <= (u64)lds_chain_capacity();
   // Pair logs: at most one record per stored entry per gate, for every gate
-  // (single-workgroup path, all segments replayed at once) or for one
-  // segment at a time (HBM path); with overlapping generators each gate's
+  // (single-workgroup path, all segments replayed at once) or for a group of
+  // segments at a time (HBM path); with overlapping generators each gate's
   // slot also holds up to one star record per stored entry.
   const size_t gate_log_bytes = n * (sizeof(PairRec) + (c->a_has_star ? sizeof(StarRec) : 0));
-  HIP_TRY(c, c->seg_states.ensure((size_t)(lds ? M : seg) * gate_log_bytes), "alloc pair logs");
-  PairRec* logs = c->seg_states.as<PairRec>();
-  auto plog_of = [&](int t) { return (PairRec*)((char*)c->seg_states.p + (size_t)t * gate_log_bytes); };
-  auto slog_of = [&](int t) {
-    return (StarRec*)((char*)c->seg_states.p + (size_t)t * gate_log_bytes + n * sizeof(PairRec));
-  };
   HIP_TRY(c, launch_mu_init(c->st, c->sigma.as<double>(), n, nn, c->mu.as<double>(), c->stream), "mu init");
   if (lds) {
     // Segments replayed side by side (one workgroup each), then one
@@ -2128,6 +2131,8 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
     // last apply call is reused.
     int r2 = upload_ckpt_table(c, nseg);
     if (r2) return r2;
+    HIP_TRY(c, c->seg_states.ensure((size_t)M * gate_log_bytes), "alloc pair logs");
+    PairRec* logs = c->seg_states.as<PairRec>();
     HIP_TRY(c, c->ctr_r.ensure((size_t)M * sizeof(unsigned)), "alloc log counters");
     HIP_TRY(c, c->partial2.ensure(adjoint_lds_part_elems((int)M) * sizeof(double)), "alloc partials");
     TIMED(c, SWCS_K_ADJOINT_REPLAY_LDS, launch_adjoint_replay_lds(c->st.keys, (unsigned)n, c->gate_tab.as<GateDesc>(), (int)M, seg,
@@ -2138,47 +2143,88 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
                                   logs, c->ctr_r.as<unsigned>(), c->partial2.as<double>(), c->gbuf.as<double>(),
                                   c->stream), "adjoint");
   } else {
-    // Per segment: restore the checkpoint into a working copy, replay the
-    // segment's gates logging their active pairs, then walk the logs back.
-    HIP_TRY(c, c->partial2.ensure((size_t)M * grid * 8), "alloc partials");
-    HIP_TRY(c, c->work.ensure(n * 8), "alloc working amplitudes");
-    HIP_TRY(c, c->ctr_r.ensure((size_t)2 * seg * sizeof(u64)), "alloc log counters");
+    // Per group of segments, the last first: restore the checkpoints into
+    // working copies, replay the segments side by side (one launch per step
+    // of a segment) logging the active pairs of every gate, then walk the
+    // logs back.
+    const size_t seg_bytes = (size_t)seg * gate_log_bytes + n * 8;
+    const int gsegs = (int)std::min<size_t>((size_t)nseg, std::max<size_t>(1, kReplayGroupBytes / seg_bytes));
+    const u64 pstride = (u64)std::max(grid, 16);  // the walk's sixteen wavefronts
+    HIP_TRY(c, c->seg_states.ensure((size_t)gsegs * seg * gate_log_bytes), "alloc pair logs");
+    HIP_TRY(c, c->partial2.ensure((size_t)M * pstride * 8), "alloc partials");
+    HIP_TRY(c, launch_fill_u32(c->partial2.p, 0u, (u64)M * pstride * 2, c->stream), "zero partials");
+    HIP_TRY(c, c->work.ensure((size_t)gsegs * n * 8), "alloc working amplitudes");
+    HIP_TRY(c, c->ctr_r.ensure((size_t)2 * gsegs * seg * sizeof(u64)), "alloc log counters");
+    r = upload_ckpt_table(c, nseg);
+    if (r) return r;
     if (c->a_ncut) {
-      r = ncut_reserve(c, 1, n);
+      r = ncut_reserve(c, gsegs, n);
       if (r) return r;
     }
+    const GenGate* gens = nullptr;
+    const int* kinds = nullptr;
+    if (c->a_has_star) {
+      HIP_TRY(c, c->gen_tab.ensure((size_t)M * (sizeof(GenGate) + sizeof(int))), "alloc generator table");
+      int* d_kinds = (int*)((char*)c->gen_tab.p + (size_t)M * sizeof(GenGate));
+      HIP_TRY(c, hipMemcpyAsync(c->gen_tab.p, c->a_gen.data(), (size_t)M * sizeof(GenGate), hipMemcpyHostToDevice,
+                                c->stream), "copy generators");
+      HIP_TRY(c, hipMemcpyAsync(d_kinds, c->a_kind.data(), (size_t)M * sizeof(int), hipMemcpyHostToDevice, c->stream),
+              "copy generators");
+      gens = c->gen_tab.as<GenGate>();
+      kinds = d_kinds;
+    }
     double* W = c->work.as<double>();
-    u64* lc = c->ctr_r.as<u64>();   // pair records per gate of the segment
-    u64* sc = lc + seg;             // star records per gate
-    for (int j = nseg - 1; j >= 0; --j) {
-      const int64_t g_lo = (int64_t)j * seg;
-      const int64_t g_hi = std::min<int64_t>(M, g_lo + seg);
-      const int len = (int)(g_hi - g_lo);
-      HIP_TRY(c, launch_restore(W, c->ckpt[j].as<double>(), c->ckpt_n.as<u64>() + j, n, c->stream), "restore");
-      HIP_TRY(c, launch_fill_u32(lc, 0u, (u64)seg * 4, c->stream), "zero log counters");
-      for (int t = 0; t < len; ++t) {
-        const int64_t g = g_lo + t;
-        if (c->a_kind[g])
-          HIP_TRY(c, launch_gen_replay(c->st, W, n, c->a_gen[g], c->a_ncut ? 0.0 : c->a_eps, plog_of(t), lc + t,
-                                       slog_of(t), sc + t, grid_blocks(c, n, 256), c->stream), "generator replay");
-        else
-          TIMED(c, SWCS_K_GATE_REPLAY, launch_gate_replay(c->st, W, n, c->ops_host[c->a_ops[g]], c->a_c[g], c->a_s[g],
-                                        c->a_ncut ? 0.0 : c->a_eps, plog_of(t), lc + t,
-                                        gate_grid(c, n, kReplayTile), c->stream), "replay");
+    const double eps_r = c->a_ncut ? 0.0 : c->a_eps;
+    const GateDesc* gates = c->gate_tab.as<GateDesc>();
+    std::vector<u64> counts((size_t)2 * gsegs * seg);
+    for (int hi = nseg; hi > 0; hi -= gsegs) {
+      const int lo = std::max(0, hi - gsegs), segs = hi - lo;
+      const int g_lo = lo * seg, g_hi = (int)std::min<int64_t>(M, (int64_t)hi * seg), ng = g_hi - g_lo;
+      u64* lc = c->ctr_r.as<u64>();
+      const ReplayGroup G{(char*)c->seg_states.p, gate_log_bytes, lc, lc + (size_t)gsegs * seg, kinds, n,
+                          seg, lo, g_lo, (int)M};
+      HIP_TRY(c, launch_restore(W, c->ckpt_ptrs.as<double*>(), c->ckpt_n.as<u64>(), lo, segs, n, c->stream), "restore");
+      HIP_TRY(c, launch_fill_u32(lc, 0u, (u64)gsegs * seg * 4, c->stream), "zero log counters");
+      for (int t = 0; t < std::min(seg, ng); ++t) {
+        bool plain = false, star = false;
+        for (int j = 0; j < segs; ++j) {
+          const int g = (lo + j) * seg + t;
+          if (g < g_hi) (c->a_kind[(size_t)g] ? star : plain) = true;
+        }
+        if (star)
+          HIP_TRY(c, launch_gen_replay(c->st, W, n, gens, eps_r, G, t, segs, grid, c->stream), "generator replay");
+        if (plain)
+          TIMED(c, SWCS_K_GATE_REPLAY, launch_gate_replay(c->st, W, n, gates, eps_r, G, t, segs,
+                                                          gate_grid(c, n, kReplayTile), c->stream), "replay");
         if (c->a_ncut)
-          HIP_TRY(c, launch_ncut(W, 0, c->st.keys, n, nullptr, c->ncut_state.p, c->ncut_cand.as<unsigned>(), 0,
-                                 (unsigned)c->a_ncut, n, 1, c->stream), "ncut");
+          HIP_TRY(c, launch_ncut(W, n, c->st.keys, n, nullptr, c->ncut_state.p, c->ncut_cand.as<unsigned>(), n,
+                                 (unsigned)c->a_ncut, n, segs, c->stream), "ncut");
       }
-      for (int t = len - 1; t >= 0; --t) {
-        const int64_t g = g_lo + t;
-        TIMED(c, SWCS_K_ADJOINT_REC, launch_adjoint_rec(plog_of(t), lc + t, c->mu.as<double>(), c->a_c[g], c->a_s[g],
-                                      c->partial2.as<double>() + (size_t)g * grid, grid, c->stream), "reverse");
-        if (c->a_kind[g])
-          HIP_TRY(c, launch_adjoint_star(slog_of(t), sc + t, c->mu.as<double>(), c->a_gen[g],
-                                         c->partial2.as<double>() + (size_t)g * grid, grid, c->stream), "reverse stars");
+      // Gates of few records are walked back by one workgroup, the others by a
+      // launch each: the counts decide.
+      HIP_TRY(c, hipMemcpyAsync(counts.data(), lc, (size_t)2 * gsegs * seg * 8, hipMemcpyDeviceToHost, c->stream), "copy");
+      HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+      auto records = [&](int g) { return counts[(size_t)(g - g_lo)] + counts[(size_t)gsegs * seg + (size_t)(g - g_lo)]; };
+      for (int g = g_hi; g > g_lo;) {
+        int first = g;
+        while (first > g_lo && records(first - 1) <= kWalkMaxRecords) --first;
+        if (first < g) {
+          TIMED(c, SWCS_K_ADJOINT_REC, launch_adjoint_walk(G, gates, gens, first, g, c->mu.as<double>(),
+                                                           c->partial2.as<double>(), pstride, c->stream), "reverse");
+          g = first;
+          continue;
+        }
+        --g;
+        double* part = c->partial2.as<double>() + (size_t)g * pstride;
+        TIMED(c, SWCS_K_ADJOINT_REC, launch_adjoint_rec(G.pairs(g), lc + (g - g_lo), c->mu.as<double>(), c->a_c[(size_t)g],
+                                                        c->a_s[(size_t)g], part, grid, c->stream), "reverse");
+        if (c->a_kind[(size_t)g])
+          HIP_TRY(c, launch_adjoint_star(G.stars(g), G.star_counts + (g - g_lo), c->mu.as<double>(), c->a_gen[(size_t)g],
+                                         part, grid, c->stream), "reverse stars");
       }
     }
-    HIP_TRY(c, launch_reduce_partials(c->partial2.as<double>(), grid, grid, (int)M, c->gbuf.as<double>(), c->stream), "reduce");
+    HIP_TRY(c, launch_reduce_partials(c->partial2.as<double>(), (int)pstride, (int)pstride, (int)M, c->gbuf.as<double>(),
+                                      c->stream), "reduce");
   }
   std::vector<double> d_unit((size_t)M);
   HIP_TRY(c, hipMemcpyAsync(d_unit.data(), c->gbuf.p, (size_t)M * 8, hipMemcpyDeviceToHost, c->stream), "copy dE");

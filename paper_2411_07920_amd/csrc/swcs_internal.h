@@ -335,9 +335,9 @@ struct StarRec;
 hipError_t launch_gen_gate(const DeviceState& st, const GenGate& g, double eps, u64* gate_n_in,
                            unsigned gate_index, u64 max_keys, int grid, hipStream_t stream,
                            u64* gate_n_act = nullptr);
-hipError_t launch_gen_replay(const DeviceState& st, double* amps, u64 n, const GenGate& g, double eps,
-                             PairRec* plog, u64* pcount, StarRec* slog, u64* scount, int grid,
-                             hipStream_t stream);
+struct ReplayGroup;
+hipError_t launch_gen_replay(const DeviceState& st, double* work, u64 n, const GenGate* gens, double eps,
+                             const ReplayGroup& G, int step, int segs, int grid, hipStream_t stream);
 hipError_t launch_adjoint_star(const StarRec* slog, const u64* scount, double* mu, const GenGate& g,
                                double* partial, int grid, hipStream_t stream);
 hipError_t launch_fill_u32(void* p, unsigned v, u64 words, hipStream_t stream);
@@ -374,14 +374,15 @@ hipError_t launch_adjoint_reverse_lds(unsigned n, const GateDesc* gates, int M,
                                       const unsigned* logcnt, double* dE_part, double* dE,
                                       hipStream_t stream);
 size_t adjoint_lds_part_elems(int M);
-hipError_t launch_gate_replay(const DeviceState& st, double* amps, u64 n, const OpDesc& op,
-                             double c, double sn, double eps, PairRec* log, u64* log_count, int grid,
-                             hipStream_t stream);
+hipError_t launch_gate_replay(const DeviceState& st, double* work, u64 n, const GateDesc* gates, double eps,
+                             const ReplayGroup& G, int step, int segs, int grid, hipStream_t stream);
+hipError_t launch_adjoint_walk(const ReplayGroup& G, const GateDesc* gates, const GenGate* gens, int g_lo, int g_hi,
+                               double* mu, double* partial, u64 pstride, hipStream_t stream);
 hipError_t launch_adjoint_rec(const PairRec* log, const u64* log_count, double* mu, double c,
                               double sn, double* partial, int grid, hipStream_t stream);
 hipError_t launch_ckpt_save(const DeviceState& st, double* dst, u64* dst_n, int grid,
                             hipStream_t stream);
-hipError_t launch_restore(double* dst, const double* src, const u64* n_src, u64 n_total,
+hipError_t launch_restore(double* work, const double* const* ckpt, const u64* ckpt_n, int seg0, int segs, u64 n,
                           hipStream_t stream);
 hipError_t launch_mark_dead_range(double* amps, u64 lo, u64 hi, hipStream_t stream);
 hipError_t launch_sigma_proj(const DeviceState& st, const Ints& I, const ExcSpace& E, u64 n,
