@@ -5,6 +5,8 @@
 // scan over (digit, tile) in digit-major order, (3) a stable scatter in which
 // each 256-item row of a tile ranks its items by wave ballots on the digit
 // bits and a prefix over the four waves.  Only ceil(key_bits / 8) passes run.
+#include <algorithm>
+#include <initializer_list>
 #include <type_traits>
 
 #include "swcs_internal.h"
@@ -15,9 +17,13 @@ constexpr int kSortThreads = 256;
 constexpr int kSortRows = 16;
 constexpr int kSortTile = kSortThreads * kSortRows;
 
-// Rows of 256 items per tile: 16 for large sorts, 1 for small ones (more
-// tiles, shorter serial row loop per tile).
-inline int sort_rows(u64 count) { return count < (1ULL << 20) ? 1 : kSortRows; }
+// Rows of 256 items per tile: 16 for large sorts; 1 for small ones, whose
+// passes are launch-bound (more tiles, shorter serial row loop per tile); 4 in
+// between, where one-row tiles would scan and read back as many counts as
+// there are items.  150,000 (key, index) pairs, nine passes, with the scan
+// below: 275 us before, 178 now.
+constexpr u64 kSortMidMin = 1ULL << 16, kSortLargeMin = 1ULL << 20;
+inline int sort_rows(u64 count) { return count < kSortMidMin ? 1 : count < kSortLargeMin ? 4 : kSortRows; }
 
 // Tile handled by workgroup `block` of `nblocks`: workgroups are dispatched to
 // the eight XCDs in turn, so XCD x (blocks x, x + 8, ...) is given a
@@ -54,119 +60,102 @@ k_radix_hist(const u64* __restrict__ keys, u64 count, int shift, u64* __restrict
   counts[(u64)threadIdx.x * nblocks + b] = hist[threadIdx.x];
 }
 
-// Exclusive scans.  Tiles of kScanChunk elements are loaded coalesced into
-// LDS (kScanItems independent loads per thread), each thread scans
-// kScanItems consecutive elements, and a block scan joins the threads.
+// Exclusive scans.  A thread loads four consecutive elements (32 bytes), scans
+// them in registers, and the block scan joins the threads through wavefront
+// shuffles and the sixteen wavefront totals: one barrier.  Arrays of more than
+// one chunk take two launches of one block a chunk (8 us for 100,000 counts;
+// one block in a loop, with two barriers per doubling step: 34).
 constexpr int kScanThreads = 1024;
 constexpr int kScanItems = 4;
 constexpr u64 kScanChunk = (u64)kScanThreads * kScanItems;
-constexpr u64 kScanSingleBlock = 1ULL << 16;
 
+// Exclusive prefix of v over the block; *total = the block's sum.  part holds
+// one element per wavefront and is used once.
 __device__ inline u64 block_exclusive_1024(u64 v, u64* part, u64* total) {
-  part[threadIdx.x] = v;
-  __syncthreads();
-  for (int off = 1; off < kScanThreads; off <<= 1) {
-    const u64 w = (threadIdx.x >= (unsigned)off) ? part[threadIdx.x - off] : 0;
-    __syncthreads();
-    part[threadIdx.x] += w;
-    __syncthreads();
+  const int lane = __lane_id(), wave = (int)(threadIdx.x >> 6);
+  u64 incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const u64 w = __shfl_up(incl, off);
+    if (lane >= off) incl += w;
   }
-  const u64 incl = part[threadIdx.x];
-  *total = part[kScanThreads - 1];
-  return incl - v;
+  if (lane == 63) part[wave] = incl;
+  __syncthreads();
+  u64 before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kScanThreads / 64; ++w) {
+    const u64 t = part[w];
+    before += w < wave ? t : 0;
+    all += t;
+  }
+  *total = all;
+  return before + incl - v;
 }
 
-// Scans the tile data[base, base + kScanChunk) in place starting from
-// `carry`; returns the tile total.  Every thread of the block calls it.
-__device__ inline u64 scan_tile(u64* __restrict__ data, u64 len, u64 base, u64 carry, u64* stage,
-                                u64* part) {
-  // loads first (indices clamped, zeroed after), so the kScanItems loads of
-  // a thread are in flight together
-  u64 ld[kScanItems];
+// This thread's elements of a chunk, zero past the end.
+__device__ inline void scan_load(const u64* __restrict__ data, u64 len, u64 at, u64 (&v)[kScanItems]) {
+  if (at + kScanItems <= len) {
 #pragma unroll
-  for (int j = 0; j < kScanItems; ++j) {
-    const u64 i = base + (u64)j * kScanThreads + threadIdx.x;
-    ld[j] = data[i < len ? i : len - 1];
-  }
+    for (int j = 0; j < kScanItems; ++j) v[j] = data[at + j];
+  } else {
 #pragma unroll
-  for (int j = 0; j < kScanItems; ++j) {
-    const u64 i = base + (u64)j * kScanThreads + threadIdx.x;
-    stage[(u64)j * kScanThreads + threadIdx.x] = (i < len) ? ld[j] : 0;
+    for (int j = 0; j < kScanItems; ++j) v[j] = at + j < len ? data[at + j] : 0;
   }
-  __syncthreads();
-  u64 v[kScanItems], t = 0;
-  for (int j = 0; j < kScanItems; ++j) {
-    v[j] = stage[(u64)threadIdx.x * kScanItems + j];
-    t += v[j];
-  }
-  u64 total;
+}
+
+// In-place exclusive scan of data[len], len <= kScanChunk, with one block.
+__device__ inline void scan_chunk(u64* __restrict__ data, u64 len, u64 at, u64 carry, u64* part) {
+  u64 v[kScanItems], t = 0, total;
+  scan_load(data, len, at, v);
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j) t += v[j];
   u64 run = carry + block_exclusive_1024(t, part, &total);
+#pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
-    stage[(u64)threadIdx.x * kScanItems + j] = run;
+    if (at + j < len) data[at + j] = run;
     run += v[j];
   }
-  __syncthreads();
-  for (int j = 0; j < kScanItems; ++j) {
-    const u64 i = base + (u64)j * kScanThreads + threadIdx.x;
-    if (i < len) data[i] = stage[(u64)j * kScanThreads + threadIdx.x];
-  }
-  __syncthreads();
-  return total;
 }
 
-// In-place exclusive scan of data[len] with one block (short arrays, and the
-// chunk sums of the multi-block scan below).
 __global__ void __launch_bounds__(kScanThreads) k_scan_exclusive(u64* __restrict__ data, u64 len) {
-  __shared__ u64 stage[kScanChunk];
-  __shared__ u64 part[kScanThreads];
-  u64 carry = 0;
-  for (u64 base = 0; base < len; base += kScanChunk) carry += scan_tile(data, len, base, carry, stage, part);
+  __shared__ u64 part[kScanThreads / 64];
+  scan_chunk(data, len, (u64)threadIdx.x * kScanItems, 0, part);
 }
 
-// Multi-block exclusive scan: chunk sums, a scan of the sums, then each
-// block scans its chunk from its offset.
+// Multi-block exclusive scan: chunk sums, then each block adds up the sums of
+// the chunks before its own (at most a few loads per thread: 2^28 sorted items
+// have 4096 chunks of counts) and scans its chunk from there.
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_chunk_sums(const u64* __restrict__ data, u64 len, u64* __restrict__ sums) {
-  __shared__ u64 red[kScanThreads];
-  const u64 base = (u64)blockIdx.x * kScanChunk;
-  u64 ld[kScanItems];
+  __shared__ u64 part[kScanThreads / 64];
+  u64 v[kScanItems], s = 0, total;
+  scan_load(data, len, (u64)blockIdx.x * kScanChunk + (u64)threadIdx.x * kScanItems, v);
 #pragma unroll
-  for (int j = 0; j < kScanItems; ++j) {
-    const u64 i = base + (u64)j * kScanThreads + threadIdx.x;
-    ld[j] = data[i < len ? i : len - 1];  // clamped: the loads issue together
-  }
-  u64 s = 0;
-#pragma unroll
-  for (int j = 0; j < kScanItems; ++j)
-    if (base + (u64)j * kScanThreads + threadIdx.x < len) s += ld[j];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = kScanThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) sums[blockIdx.x] = red[0];
+  for (int j = 0; j < kScanItems; ++j) s += v[j];
+  (void)block_exclusive_1024(s, part, &total);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
 __global__ void __launch_bounds__(kScanThreads)
-k_scan_chunk_apply(u64* __restrict__ data, u64 len, const u64* __restrict__ offs) {
-  __shared__ u64 stage[kScanChunk];
-  __shared__ u64 part[kScanThreads];
-  (void)scan_tile(data, len, (u64)blockIdx.x * kScanChunk, offs[blockIdx.x], stage, part);
+k_scan_chunk_apply(u64* __restrict__ data, u64 len, const u64* __restrict__ sums) {
+  __shared__ u64 part[2][kScanThreads / 64];
+  u64 s = 0, before;
+  for (u64 i = threadIdx.x; i < blockIdx.x; i += kScanThreads) s += sums[i];
+  (void)block_exclusive_1024(s, part[0], &before);
+  scan_chunk(data, len, (u64)blockIdx.x * kScanChunk + (u64)threadIdx.x * kScanItems, before, part[1]);
 }
 
 // Extra scratch (u64 elements) that scan_exclusive needs for len elements.
-u64 scan_scratch_elems(u64 len) { return len <= kScanSingleBlock ? 0 : (len + kScanChunk - 1) / kScanChunk; }
+u64 scan_scratch_elems(u64 len) { return len <= kScanChunk ? 0 : (len + kScanChunk - 1) / kScanChunk; }
 
 // Exclusive scan of data[len] in place; sums has scan_scratch_elems(len) elements.
 void scan_exclusive(u64* data, u64 len, u64* sums, hipStream_t stream) {
-  if (len <= kScanSingleBlock) {
-    hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, stream, data, len);
+  if (len <= kScanChunk) {
+    hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(kScanThreads), 0, stream, data, len);
     return;
   }
   const u64 nb = (len + kScanChunk - 1) / kScanChunk;
   hipLaunchKernelGGL(k_scan_chunk_sums, dim3((unsigned)nb), dim3(kScanThreads), 0, stream, data, len, sums);
-  hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, stream, sums, nb);
   hipLaunchKernelGGL(k_scan_chunk_apply, dim3((unsigned)nb), dim3(kScanThreads), 0, stream, data, len,
                      (const u64*)sums);
 }
@@ -303,8 +292,8 @@ k_radix_scatter(const u64* __restrict__ keys_in, const V* __restrict__ vals_in, 
 }
 
 // Scratch (u64 elements) for sorting any count up to `count`: the tiling
-// switches from one-row to 16-row tiles at 2^20 items, so just below the
-// switch a sort needs more scratch than just above it.
+// switches to more rows per tile at two counts, and just below such a switch a
+// sort needs more scratch than just above it.
 static u64 radix_sort_scratch_exact(u64 count) {
   const u64 tile = (u64)kSortThreads * sort_rows(count);
   const u64 nblocks = (count + tile - 1) / tile;
@@ -314,7 +303,8 @@ static u64 radix_sort_scratch_exact(u64 count) {
 
 u64 radix_sort_scratch_elems(u64 count) {
   u64 r = radix_sort_scratch_exact(count);
-  if (count >= (1ULL << 20)) r = std::max(r, radix_sort_scratch_exact((1ULL << 20) - 1));
+  for (u64 at : {kSortMidMin, kSortLargeMin})
+    if (count >= at) r = std::max(r, radix_sort_scratch_exact(at - 1));
   return r;
 }
 
@@ -342,6 +332,9 @@ hipError_t radix_sort_impl(u64* keys, V* vals, u64* tmp_keys, V* tmp_vals, u64 c
     if (rows == 1)
       hipLaunchKernelGGL(k_radix_hist<1>, dim3(nblocks), dim3(kSortThreads), 0, stream, kin, count,
                          shift, scratch, nblocks);
+    else if (rows == 4)
+      hipLaunchKernelGGL(k_radix_hist<4>, dim3(nblocks), dim3(kSortThreads), 0, stream, kin, count,
+                         shift, scratch, nblocks);
     else
       hipLaunchKernelGGL(k_radix_hist<kSortRows>, dim3(nblocks), dim3(kSortThreads), 0, stream, kin,
                          count, shift, scratch, nblocks);
@@ -349,6 +342,9 @@ hipError_t radix_sort_impl(u64* keys, V* vals, u64* tmp_keys, V* tmp_vals, u64 c
     // the scatter tile equals the histogram tile (kSortThreads * rows items)
     if (rows == 1)
       hipLaunchKernelGGL((k_radix_scatter<kSortThreads, 1, V>), dim3(nblocks), dim3(kSortThreads), 0, stream,
+                         kin, vin, count, shift, scratch, nblocks, kout, vout);
+    else if (rows == 4)
+      hipLaunchKernelGGL((k_radix_scatter<2 * kSortThreads, 2, V>), dim3(nblocks), dim3(2 * kSortThreads), 0, stream,
                          kin, vin, count, shift, scratch, nblocks, kout, vout);
     else
       hipLaunchKernelGGL((k_radix_scatter<2 * kSortThreads, kSortRows / 2, V>), dim3(nblocks),
@@ -800,7 +796,7 @@ hipError_t launch_select(const float* score, const uint32_t* rnd, long long K, l
   }
   const int nblocks = (int)((K + kSortTile - 1) / kSortTile);
   hipLaunchKernelGGL(k_flag_count, dim3(nblocks), dim3(kSortThreads), 0, stream, flags, K, hist);
-  hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, stream, hist, (u64)nblocks);
+  scan_exclusive(hist, (u64)nblocks, hist + nblocks, stream);
   hipLaunchKernelGGL(k_flag_scatter, dim3(nblocks), dim3(kSortThreads), 0, stream, flags, K, hist,
                      idx);
   return hipGetLastError();
