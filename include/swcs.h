@@ -138,8 +138,11 @@ int swcs_set_table_budget(swcs_ctx* ctx, int64_t bytes);
  * (states of at most 4,096 stored determinants; larger ones fall back to
  * AUTO's choice among the others) tests every pair of stored determinants in
  * LDS by popcount.  AUTO (default) takes PAIRS when the state
- * fits and n <= 8 C, otherwise HOLE_PAIRS when the probe count would exceed
- * 3e7, otherwise ENUMERATE.  All give the same sigma up to summation order.
+ * fits and n <= 8 C, otherwise ENUMERATE up to 3e7 probes, otherwise one sort
+ * of the determinants by each spin's occupation and pair tests within these
+ * groups (40 bytes per determinant and spin of device memory), or HOLE_PAIRS
+ * where a sample finds the groups large.  All give the same sigma up to
+ * summation order.
  * Returns SWCS_E_INVALID for an unknown method. */
 enum { SWCS_SIGMA_AUTO = 0, SWCS_SIGMA_ENUMERATE = 1, SWCS_SIGMA_HOLE_PAIRS = 2, SWCS_SIGMA_PAIRS = 3 };
 int swcs_set_sigma_method(swcs_ctx* ctx, int method);

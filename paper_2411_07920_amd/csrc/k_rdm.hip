@@ -150,12 +150,12 @@ k_rdm_emit(const u64* __restrict__ keys, const double* __restrict__ amps, u64 n,
       const int j = __ffsll((long long)m) - 1;
       const u64 D = rdm_lane(key, j), d = ch * kRdmEmitChunk + (u64)j;
       if (lane < ne) s_bit[wave][lane] = 1ULL << rdm_select(D, (unsigned)lane);
-      __builtin_amdgcn_wave_barrier();  // read by this wavefront only, after its writes
+      wave_sync();  // read by this wavefront only, after its writes
       unsigned cls;
       for (unsigned t = (unsigned)lane; t < ntri; t += 64)
         recs[base + t] = rdm_emit_record(fm, d, D, s_bit[wave], s_tri, t, &cls);
       base += ntri;
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
     }
   }
 }
@@ -202,7 +202,7 @@ k_rdm_emit_class(const u64* __restrict__ keys, const double* __restrict__ amps, 
     const bool live = d < n && !is_dead(amps[d < n ? d : 0]);
     const u64 D = live ? keys[d] : 0ULL;
     if (live && lane < ne) s_bit[wave][lane] = 1ULL << rdm_select(D, (unsigned)lane);
-    __builtin_amdgcn_wave_barrier();  // read by this wavefront only, after its writes
+    wave_sync();  // read by this wavefront only, after its writes
     for (unsigned t0 = 0; t0 < ntri; t0 += 64) {
       const unsigned t = t0 + (unsigned)lane;
       bool put = live && t < ntri;
@@ -224,7 +224,7 @@ k_rdm_emit_class(const u64* __restrict__ keys, const double* __restrict__ amps, 
         round = 0;
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
   flush();
 }
@@ -495,7 +495,7 @@ k_rdm_diag(const u64* __restrict__ keys, const double* __restrict__ amps, u64 n,
     const int na = __popcll(D & amask), nb = __popcll(D & ~amask);
     if (lane < na) s_occ[wave][0][lane] = rdm_select(D & amask, (unsigned)lane) >> 1;
     if (lane < nb) s_occ[wave][1][lane] = rdm_select(D & ~amask, (unsigned)lane) >> 1;
-    __builtin_amdgcn_wave_barrier();  // read by this wavefront only, after its writes
+    wave_sync();  // read by this wavefront only, after its writes
     const int* ox = s_occ[wave][sp];
     const int* oy = s_occ[wave][1 - sp];
     const int nx = sp ? nb : na, ny = sp ? na : nb;
@@ -521,7 +521,7 @@ k_rdm_diag(const u64* __restrict__ keys, const double* __restrict__ amps, u64 n,
         if (id < len) atomicAdd(&s_diag[id], w);
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
   }
   __syncthreads();

@@ -174,7 +174,8 @@ struct swcs_ctx {
   DevBuf gacc, selected, ncut_state, ncut_cand, qfilt;
   DevBuf partial, partial2, sigma, mu, work, seg_states, acc_tab, gbuf, subset_buf, scalars,
       exp_keys, exp_amps, exp_tmp_k, exp_tmp_v, sort_scratch, ctr_r, occ, sel_scratch, mlp_partial, mse_partial, hp_key, hp_val, hp_tk, hp_tv, diag, join_src,
-      join_w, join_j, join_bins, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs;
+      join_w, join_j, join_bins, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs,
+      str_rec, str_key, str_val, str_oth, str_tab;
   int sigma_method = SWCS_SIGMA_AUTO;
   int pool_method = SWCS_POOL_AUTO;
   double ext_count = 0.0, ext_alive = 0.0;  // distinct external keys of the last full pool pass
@@ -195,7 +196,8 @@ struct swcs_ctx {
                      &subset_buf, &scalars, &exp_keys, &exp_amps, &exp_tmp_k, &exp_tmp_v,
                      &sort_scratch, &ctr_r, &occ, &sel_scratch, &mlp_partial, &mse_partial,
                      &hp_key, &hp_val, &hp_tk, &hp_tv, &diag, &qfilt, &join_src, &join_w, &join_j,
-                     &join_bins, &rdm_g3, &rdm_g2, &rdm_vtab, &rdm_part, &rdm_bs};
+                     &join_bins, &rdm_g3, &rdm_g2, &rdm_vtab, &rdm_part, &rdm_bs, &str_rec, &str_key,
+                     &str_val, &str_oth, &str_tab};
     for (DevBuf* b : all) f(*b);
     for (auto& b : ckpt) f(b);
   }
@@ -330,7 +332,8 @@ size_t avail_bytes(swcs_ctx* c) {
 void release_scratch(swcs_ctx* c) {
   DevBuf* bufs[] = {&c->acc_tab, &c->hp_key, &c->hp_val, &c->hp_tk, &c->hp_tv, &c->sort_scratch,
                     &c->exp_keys, &c->exp_amps, &c->exp_tmp_k, &c->exp_tmp_v, &c->qfilt, &c->join_src, &c->join_w,
-                    &c->join_j, &c->rdm_g3, &c->rdm_part, &c->seg_states, &c->work};
+                    &c->join_j, &c->rdm_g3, &c->rdm_part, &c->seg_states, &c->work, &c->str_rec, &c->str_key,
+                    &c->str_val, &c->str_oth, &c->str_tab};
   for (DevBuf* b : bufs) b->release();
 }
 
@@ -1249,6 +1252,14 @@ int swcs_get_state(swcs_ctx* c, uint64_t* keys, double* amps, int64_t cap, int64
 // probes); hole-pair grouping sorts n * C(N_e, 2) records instead.  The
 // automatic choice takes grouping once the probe count passes this bound.
 constexpr double kHolePairProbes = 3.0e7;
+// Pair tests of the spin-string pass per hole-pair record up to which AUTO takes
+// it.  A test costs about a tenth of a picosecond to a picosecond over the
+// device, a record's share of emit, sort and group scan 60 to 100.  Strings
+// against hole pairs, tests per record: 2e6 determinants of (26 orbitals, 8 + 8
+// electrons) 4.8 to 9.5 ms at 3; 1e6 of (18, 6 + 6) 3.1 to 5.3 at 62; 3e5 of
+// (14, 5 + 5) 1.9 to 3.0 at 158; 2e5 clustered of (26, 8 + 8) 2.6 to 6.1 at 411;
+// 1e6 of (14, 5 + 5) 16.9 to 20.1 at 523.
+constexpr double kStringTests = 500.0;
 
 static bool use_holepair(swcs_ctx* c, u64 alive) {
   const int ne = c->na + c->nb;
@@ -1279,8 +1290,76 @@ static int diag_enqueue(swcs_ctx* c, u64 n) {
   return SWCS_OK;
 }
 
+// sigma_P by spin strings into c->sigma (k_strings.hip); returns 1 when
+// hole-pair grouping is the better choice: the entries share so few strings that
+// the groups' pair tests outweigh its sort.  Synchronizes for that decision,
+// which rests on a sample (20 us; deciding after the sorts cost a state that is
+// turned away 200).
+static int string_sigma(swcs_ctx* c, const Counters& h) {
+  const u64 n = h.n, alive = h.alive;
+  if (c->sigma_method != SWCS_SIGMA_AUTO || alive == 0 || n >= (1ULL << 31)) return 1;
+  const int ne = c->na + c->nb;
+  const int occ[2] = {c->na, c->nb};
+  const int shift = (c->n + 1 + 7) / 8 * 8;  // whole digits: the sort never reads the index
+  if (shift < 64 && ((n - 1) >> (64 - shift)) != 0) return 1;
+  // Tests per determinant, from the sampled chance that two share a string.
+  // The spin whose strings lead the (1, 1) pass is the one with fewer tests: a
+  // string's neighbours are at most nocc nvir groups of about its own size.
+  unsigned sample[kStrSampleBlocks][5];
+  HIP_TRY(c, c->partial.ensure(sizeof(sample)), "alloc partial");
+  HIP_TRY(c, launch_str_sample(c->st, n, c->partial.as<unsigned>(), c->stream), "sample strings");
+  const unsigned blocks = str_sample_blocks(n);
+  HIP_TRY(c, hipMemcpyAsync(sample, c->partial.p, blocks * sizeof(sample[0]), hipMemcpyDeviceToHost, c->stream), "copy");
+  HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+  double hits[2] = {0.0, 0.0}, cols = 0.0, self = 0.0;
+  for (unsigned b = 0; b < blocks; ++b) {
+    for (int s = 0; s < 2; ++s) hits[s] += sample[b][s];
+    cols += sample[b][2];
+    self += sample[b][4];
+  }
+  const double pairs = std::max(1.0, cols * sample[0][3] - self);
+  double own[2], adj[2];
+  for (int s = 0; s < 2; ++s) {
+    own[s] = 1.0 + hits[s] / pairs * (double)(alive - 1);
+    adj[s] = own[s] * (double)(occ[s] * (c->n - occ[s]));
+  }
+  const int lead = adj[0] <= adj[1] ? 0 : 1;
+  if (adj[lead] + own[0] + own[1] > kStringTests * (double)(ne * (ne - 1) / 2)) return 1;
+  const u64 scr = radix_sort_scratch_elems(n);
+  u64 slots[2];  // strings that can occur, at load 1/2
+  for (int s = 0; s < 2; ++s)
+    slots[s] = next_pow2(2 * std::max<u64>(32, std::min<u64>(alive, binomial_u64(c->n, occ[s]))));
+  const int grid = grid_blocks(c, alive, 256);
+  // per spin: records and their sort buffer, then keys, amplitudes and strings
+  // in sorted order
+  HIP_TRY(c, c->str_rec.ensure(4 * n * 8), "alloc strings");
+  HIP_TRY(c, c->str_key.ensure(2 * alive * 8), "alloc strings");
+  HIP_TRY(c, c->str_val.ensure(2 * alive * 8), "alloc strings");
+  HIP_TRY(c, c->str_oth.ensure(2 * alive * 4), "alloc strings");
+  HIP_TRY(c, c->str_tab.ensure((slots[0] + slots[1]) * str_slot_bytes()), "alloc strings");
+  HIP_TRY(c, c->sort_scratch.ensure(scr * 8), "alloc sort scratch");
+  u64* rec[2] = {c->str_rec.as<u64>(), c->str_rec.as<u64>() + n};
+  u64* tmp[2] = {c->str_rec.as<u64>() + 2 * n, c->str_rec.as<u64>() + 3 * n};
+  void* tab[2] = {c->str_tab.p, (char*)c->str_tab.p + slots[0] * str_slot_bytes()};
+  HIP_TRY(c, launch_str_emit(c->st, n, c->n, shift, rec[0], rec[1], grid_blocks(c, n, 256), c->stream), "strings");
+  for (int s = 0; s < 2; ++s) {
+    HIP_TRY(c, radix_sort_keys(rec[s], tmp[s], n, shift, c->sort_scratch.as<u64>(), scr, c->stream, &rec[s]), "sort");
+    HIP_TRY(c, launch_str_groups(c->st, rec[s], alive, c->n, shift, s, c->str_key.as<u64>() + s * alive,
+                                 c->str_val.as<double>() + s * alive, c->str_oth.as<unsigned>() + s * alive, tab[s],
+                                 slots[s], grid, c->stream), "groups");
+  }
+  const Ints I = ints_view(c);
+  HIP_TRY(c, launch_sigma_diag(c->st, I, n, c->sigma.as<double>(), grid_blocks(c, n, 256), c->stream), "diagonal sigma");
+  for (int s = 0; s < 2; ++s)
+    TIMED(c, SWCS_K_HOLEPAIR,
+          launch_str_sigma(I, rec[s], alive, shift, occ[s], c->str_key.as<u64>() + s * alive,
+                           c->str_val.as<double>() + s * alive, c->str_oth.as<unsigned>() + s * alive, tab[s], slots[s],
+                           s == lead, c->sigma.as<double>(), grid_blocks(c, alive, 32), c->stream), "string pairs");
+  return SWCS_OK;
+}
+
 // sigma_P over the stored entries; (numer, norm2) land in scalars[0..1] on
-// the device, without synchronizing.
+// the device (synchronizing only where a pass has to size or choose itself).
 static int energy_enqueue(swcs_ctx* c, u64 n) {
   const int grid = sigma_grid(c, n);
   int rd = diag_enqueue(c, n);
@@ -1298,7 +1377,15 @@ static int energy_enqueue(swcs_ctx* c, u64 n) {
     HIP_TRY(c, launch_reduce_partials(c->partial.as<double>(), pgrid, pgrid, 2, c->scalars.as<double>(), c->stream), "reduce");
     return SWCS_OK;
   }
-  if (n > 0 && n < (1ULL << 32) && use_holepair(c, h.alive)) {
+  int by_strings = 1;
+  if (n > 0 && use_holepair(c, h.alive)) {
+    by_strings = string_sigma(c, h);
+    if (by_strings < 0) return by_strings;
+  }
+  if (by_strings == SWCS_OK) {
+    HIP_TRY(c, c->partial.ensure((size_t)2 * grid * 8), "alloc partial");
+    HIP_TRY(c, launch_sigma_dots(c->st, c->sigma.as<double>(), n, c->partial.as<double>(), grid, c->stream), "dots");
+  } else if (n > 0 && n < (1ULL << 32) && use_holepair(c, h.alive)) {
     const int ne = c->na + c->nb;
     const u64 total = n * ((u64)ne * (u64)(ne - 1) / 2);
     // Segments of the three removal classes (alpha-alpha, alpha-beta,

@@ -160,6 +160,14 @@ struct Counters {
 // many blocks tens.
 __device__ inline void device_atomics_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Orders a wavefront's own LDS accesses (its LDS operations execute in order;
+// this keeps the compiler from moving or reusing them across the point).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // kFlagOverflow: an append or table insert found no room (a bug guard: the
 // host sizes buffers so it cannot happen).  kFlagStopped: a gate found too
 // little capacity and did nothing; later gates of the chain skip too.
@@ -399,6 +407,17 @@ hipError_t launch_sigma_diag(const DeviceState& st, const Ints& I, u64 n, double
 hipError_t launch_holepair_sigma(const DeviceState& st, const Ints& I, int na, u64 n, const u64* skey,
                                  const unsigned* sidx, int shift, u64 total, int cls, double* sigma, int grid,
                                  hipStream_t stream);
+// sigma_P by spin strings (k_strings.hip).
+size_t str_slot_bytes();
+constexpr unsigned kStrSampleBlocks = 64;  // lines of five counts
+unsigned str_sample_blocks(u64 cnt);
+hipError_t launch_str_sample(const DeviceState& st, u64 cnt, unsigned* out, hipStream_t stream);
+hipError_t launch_str_emit(const DeviceState& st, u64 cnt, int n, int shift, u64* ra, u64* rb, int grid, hipStream_t stream);
+hipError_t launch_str_groups(const DeviceState& st, const u64* rec, u64 alive, int n, int shift, int spin, u64* skey,
+                             double* sval, unsigned* oth, void* tab, u64 slots, int grid, hipStream_t stream);
+hipError_t launch_str_sigma(const Ints& I, const u64* rec, u64 alive, int shift, int nocc, const u64* skey,
+                            const double* sval, const unsigned* oth, const void* tab, u64 slots, bool adj,
+                            double* sigma, int grid, hipStream_t stream);
 hipError_t launch_sigma_dots(const DeviceState& st, const double* sigma, u64 n, double* partial,
                              int grid, hipStream_t stream);
 hipError_t launch_mu_init(const DeviceState& st, const double* sigma, u64 n, const double* nn,
