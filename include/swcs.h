@@ -164,9 +164,11 @@ int swcs_set_sigma_method(swcs_ctx* ctx, int method);
  * three-body density matrix of the stored determinants instead: pairs that
  * share N_e - 3 electrons, found by a sort of alive * C(N_e, 3) records, then
  * a dense contraction with the integrals (3 to 32 electrons; from 3e7 join
- * records, more beyond 20 orbitals; not where a sample of the state shows more
- * such pairs than join records; up to 1.3 GB at 26 orbitals plus 16 bytes a
- * record, within half of the free device memory).  It serves screened subsets
+ * records, more beyond 20 orbitals; not where a sample of the state shows so
+ * many such pairs -- more than join records, or some ten times as many where
+ * another 16 bytes a record fit -- that the join does less work; up to 1.3 GB at
+ * 26 orbitals plus 16 bytes a record, within half of the free device memory).
+ * It serves screened subsets
  * that would otherwise count their query keys as well.  Where it does not
  * apply, AUTO takes JOIN when there are at most 2^31 records (beyond that the
  * table was faster at 52 spin-orbitals) and they fit within half of the free

@@ -24,7 +24,8 @@
 //                   the subset;
 //         sort   -- radix sort on low hash bits (k_sort.hip);
 //         pairs  -- records of one subset are the entries that share it:
-//                   psi_D psi_D' into one triangle of Gamma for each pair;
+//                   psi_D psi_D' into one triangle of Gamma for each pair; a
+//                   state with more pairs than records sums the rows in LDS;
 //         diag   -- Gamma(A, A), every subset's own square, summed in LDS;
 //         mirror -- the other triangle;
 //         two    -- the two-body matrix as the partial trace of Gamma;
@@ -37,7 +38,7 @@
 // accumulation table (beyond): 39,484 determinants of 52 spin-orbitals and 16
 // electrons 69.6 -> 4.8 ms, 137,595 of them 480 -> 7.8 ms (813 where three
 // contexts share the memory and the table is split), 224,982 of 30
-// spin-orbitals and 11 electrons 67.7 -> 21.1 ms; 6 % of the pool on the first
+// spin-orbitals and 11 electrons 67.7 -> 6.2 ms; 6 % of the pool on the first
 // state 38.6 -> 4.6 ms.  Errors against 64-bit references are those of the
 // other paths (2.6e-14, 1.5e-14 relative).
 #include <algorithm>
@@ -391,6 +392,216 @@ k_rdm_pairs(const u64* __restrict__ recs, u64 R, RdmFmt fm, int sort_bits, int n
         unsafeAtomicAdd(&g[(u64)lo * ld + hi], vi * o.val);
       }
     }
+  }
+}
+
+// ---------------------------------------------------------------- rows
+// The pairs of a crowded state.  k_rdm_pairs adds every pair to Gamma in memory,
+// 18 G/s whatever the size of Gamma: 14.4 of 16.2 ms for 2.6e8 pairs of 225,000
+// determinants of 30 spin-orbitals.  Here a row of Gamma lies in LDS while its
+// pairs are added (at most 15,872 doubles, 124 KB, at 32 orbitals):
+//   members -- the sorted records, decoded, in the order (bucket, subset,
+//              triple): a record's place is counted over its bucket in LDS
+//              (1.2 ms for 3.7e7 records); one with others behind it is also
+//              listed under its triple, which is its row;
+//   sort    -- the list by row, two digits (0.5 ms);
+//   rows    -- a block takes a range of the list; eight lanes add a record's
+//              pairs with the members behind it, 16 bytes each, and the row
+//              goes to memory when it is done (1.4 ms, bound by these reads).
+// RdmMember.rem: members of the subset behind this one.
+struct alignas(16) RdmMember {
+  double val;
+  unsigned idx, rem;
+};
+
+constexpr int kRdmRowBits = 16;  // block (2) and index (14) of a row
+constexpr int kRdmMemTile = 1024;
+constexpr int kRdmMemHalo = 1024;
+constexpr int kRdmMemAll = kRdmMemTile + kRdmMemHalo;
+constexpr int kRdmMemBlock = 512;
+constexpr int kRdmMemPer = kRdmMemAll / kRdmMemBlock;
+
+// A block takes the buckets that begin in its tile; one that goes on past the
+// halo (more than 1,024 records) sets cursor[1], and the caller takes
+// k_rdm_pairs.  cursor[0]: length of the list.
+__global__ void __launch_bounds__(kRdmMemBlock)
+k_rdm_members(const u64* __restrict__ recs, u64 R, RdmFmt fm, int sort_bits, int ne, unsigned ntri,
+              const u64* __restrict__ keys, const double* __restrict__ amps, u64 n, RdmDims dm,
+              RdmMember* __restrict__ mem, u64* __restrict__ list, u64* __restrict__ cursor) {
+  constexpr unsigned kWords = kRdmMemAll / 64;
+  __shared__ u64 s_S[kRdmMemAll];
+  __shared__ unsigned s_b[kRdmMemAll + 1], s_idx[kRdmMemAll];
+  __shared__ u64 s_head[kWords];  // one bit per record that begins a bucket
+  __shared__ unsigned s_cnt;
+  __shared__ u64 s_base;
+  extern __shared__ unsigned s_tri[];  // ntri
+  rdm_triple_table(s_tri, ne, ntri);
+  const u64 bmask = (1ULL << sort_bits) - 1ULL;
+  const u64 ntiles = (R + kRdmMemTile - 1) / kRdmMemTile;
+  const int lane = (int)(threadIdx.x & 63u);
+  // first bucket that begins at i or later (kRdmMemAll: none in the tile)
+  auto next_head = [&](unsigned i) {
+    unsigned w = i >> 6;
+    if (w >= kWords) return (unsigned)kRdmMemAll;
+    u64 m = s_head[w] & (~0ULL << (i & 63u));
+    while (m == 0 && ++w < kWords) m = s_head[w];
+    return m ? (w << 6) + (unsigned)__ffsll((long long)m) - 1u : (unsigned)kRdmMemAll;
+  };
+  for (u64 tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
+    const u64 t0 = tl * kRdmMemTile;
+    const unsigned have = (unsigned)((R - t0) < (u64)kRdmMemAll ? (R - t0) : (u64)kRdmMemAll);
+    const unsigned own = have < (unsigned)kRdmMemTile ? have : (unsigned)kRdmMemTile;
+    u64 rec[kRdmMemPer];
+#pragma unroll
+    for (int k = 0; k < kRdmMemPer; ++k) {
+      const u64 at = t0 + threadIdx.x + (u64)k * kRdmMemBlock;
+      rec[k] = recs[at < R ? at : R - 1];
+    }
+    __syncthreads();  // the tile before is done with LDS
+#pragma unroll
+    for (int k = 0; k < kRdmMemPer; ++k) s_b[1 + threadIdx.x + k * kRdmMemBlock] = (unsigned)(rec[k] & bmask);
+    if (threadIdx.x == 0) {
+      s_b[0] = t0 > 0 ? (unsigned)(recs[t0 - 1] & bmask) : ~s_b[1];  // bucket before the tile
+      s_cnt = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRdmMemPer; ++k) {
+      const unsigned i = threadIdx.x + k * kRdmMemBlock;
+      const u64 m = __ballot(i < have ? s_b[i] != s_b[i + 1] : t0 + have == R);  // past the end: a head
+      if (lane == 0) s_head[i >> 6] = m;
+    }
+    __syncthreads();
+    const unsigned begin = next_head(0);
+    unsigned end = next_head(own);
+    if (begin >= own) continue;  // inside a bucket of an earlier tile
+    if (end == (unsigned)kRdmMemAll && t0 + (u64)kRdmMemAll != R) {
+      // a head may still stand right behind the halo; it is not looked for
+      if (threadIdx.x == 0) __hip_atomic_store(&cursor[1], (u64)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    double val[kRdmMemPer];
+#pragma unroll
+    for (int k = 0; k < kRdmMemPer; ++k) {
+      const unsigned i = threadIdx.x + k * kRdmMemBlock;
+      val[k] = 0.0;
+      if (i < begin || i >= end) continue;
+      const RdmSide o = rdm_decode(rec[k], fm, dm, ne, s_tri, ntri, keys, amps, n);
+      val[k] = o.val;
+      s_S[i] = o.S;
+      s_idx[i] = ((unsigned)o.blk << 14) | o.idx;
+    }
+    __syncthreads();
+    unsigned slot[kRdmMemPer], at[kRdmMemPer];
+#pragma unroll
+    for (int k = 0; k < kRdmMemPer; ++k) {
+      const unsigned i = threadIdx.x + k * kRdmMemBlock;
+      bool put = false;
+      slot[k] = 0xffffffffu;
+      at[k] = 0;
+      if (i >= begin && i < end) {
+        // bucket [lo, hi) of record i
+        unsigned w = i >> 6;
+        u64 m = s_head[w] & (~0ULL >> (63u - (i & 63u)));
+        while (m == 0) m = s_head[--w];  // `begin` is a head
+        const unsigned lo = (w << 6) + 63u - (unsigned)__clzll((long long)m);
+        const unsigned hi = next_head(i + 1) < end ? next_head(i + 1) : end;
+        // place within the bucket by (subset, triple); one subset's triples differ
+        const unsigned id = s_idx[i];
+        const u64 S = s_S[i];
+        unsigned less = 0, rem = 0;
+        for (unsigned j0 = lo; j0 < hi; j0 += 4) {
+          u64 Sj[4];
+          unsigned dj[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const unsigned j = j0 + u < hi ? j0 + u : i;  // record i itself counts for nothing
+            Sj[u] = s_S[j];
+            dj[u] = s_idx[j];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const bool same = Sj[u] == S;
+            less += (Sj[u] < S || (same && dj[u] < id)) ? 1u : 0u;
+            rem += (same && dj[u] > id) ? 1u : 0u;
+          }
+        }
+        at[k] = lo + less;
+        mem[t0 + at[k]] = RdmMember{val[k], id, rem};
+        put = rem != 0;
+      }
+      const u64 m = __ballot(put);
+      if (m) {
+        unsigned first = 0;
+        if (lane == 0) first = atomicAdd(&s_cnt, (unsigned)__popcll(m));
+        first = (unsigned)__shfl((int)first, 0);
+        if (put) slot[k] = first + (unsigned)__popcll(m & ((1ULL << lane) - 1ULL));
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) s_base = atomicAdd((unsigned long long*)cursor, (unsigned long long)s_cnt);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRdmMemPer; ++k)
+      if (slot[k] != 0xffffffffu)
+        list[s_base + slot[k]] = ((t0 + at[k]) << kRdmRowBits) | s_idx[threadIdx.x + k * kRdmMemBlock];
+  }
+}
+
+// End of every row that occurs in the sorted list.
+__global__ void __launch_bounds__(256)
+k_rdm_row_ends(const u64* __restrict__ list, u64 Q, unsigned* __restrict__ row_end) {
+  const u64 stride = (u64)gridDim.x * blockDim.x, mask = (1ULL << kRdmRowBits) - 1ULL;
+  for (u64 q = (u64)blockIdx.x * blockDim.x + threadIdx.x; q < Q; q += stride) {
+    const u64 r = list[q] & mask;
+    if (q + 1 == Q || (list[q + 1] & mask) != r) row_end[r] = (unsigned)(q + 1);
+  }
+}
+
+constexpr int kRdmRowBlock = 512;
+constexpr int kRdmRowLanes = 8;      // of a record: eight members are a cache line
+constexpr unsigned kRdmRowChunk = 8192;  // records of the list per block
+
+__global__ void __launch_bounds__(kRdmRowBlock)
+k_rdm_rows(const u64* __restrict__ list, u64 Q, const unsigned* __restrict__ row_end,
+           const RdmMember* __restrict__ mem, u64 R, unsigned width, RdmView V) {
+  extern __shared__ double s_row[];  // width
+  const u64 mask = (1ULL << kRdmRowBits) - 1ULL;
+  const unsigned l = threadIdx.x % kRdmRowLanes, g = threadIdx.x / kRdmRowLanes;
+  constexpr unsigned kStep = kRdmRowBlock / kRdmRowLanes;
+  for (unsigned i = threadIdx.x; i < width; i += kRdmRowBlock) s_row[i] = 0.0;
+  __syncthreads();
+  const u64 q1 = (u64)(blockIdx.x + 1) * kRdmRowChunk < Q ? (u64)(blockIdx.x + 1) * kRdmRowChunk : Q;
+  for (u64 q = (u64)blockIdx.x * kRdmRowChunk; q < q1;) {
+    const unsigned row = (unsigned)(list[q] & mask);
+    const u64 e = row_end[row] < q1 ? row_end[row] : q1;
+    u64 p = q + g < e ? list[q + g] >> kRdmRowBits : 0;
+    for (u64 r = q + g; r < e; r += kStep) {
+      const u64 next = list[r + kStep < e ? r + kStep : r];
+      const RdmMember me = mem[p];
+      // the first eight members behind, loaded before their number is known
+      const u64 first = p + 1 + l;
+      const RdmMember o = mem[first < R ? first : R - 1];
+      if (l < me.rem) unsafeAtomicAdd(&s_row[o.idx & 0x3fffu], me.val * o.val);
+      for (unsigned k = l + kRdmRowLanes; k < me.rem; k += kRdmRowLanes) {
+        const RdmMember x = mem[p + 1 + k];
+        unsafeAtomicAdd(&s_row[x.idx & 0x3fffu], me.val * x.val);
+      }
+      p = next >> kRdmRowBits;
+    }
+    __syncthreads();
+    const int blk = (int)(row >> 14);
+    const unsigned A = row & 0x3fffu, len = V.d.len[blk];
+    double* __restrict__ gr = V.g3 + V.d.off[blk] + (u64)A * V.d.ld[blk];
+    for (unsigned i = threadIdx.x; i < len; i += kRdmRowBlock) {
+      const double v = s_row[i];
+      if (v != 0.0) {
+        s_row[i] = 0.0;
+        unsafeAtomicAdd(&gr[i], v);
+      }
+    }
+    __syncthreads();
+    q = e;
   }
 }
 
@@ -1040,6 +1251,39 @@ hipError_t launch_rdm_pairs(const DeviceState& st, u64 n, int n_spatial, int ne,
   const RdmView V{rdm_dims(n_spatial), g3, nullptr};
   hipLaunchKernelGGL(k_rdm_pairs, dim3(grid), dim3(kRdmPairBlock), ntri * sizeof(unsigned), stream, recs, R, fm, sort_bits, ne, ntri,
                      st.keys, st.amps, n, V);
+  return hipGetLastError();
+}
+
+size_t rdm_member_bytes() { return sizeof(RdmMember); }
+int rdm_row_bits() { return kRdmRowBits; }
+
+hipError_t launch_rdm_members(const DeviceState& st, u64 n, int n_spatial, int ne, RdmFmt fm, int sort_bits,
+                              const u64* recs, u64 R, void* mem, u64* list, u64* cursor, int grid,
+                              hipStream_t stream) {
+  const unsigned ntri = (unsigned)(ne * (ne - 1) * (ne - 2) / 6);
+  hipError_t e = launch_fill_u32(cursor, 0u, 4, stream);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_rdm_members, dim3(grid), dim3(kRdmMemBlock), ntri * sizeof(unsigned), stream, recs, R, fm,
+                     sort_bits, ne, ntri, st.keys, st.amps, n, rdm_dims(n_spatial), (RdmMember*)mem, list, cursor);
+  return hipGetLastError();
+}
+
+// list sorted by row; row_end: 2^16 words.
+hipError_t launch_rdm_rows(int n_spatial, const u64* list, u64 Q, unsigned* row_end, const void* mem, u64 R, double* g3,
+                           hipStream_t stream) {
+  if (Q == 0) return hipSuccess;
+  if (Q >= (1ULL << 32)) return hipErrorInvalidValue;
+  const RdmView V{rdm_dims(n_spatial), g3, nullptr};
+  const unsigned width = std::max(V.d.len[0], V.d.len[1]);
+  if (width > (1u << 14)) return hipErrorInvalidValue;
+  const int bytes = (int)(width * sizeof(double));
+  hipError_t e = hipFuncSetAttribute((const void*)k_rdm_rows, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_rdm_row_ends, dim3((unsigned)std::min<u64>((Q + 255) / 256, 4096)), dim3(256), 0, stream, list, Q,
+                     row_end);
+  const unsigned blocks = (unsigned)((Q + kRdmRowChunk - 1) / kRdmRowChunk);
+  hipLaunchKernelGGL(k_rdm_rows, dim3(blocks), dim3(kRdmRowBlock), (size_t)bytes, stream, list, Q, row_end,
+                     (const RdmMember*)mem, R, width, V);
   return hipGetLastError();
 }
 

@@ -174,7 +174,7 @@ struct swcs_ctx {
   DevBuf gacc, selected, ncut_state, ncut_cand, qfilt;
   DevBuf partial, partial2, sigma, mu, work, seg_states, acc_tab, gbuf, subset_buf, scalars,
       exp_keys, exp_amps, exp_tmp_k, exp_tmp_v, sort_scratch, ctr_r, occ, sel_scratch, mlp_partial, mse_partial, hp_key, hp_val, hp_tk, hp_tv, diag, join_src,
-      join_w, join_j, join_bins, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs,
+      join_w, join_j, join_bins, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs, rdm_mem,
       str_rec, str_key, str_val, str_oth, str_tab;
   int sigma_method = SWCS_SIGMA_AUTO;
   int pool_method = SWCS_POOL_AUTO;
@@ -196,7 +196,7 @@ struct swcs_ctx {
                      &subset_buf, &scalars, &exp_keys, &exp_amps, &exp_tmp_k, &exp_tmp_v,
                      &sort_scratch, &ctr_r, &occ, &sel_scratch, &mlp_partial, &mse_partial,
                      &hp_key, &hp_val, &hp_tk, &hp_tv, &diag, &qfilt, &join_src, &join_w, &join_j,
-                     &join_bins, &rdm_g3, &rdm_g2, &rdm_vtab, &rdm_part, &rdm_bs, &str_rec, &str_key,
+                     &join_bins, &rdm_g3, &rdm_g2, &rdm_vtab, &rdm_part, &rdm_bs, &rdm_mem, &str_rec, &str_key,
                      &str_val, &str_oth, &str_tab};
     for (DevBuf* b : all) f(*b);
     for (auto& b : ckpt) f(b);
@@ -332,7 +332,7 @@ size_t avail_bytes(swcs_ctx* c) {
 void release_scratch(swcs_ctx* c) {
   DevBuf* bufs[] = {&c->acc_tab, &c->hp_key, &c->hp_val, &c->hp_tk, &c->hp_tv, &c->sort_scratch,
                     &c->exp_keys, &c->exp_amps, &c->exp_tmp_k, &c->exp_tmp_v, &c->qfilt, &c->join_src, &c->join_w,
-                    &c->join_j, &c->rdm_g3, &c->rdm_part, &c->seg_states, &c->work, &c->str_rec, &c->str_key,
+                    &c->join_j, &c->rdm_g3, &c->rdm_part, &c->rdm_mem, &c->seg_states, &c->work, &c->str_rec, &c->str_key,
                     &c->str_val, &c->str_oth, &c->str_tab};
   for (DevBuf* b : bufs) b->release();
 }
@@ -1576,11 +1576,26 @@ constexpr u64 kRdmMaxRecords = 1ULL << 28;
 // About this many determinants are looked at before the pass is taken.
 constexpr u64 kRdmSample = 1024;
 // Largest number of pairs (determinants within a triple excitation, counted
-// once per subset they share) per record of the join: a pair costs one
-// device-scope add, 18 G/s measured, a join record 14-22 G/s.  The pass is
-// slower than the join only where the state fills its sector so far that
-// every determinant has more neighbours than connections.
+// once per subset they share) per record of the join, where every pair is added
+// in memory: one device-scope add, 18 G/s measured, against 14-22 G/s for a join
+// record.
 constexpr double kRdmPairLimit = 1.0;
+// Pairs per subset record from which the rows of the density matrix are summed
+// in LDS: listing and sorting the records by row costs as much as one add in
+// memory each (50 ps), and a pair then 5 ps instead of 55.  224,982 determinants
+// of 30 spin-orbitals (7 pairs a record): 14.4 to 3.0 ms for this part;
+// 137,595 of 52 (0.3 a record) would go from 2.0 to 4.
+constexpr double kRdmRowPairs = 1.0;
+
+// Whether that form is taken where the pairs outnumber the join's records: its
+// measured share per subset record and per pair (both on the safe side), 1.1 ms
+// for what does not depend on the state, and 65 ps per join record.  Measured
+// against the join: 100,000 of (12 orbitals, 5 + 6 electrons) 2.6 to 13.6 ms at
+// 1.3 pairs per join record; the full (12, 6 + 6) sector 69 to 118 at 10.4; the
+// full (10, 5 + 5) sector, 63,504 determinants, is even (4.5).
+static bool rdm_rows_pay(double records, double pairs, double join_records) {
+  return 1.1e-3 + 8e-11 * records + 5e-12 * pairs < 6.5e-11 * join_records;
+}
 
 // Join records (alive (C + 1)) from which AUTO takes the density matrix.  Its
 // cost on a small state is the contraction, n^7: 3.4 ms in all at 26 orbitals,
@@ -1601,6 +1616,7 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
   if (ne < 3 || ne > kRdmMaxElectrons) return 1;
   const double R_join = (double)h.alive * (double)(c->exc.total + 1);
   if (R_join < rdm_min_records(c->n)) return 1;
+  const u64 n = h.n, ntri = (u64)ne * (u64)(ne - 1) * (u64)(ne - 2) / 6, total = h.alive * ntri;
   // pairs of a state that is spread evenly over its sector: a state is at least
   // this crowded, so a full sector needs no sample
   {
@@ -1610,9 +1626,9 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
     const double t1 = a * va + b * vb, t2 = c2(a) * c2(va) + c2(b) * c2(vb) + a * b * va * vb;
     const double t3 = c3(a) * c3(va) + c3(b) * c3(vb) + c2(a) * c2(va) * b * vb + c2(b) * c2(vb) * a * va;
     const double share = (double)h.alive / (double)c->sector;
-    if (0.5 * (double)h.alive * share * (t3 + (ne - 2.0) * t2 + c2(ne - 1.0) * t1) > kRdmPairLimit * R_join) return 1;
+    const double pairs = 0.5 * (double)h.alive * share * (t3 + (ne - 2.0) * t2 + c2(ne - 1.0) * t1);
+    if (pairs > kRdmPairLimit * R_join && !rdm_rows_pay((double)total, pairs, R_join)) return 1;
   }
-  const u64 n = h.n, ntri = (u64)ne * (u64)(ne - 1) * (u64)(ne - 2) / 6, total = h.alive * ntri;
   auto bits_for = [](u64 v) {
     int b = 1;
     while (b < 64 && (v >> b) != 0) ++b;
@@ -1632,7 +1648,8 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
                vt = rdm_vtab_elems(c->n);
   const double need = 8.0 * ((double)g3 + (double)part + (double)two + (double)vt + 2.0 * (double)cap + (double)scr);
   const double have = (double)(avail_bytes(c) + c->hp_key.bytes + c->hp_tk.bytes + c->sort_scratch.bytes +
-                               c->rdm_g3.bytes + c->rdm_part.bytes + c->rdm_g2.bytes + c->rdm_vtab.bytes);
+                               c->rdm_g3.bytes + c->rdm_part.bytes + c->rdm_g2.bytes + c->rdm_vtab.bytes +
+                               c->rdm_mem.bytes);
   if (need > 0.5 * have) return 1;
   HIP_TRY(c, c->rdm_g3.ensure(g3 * 8), "alloc density matrix");
   HIP_TRY(c, c->rdm_part.ensure(part * 8), "alloc density matrix");
@@ -1645,6 +1662,7 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
   double* gam = c->rdm_g3.as<double>();
   u64* cursor = c->scalars.as<u64>() + 32;
   // Decide by the pairs among a sample of the determinants, one in `share`.
+  bool rows = false, crowded = false;
   {
     double share = 8.0;
     while (share < 1024.0 && ((double)h.alive / share > 2.0 * (double)kRdmSample ||
@@ -1677,7 +1695,12 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
       HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
       pairs = std::max(0.0, pairs - 0.5 * (double)R * (double)R / (double)(1ULL << bits));
     }
-    if (pairs * share * share > kRdmPairLimit * R_join) return 1;
+    pairs *= share * share;
+    const size_t mem = cap * rdm_member_bytes() + ((size_t)4 << rdm_row_bits());
+    rows = pairs > kRdmRowPairs * (double)total && need + (double)mem <= 0.5 * have;
+    crowded = pairs > kRdmPairLimit * R_join;
+    if (crowded && !(rows && rdm_rows_pay((double)total, pairs, R_join))) return 1;
+    if (rows) HIP_TRY(c, c->rdm_mem.ensure(mem), "alloc subset members");
   }
   HIP_TRY(c, launch_rdm_clear(c->n, gam, c->stream), "zero density matrix");
   for (int b = 0; b < nbatch; ++b) {
@@ -1696,9 +1719,24 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
     u64* sorted = c->hp_key.as<u64>();
     HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, sort_bits, c->sort_scratch.as<u64>(), scr, c->stream,
                                &sorted), "subset sort");
-    const u64 tiles = (R + 1023) / 1024;
-    HIP_TRY(c, launch_rdm_pairs(c->st, n, c->n, ne, fm, sort_bits, sorted, R, gam,
-                                (int)std::min<u64>(std::max<u64>(tiles, 1), (u64)c->num_cu * 16), c->stream), "pairs");
+    const int tiles = (int)std::min<u64>(std::max<u64>((R + 1023) / 1024, 1), (u64)c->num_cu * 16);
+    if (rows && R > 0) {
+      u64* list = sorted == c->hp_key.as<u64>() ? c->hp_tk.as<u64>() : c->hp_key.as<u64>();
+      HIP_TRY(c, launch_rdm_members(c->st, n, c->n, ne, fm, sort_bits, sorted, R, c->rdm_mem.p, list, cursor, tiles,
+                                    c->stream), "subset members");
+      u64 got[2] = {0, 0};  // records of the list; a bucket longer than the pass takes
+      HIP_TRY(c, hipMemcpyAsync(got, cursor, sizeof(got), hipMemcpyDeviceToHost, c->stream), "copy");
+      HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+      if (!got[1]) {
+        HIP_TRY(c, radix_sort_keys(list, sorted, got[0], rdm_row_bits(), c->sort_scratch.as<u64>(), scr, c->stream,
+                                   &list), "row sort");
+        HIP_TRY(c, launch_rdm_rows(c->n, list, got[0], (unsigned*)((char*)c->rdm_mem.p + cap * rdm_member_bytes()),
+                                   c->rdm_mem.p, R, gam, c->stream), "rows");
+        continue;
+      }
+      if (crowded) return 1;
+    }
+    HIP_TRY(c, launch_rdm_pairs(c->st, n, c->n, ne, fm, sort_bits, sorted, R, gam, tiles, c->stream), "pairs");
   }
   HIP_TRY(c, launch_rdm_diag(c->st, n, c->n, gam, (int)std::min<u64>((n + 7) / 8, (u64)c->num_cu), c->stream),
           "diagonal");

@@ -464,6 +464,13 @@ hipError_t launch_rdm_clear(int n_spatial, double* g3, hipStream_t stream);
 hipError_t launch_rdm_count(const u64* recs, u64 R, int sort_bits, double* partial, int grid, hipStream_t stream);
 hipError_t launch_rdm_pairs(const DeviceState& st, u64 n, int n_spatial, int ne, RdmFmt fm, int sort_bits,
                             const u64* recs, u64 R, double* g3, int grid, hipStream_t stream);
+size_t rdm_member_bytes();
+int rdm_row_bits();
+hipError_t launch_rdm_members(const DeviceState& st, u64 n, int n_spatial, int ne, RdmFmt fm, int sort_bits,
+                              const u64* recs, u64 R, void* mem, u64* list, u64* cursor, int grid,
+                              hipStream_t stream);
+hipError_t launch_rdm_rows(int n_spatial, const u64* list, u64 Q, unsigned* row_end, const void* mem, u64 R, double* g3,
+                           hipStream_t stream);
 hipError_t launch_rdm_diag(const DeviceState& st, u64 n, int n_spatial, double* g3, int grid, hipStream_t stream);
 hipError_t launch_rdm_gradients(const Ints& I, const double* eri, int na, int nb, double* g3, double* g2, double* vtab, double* part, double* bs,
                                 const OpDesc* ops, const int* subset, long long count, const double* norm2,
