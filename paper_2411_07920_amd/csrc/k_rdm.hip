@@ -560,19 +560,21 @@ k_rdm_row_ends(const u64* __restrict__ list, u64 Q, unsigned* __restrict__ row_e
 
 constexpr int kRdmRowBlock = 512;
 constexpr int kRdmRowLanes = 8;      // of a record: eight members are a cache line
-constexpr unsigned kRdmRowChunk = 8192;  // records of the list per block
+// Records of the list per block: 8,192, fewer where that leaves the chip idle (a
+// block writes out the rows of its range one after the other).
+constexpr unsigned kRdmRowChunkMax = 8192, kRdmRowChunkMin = 512;
 
 __global__ void __launch_bounds__(kRdmRowBlock)
 k_rdm_rows(const u64* __restrict__ list, u64 Q, const unsigned* __restrict__ row_end,
-           const RdmMember* __restrict__ mem, u64 R, unsigned width, RdmView V) {
+           const RdmMember* __restrict__ mem, u64 R, unsigned width, unsigned chunk, RdmView V) {
   extern __shared__ double s_row[];  // width
   const u64 mask = (1ULL << kRdmRowBits) - 1ULL;
   const unsigned l = threadIdx.x % kRdmRowLanes, g = threadIdx.x / kRdmRowLanes;
   constexpr unsigned kStep = kRdmRowBlock / kRdmRowLanes;
   for (unsigned i = threadIdx.x; i < width; i += kRdmRowBlock) s_row[i] = 0.0;
   __syncthreads();
-  const u64 q1 = (u64)(blockIdx.x + 1) * kRdmRowChunk < Q ? (u64)(blockIdx.x + 1) * kRdmRowChunk : Q;
-  for (u64 q = (u64)blockIdx.x * kRdmRowChunk; q < q1;) {
+  const u64 q0 = (u64)blockIdx.x * chunk, q1 = q0 + chunk < Q ? q0 + chunk : Q;
+  for (u64 q = q0; q < q1;) {
     const unsigned row = (unsigned)(list[q] & mask);
     const u64 e = row_end[row] < q1 ? row_end[row] : q1;
     u64 p = q + g < e ? list[q + g] >> kRdmRowBits : 0;
@@ -1281,9 +1283,11 @@ hipError_t launch_rdm_rows(int n_spatial, const u64* list, u64 Q, unsigned* row_
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_rdm_row_ends, dim3((unsigned)std::min<u64>((Q + 255) / 256, 4096)), dim3(256), 0, stream, list, Q,
                      row_end);
-  const unsigned blocks = (unsigned)((Q + kRdmRowChunk - 1) / kRdmRowChunk);
+  const u64 even = (Q + 4095) / 4096;  // sixteen blocks a CU
+  const unsigned chunk = (unsigned)std::min<u64>(kRdmRowChunkMax, std::max<u64>(kRdmRowChunkMin, even));
+  const unsigned blocks = (unsigned)((Q + chunk - 1) / chunk);
   hipLaunchKernelGGL(k_rdm_rows, dim3(blocks), dim3(kRdmRowBlock), (size_t)bytes, stream, list, Q, row_end,
-                     (const RdmMember*)mem, R, width, V);
+                     (const RdmMember*)mem, R, width, chunk, V);
   return hipGetLastError();
 }
 

@@ -1597,11 +1597,27 @@ static bool rdm_rows_pay(double records, double pairs, double join_records) {
   return 1.1e-3 + 8e-11 * records + 5e-12 * pairs < 6.5e-11 * join_records;
 }
 
-// Join records (alive (C + 1)) from which AUTO takes the density matrix.  Its
-// cost on a small state is the contraction, n^7: 3.4 ms in all at 26 orbitals,
-// as long as a join of 6e7 records; below about 3e7 records (2 ms) the pass
-// has no lead at any n because of its fifteen small launches.
-static double rdm_min_records(int n) { return std::max(3.0e7, 0.0075 * std::pow((double)n, 7.0)); }
+// Seconds of the density-matrix pass at n orbitals and `records` subset records,
+// `each` seconds a record: fifteen small launches and the sample, the
+// contraction's n^7, and emit, sort and pairs.
+static double rdm_seconds(int n, double records, double each) {
+  return 0.9e-3 + 4e-13 * std::pow((double)n, 7.0) + each * records;
+}
+// Whether AUTO takes it for a whole pool: 55 ps a subset record (the pairs of a
+// crowded state are judged by the sample) against 60 ps a join record.  26
+// orbitals: 4.0 ms against 5.5 at 8.9e7 join records, 3.7 against 2.8 at 4.6e7.
+// Below 3e7 records (2 ms) the launches leave it no lead at any n.
+static bool rdm_pays(int n, double records, double join_records) {
+  return join_records >= 3.0e7 && rdm_seconds(n, records, 5.5e-11) < 6e-11 * join_records;
+}
+// Whether it is taken for a share of the pool.  The screened pass takes 15 to 25
+// ps a join record and 350 to 550 more times the share of the operators (1 to
+// 10 % of 15 to 26 orbitals, 3e7 to 5e8 records); a subset record here 150 with
+// the pairs of a clustered state.  26 orbitals, 8 + 8 electrons, 4,392
+// determinants: 4.9 against 8.6 ms at 10 %, 4.8 against 3.2 at 3 %.
+static bool rdm_pays_screened(int n, double records, double join_records, double share) {
+  return rdm_seconds(n, records, 1.5e-10) < (1.5e-11 + 3.5e-10 * share) * join_records;
+}
 
 // Pool gradients of the `count` operators d_subset (NULL: the whole pool) into
 // d_out from the three-body density matrix (k_rdm.hip).  Returns 1 when the
@@ -1615,8 +1631,8 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
   const int ne = c->na + c->nb;
   if (ne < 3 || ne > kRdmMaxElectrons) return 1;
   const double R_join = (double)h.alive * (double)(c->exc.total + 1);
-  if (R_join < rdm_min_records(c->n)) return 1;
   const u64 n = h.n, ntri = (u64)ne * (u64)(ne - 1) * (u64)(ne - 2) / 6, total = h.alive * ntri;
+  if (!rdm_pays(c->n, (double)total, R_join)) return 1;
   // pairs of a state that is spread evenly over its sector: a state is at least
   // this crowded, so a full sector needs no sample
   {
@@ -1769,9 +1785,13 @@ static int screened_gradients(swcs_ctx* c, const Counters& h, const int* d_subse
   const bool op_major = n_subset <= c->exc.total;
   const double bound = std::min<double>((double)c->sector,
                                         (double)alive * (double)(op_major ? n_subset : c->exc.total));
-  // a pass that would count its query keys synchronizes anyway; the density
-  // matrix of the state then gives any subset at the price of the whole pool
-  if (2.0 * bound * sizeof(AccSlot) > kQueryBoundBytes) {
+  // The density matrix of the state gives any subset at the price of the whole
+  // pool.  It synchronizes: for calls that do so anyway, and those that would
+  // count their query keys.
+  const double ne = c->na + c->nb;
+  if ((may_sync || 2.0 * bound * sizeof(AccSlot) > kQueryBoundBytes) &&
+      rdm_pays_screened(c->n, (double)alive * ne * (ne - 1.0) * (ne - 2.0) / 6.0,
+                        (double)alive * (double)(c->exc.total + 1), (double)n_subset / (double)c->K_pool)) {
     int r = rdm_gradients(c, h, d_subset, n_subset, norm2, d_out);
     if (r <= 0) {
       c->ps_screened = 1;
