@@ -592,9 +592,11 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     if (r) return r;
   }
   // overlapping generators have no single-workgroup kernel: such chains run
-  // in HBM from the first gate
-  if (!has_star && n_start <= (u64)lds_chain_capacity() && c->st.cap >= (u64)lds_chain_capacity() &&
-      M <= (int64_t)1 << 30) {
+  // in HBM from the first gate.  The arrays have to hold what the kernel may
+  // write back: the LDS capacity, or a whole sector smaller than that (12
+  // spin-orbitals: 225 determinants, 30 gates 163 us in HBM, 32 here)
+  if (!has_star && n_start <= (u64)lds_chain_capacity() &&
+      c->st.cap >= std::min((u64)lds_chain_capacity(), c->sector) && M <= (int64_t)1 << 30) {
     TIMED(c, SWCS_K_CHAIN_LDS, launch_chain_lds(c->st, c->gate_tab.as<GateDesc>(), 0, (int)M, eps, eps > 0.0 ? 1 : 0,
                                 ckpt ? c->ckpt_ptrs.as<double*>() : nullptr, c->ckpt_n.as<u64>(),
                                 c->seg, c->gate_n_in.as<u64>(), c->sector, ncut, c->stream), "chain");
