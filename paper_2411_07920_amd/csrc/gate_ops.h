@@ -267,10 +267,11 @@ __device__ inline void ncut_pick(NcutState& st, int d) {
 struct NcutSelect {
   unsigned skip;    // 1: keep everything (fewer than ncut alive, or chain stopped)
   unsigned k;       // rank still to find inside the current prefix
-  unsigned prefix;  // leading bits of |c| found so far
+  unsigned prefix;  // digits of |c| found so far
   unsigned ncand;   // entries with the whole prefix
   unsigned ticket;  // blocks of the current launch that are done
-  unsigned pad[3];
+  unsigned narrow;  // 1: the first digit left so few that the second is not looked at
+  unsigned pad[2];
   unsigned hist[2][4096];
 };
 

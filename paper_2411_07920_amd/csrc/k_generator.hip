@@ -176,44 +176,29 @@ __device__ inline u64 wave_reserve(bool want, u64* counter) {
 
 constexpr int kGenThreads = 256;
 
-// Forward gate: the same stop / fold protocol as k_gate (appends of a star
-// gate are bounded by twice the alive count).
+// Forward gate: the same stop and count protocol as k_gate (appends of a star
+// gate are bounded by twice the alive count).  A block's new keys take one add
+// on the append counter per 256 entries; one per wavefront and member on the
+// same address made the launch 34 us at 100,000 entries; it takes 10.
 __global__ void __launch_bounds__(kGenThreads)
 k_gen_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__ hash, u64 hmask,
            u64 cap, Counters* __restrict__ ctr, GenGate g, double eps, u64* __restrict__ gate_n_in,
-           int check_cap, unsigned gate_index, u64 max_keys, u64* __restrict__ gate_n_act) {
-  __shared__ int s_run;
-  __shared__ u64 s_n_in;
+           unsigned gate_index, u64 max_keys, u64* __restrict__ gate_n_act) {
   __shared__ long long s_wsum[kGenThreads / 64];
-  __shared__ bool is_last;
-  if (threadIdx.x == 0) {
-    int run = 1;
-    const unsigned fl = __hip_atomic_load(&ctr->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const u64 n_in = __hip_atomic_load(&ctr->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (fl & kFlagStopped) {
-      run = 0;
-    } else if (check_cap) {
-      const u64 alive_in = __hip_atomic_load(&ctr->alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const u64 room = max_keys > n_in ? max_keys - n_in : 0;
-      if (n_in + (2 * alive_in < room ? 2 * alive_in : room) > cap) {
-        run = 0;
-        if (blockIdx.x == 0) {
-          ctr->stop_gate = gate_index;
-          atomicOr(&ctr->flags, kFlagStopped);
-        }
-      }
-    }
-    s_run = run;
-    s_n_in = n_in;
-  }
-  __syncthreads();
-  if (!s_run) return;
-  const u64 n_in = s_n_in;
+  __shared__ unsigned s_nact[kGenThreads / 64];
+  __shared__ unsigned s_wcnt[2][kGenThreads / 64];
+  __shared__ u64 s_base[2];
+  u64 n_in;
+  const bool run = gate_begin(ctr, gate_index, cap, max_keys, 2, &n_in, gate_n_in);
+  if (!run) return;  // the same in every thread
+  LiveCounts* __restrict__ own = &ctr->live[live_slot(gate_index)];
   GlobalStore S{keys, amps, hash, hmask};
+  const int lane = __lane_id(), wave = (int)(threadIdx.x >> 6);
+  const u64 below = (1ULL << lane) - 1ULL;
   long long dalive = 0;
-  unsigned nact = 0;
+  unsigned nact = 0, par = 0;
   const u64 stride = (u64)gridDim.x * kGenThreads;
-  for (u64 base = (u64)blockIdx.x * kGenThreads; base < n_in; base += stride) {
+  for (u64 base = (u64)blockIdx.x * kGenThreads; base < n_in; base += stride, par ^= 1u) {
     const u64 i = base + threadIdx.x;
     GenOut o;
     o.napp = 0;
@@ -224,12 +209,24 @@ k_gen_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restri
       o = gen_entry(S, i, g, eps);
     }
     dalive += o.dalive;
+    const u64 m0 = __ballot(o.napp > 0), m1 = __ballot(o.napp > 1);
+    const unsigned mine = (unsigned)(__popcll(m0) + __popcll(m1));
+    if (lane == 0) s_wcnt[par][wave] = mine;
+    __syncthreads();
+    unsigned before = 0, all = 0;
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const bool want = o.napp > a;
-      const u64 slot = wave_reserve(want, &ctr->app);
-      if (want) {
-        const u64 idx = n_in + slot;
+    for (int w = 0; w < kGenThreads / 64; ++w) {
+      before += w < wave ? s_wcnt[par][w] : 0u;
+      all += s_wcnt[par][w];
+    }
+    if (all) {  // the same in the whole block
+      if (threadIdx.x == 0) s_base[par] = atomicAdd((unsigned long long*)&own->app, (unsigned long long)all);
+      __syncthreads();
+      const u64 at = n_in + s_base[par] + before;
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        if (o.napp <= a) continue;
+        const u64 idx = at + (a ? (u64)__popcll(m0) + (u64)__popcll(m1 & below) : (u64)__popcll(m0 & below));
         if (idx < cap) {
           keys[idx] = o.key[a];
           amps[idx] = o.val[a];
@@ -244,10 +241,9 @@ k_gen_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restri
     dalive += __shfl_xor(dalive, off);
     nact += __shfl_xor(nact, off);
   }
-  __shared__ unsigned s_nact[kGenThreads / 64];
-  if (__lane_id() == 0) {
-    s_wsum[threadIdx.x / 64] = dalive;
-    s_nact[threadIdx.x / 64] = nact;
+  if (lane == 0) {
+    s_wsum[wave] = dalive;
+    s_nact[wave] = nact;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -258,22 +254,7 @@ k_gen_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restri
       na += s_nact[w];
     }
     if (gate_n_act && na) atomicAdd((unsigned long long*)gate_n_act, (unsigned long long)na);
-    if (d != 0) atomicAdd((unsigned long long*)&ctr->dalive, (unsigned long long)d);
-    device_atomics_done();
-    const unsigned tk = atomicAdd(&ctr->ticket, 1u);
-    is_last = (tk == gridDim.x - 1);
-  }
-  __syncthreads();
-  if (is_last && threadIdx.x == 0) {
-    const u64 app = atomicAdd(&ctr->app, 0ULL);
-    const long long da = (long long)atomicAdd((unsigned long long*)&ctr->dalive, 0ULL);
-    const u64 alive = ctr->alive;
-    if (gate_n_in) *gate_n_in = alive;
-    ctr->n = n_in + (app < cap - n_in ? app : cap - n_in);
-    ctr->alive = (u64)((long long)alive + da);
-    ctr->app = 0;
-    ctr->dalive = 0;
-    ctr->ticket = 0;
+    if (d != 0) atomicAdd((unsigned long long*)&own->dalive, (unsigned long long)d);
   }
 }
 
@@ -333,7 +314,7 @@ k_adjoint_star(const StarRec* __restrict__ slog, const u64* __restrict__ scount,
 hipError_t launch_gen_gate(const DeviceState& st, const GenGate& g, double eps, u64* gate_n_in,
                            unsigned gate_index, u64 max_keys, int grid, hipStream_t stream, u64* gate_n_act) {
   hipLaunchKernelGGL(k_gen_gate, dim3(grid), dim3(kGenThreads), 0, stream, st.keys, st.amps, st.hash,
-                     st.hmask, st.cap, st.ctr, g, eps, gate_n_in, 1, gate_index, max_keys, gate_n_act);
+                     st.hmask, st.cap, st.ctr, g, eps, gate_n_in, gate_index, max_keys, gate_n_act);
   return hipGetLastError();
 }
 

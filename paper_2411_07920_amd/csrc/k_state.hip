@@ -34,48 +34,35 @@ template <int SCAN>
 __global__ void __launch_bounds__(kGateThreads, 8)
 k_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__ hash, u64 hmask,
        u64 cap, Counters* __restrict__ ctr, OpDesc op, double c, double sn, double eps,
-       u64* __restrict__ gate_n_in, int check_cap, unsigned gate_index, u64 max_keys,
-       u64* __restrict__ gate_n_act) {
+       u64* __restrict__ gate_n_in, unsigned gate_index, u64 max_keys, u64* __restrict__ gate_n_act) {
   constexpr int kScan = kGateThreads * SCAN;  // entries per tile (< 2^16)
   __shared__ unsigned short s_act[kScan];
   __shared__ u64 s_key[kGateTile];
   __shared__ double s_val[kGateTile];
   __shared__ unsigned s_nact, s_cnt;
-  __shared__ int s_run;
-  __shared__ u64 s_n_in, s_base;
+  __shared__ u64 s_base;
   __shared__ long long s_wsum[kGateThreads / 64];
-  __shared__ bool is_last;
-  if (threadIdx.x == 0) {
-    // A stopped chain skips every later gate; the host resumes it after
-    // growing.  Appends are bounded by the alive sources and by the number of
-    // keys not yet stored (max_keys = size of the electron-number sector), so
-    // n_in + min(alive_in, max_keys - n_in) <= cap guarantees the gate fits.
-    // Every block reads the same values and takes the same decision; nothing
-    // has been modified when it stops.
-    int run = 1;
-    const unsigned fl = __hip_atomic_load(&ctr->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const u64 n_in = __hip_atomic_load(&ctr->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (fl & kFlagStopped) {
-      run = 0;
-    } else if (check_cap) {
-      const u64 alive_in = __hip_atomic_load(&ctr->alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const u64 room = max_keys > n_in ? max_keys - n_in : 0;
-      if (n_in + (alive_in < room ? alive_in : room) > cap) {
-        run = 0;
-        if (blockIdx.x == 0) {
-          ctr->stop_gate = gate_index;
-          atomicOr(&ctr->flags, kFlagStopped);
-        }
-      }
+  // In a launch that is mostly latency, the first tile's keys are on their way
+  // before the entry count is known; wide tiles of blocks beyond it would be
+  // read for nothing.
+  constexpr bool kAhead = SCAN <= 2;
+  u64 D[SCAN];
+  if (kAhead) {
+#pragma unroll
+    for (int j = 0; j < SCAN; ++j) {
+      const u64 i = (u64)blockIdx.x * kScan + (u64)j * kGateThreads + threadIdx.x;
+      D[j] = keys[i < cap ? i : 0];
     }
-    s_run = run;
-    s_n_in = n_in;
+  }
+  u64 n_in;
+  const bool run = gate_begin(ctr, gate_index, cap, max_keys, 1, &n_in, gate_n_in);
+  if (!run) return;  // the same in every thread
+  if (threadIdx.x == 0) {
     s_nact = 0;
     s_cnt = 0;
   }
   __syncthreads();
-  if (!s_run) return;
-  const u64 n_in = s_n_in;
+  LiveCounts* __restrict__ own = &ctr->live[live_slot(gate_index)];
   long long dalive = 0;
   u64 nact = 0;
   const int lane = __lane_id();
@@ -86,11 +73,12 @@ k_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__
     const u64 base = t * (u64)kScan;
     // scan: keys of the tile, active entries listed in LDS
     {
-      u64 D[SCAN];
+      if (!kAhead || t != blockIdx.x) {
 #pragma unroll
-      for (int j = 0; j < SCAN; ++j) {
-        const u64 i = base + (u64)j * kGateThreads + threadIdx.x;
-        D[j] = (i < n_in) ? keys[i] : 0ULL;
+        for (int j = 0; j < SCAN; ++j) {
+          const u64 i = base + (u64)j * kGateThreads + threadIdx.x;
+          D[j] = (i < n_in) ? keys[i] : 0ULL;
+        }
       }
 #pragma unroll
       for (int j = 0; j < SCAN; ++j) {
@@ -144,7 +132,7 @@ k_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__
       // append: one counter atomic, coalesced writes
       const unsigned cnt = s_cnt;
       if (cnt) {
-        if (threadIdx.x == 0) s_base = atomicAdd(&ctr->app, (u64)cnt);
+        if (threadIdx.x == 0) s_base = atomicAdd(&own->app, (u64)cnt);
         __syncthreads();
         const u64 gb = n_in + s_base;
         for (unsigned j = threadIdx.x; j < cnt; j += kGateThreads) {
@@ -165,7 +153,7 @@ k_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__
     if (threadIdx.x == 0) s_nact = 0;
     __syncthreads();
   }
-  // Block reduction of the alive-count change, then last-block finalization.
+  // the block's change of the alive count
   for (int off = 32; off > 0; off >>= 1) dalive += __shfl_xor(dalive, off);
   if (lane == 0) s_wsum[threadIdx.x / 64] = dalive;
   __syncthreads();
@@ -173,22 +161,7 @@ k_gate(u64* __restrict__ keys, double* __restrict__ amps, HashSlot* __restrict__
     long long d = 0;
     for (int w = 0; w < kGateThreads / 64; ++w) d += s_wsum[w];
     if (gate_n_act && nact) atomicAdd((unsigned long long*)gate_n_act, (unsigned long long)nact);
-    if (d != 0) atomicAdd((unsigned long long*)&ctr->dalive, (unsigned long long)d);
-    device_atomics_done();
-    const unsigned tk = atomicAdd(&ctr->ticket, 1u);
-    is_last = (tk == gridDim.x - 1);
-  }
-  __syncthreads();
-  if (is_last && threadIdx.x == 0) {
-    const u64 app = atomicAdd(&ctr->app, 0ULL);
-    const long long da = (long long)atomicAdd((unsigned long long*)&ctr->dalive, 0ULL);
-    const u64 alive = ctr->alive;
-    if (gate_n_in) *gate_n_in = alive;
-    ctr->n = n_in + (app < cap - n_in ? app : cap - n_in);
-    ctr->alive = (u64)((long long)alive + da);
-    ctr->app = 0;
-    ctr->dalive = 0;
-    ctr->ticket = 0;
+    if (d != 0) atomicAdd((unsigned long long*)&own->dalive, (unsigned long long)d);
   }
 }
 
@@ -354,22 +327,32 @@ __global__ void k_filter_set(const u64* __restrict__ keys, const double* __restr
 // N_CUT pruning of a state in HBM: a radix select of the ncut-th largest value
 // in the N_CUT order (gate_ops.h) in three launches -- two histograms of twelve
 // bits of |c| each, whose last block to finish picks the digit, and a marking
-// pass that drops everything below the 24-bit prefix found, collects the
-// entries that have it, and leaves their order (the remaining bits of |c|, then
-// the key) to its last block.  With 8-bit digits, a launch per histogram and one
-// per pick the selection was 34 launches a gate: 100 us at 10,000 to 40,000
-// entries; the three launches take 18 us (evaluation of 100 generators at
-// N_CUT = 10,000: 50.1 -> 13.9 ms).  blockIdx.y is one of several states of the
-// same keys.  With ctr the stored count comes from the counters and the alive
-// count is updated; otherwise n_host entries are scanned.
+// pass that drops everything below the digits found, collects the entries that
+// have them, and leaves their order (all of |c|, then the key) to its last
+// block.  Where the first digit leaves few entries the second histogram does
+// nothing (2.5 us instead of 7).  With 8-bit digits, a launch per histogram and
+// one per pick the selection was 34 launches a gate: 100 us at 10,000 to 40,000
+// entries (evaluation of 100 generators at N_CUT = 10,000: 50.1 -> 6.9 ms in all).
+// blockIdx.y is one of several states of the same keys.  With ctr the counts are
+// those after gate `gate` of a chain; otherwise n_host entries are scanned.
 constexpr int kNcutThreads = 1024;
 constexpr int kNcutBits = 12;
 constexpr int kNcutBins = 1 << kNcutBits;
+constexpr unsigned kNcutRank = 1024;  // candidates ordered by counting in LDS
 
 __device__ inline u64 ncut_bits(double a) { return (u64)__double_as_longlong(fabs(a)); }
-// first digit: the exponent and one bit of the mantissa; second: the next twelve
-__device__ inline unsigned ncut_first(u64 hi) { return (unsigned)(hi >> 51); }
-__device__ inline unsigned ncut_prefix(u64 hi) { return (unsigned)(hi >> 39); }
+// First digit: six bits of the exponent (2^-63 to 2) and six of the mantissa, so
+// that one bin of a spread state holds few entries; smaller and larger values
+// share the end bins.  Second: the next twelve bits, or within an end bin the
+// whole exponent and one bit of the mantissa.
+__device__ inline unsigned ncut_first(u64 hi) {
+  const unsigned b = (unsigned)(hi >> 46), lo = (1023u - 63u) << 6;
+  if (b < lo) return 0u;
+  return b - lo < kNcutBins - 1u ? b - lo : kNcutBins - 1u;
+}
+__device__ inline unsigned ncut_second(u64 hi, unsigned first) {
+  return first == 0u || first == kNcutBins - 1u ? (unsigned)(hi >> 51) : (unsigned)(hi >> 34) & (kNcutBins - 1u);
+}
 
 // True in every thread of the block that finishes last of this blockIdx.y.  The
 // other blocks' device-scope atomics are then done (each wavefront waits for
@@ -387,9 +370,10 @@ __device__ inline bool ncut_last_block(unsigned* ticket, bool* s_last) {
 
 // Digit that holds rank k (from the largest) of a histogram in memory, which is
 // cleared; returns false when fewer than k values were counted.  Called by a
-// whole block; *digit and *rest (the rank within the digit) in every thread.
+// whole block; *digit, *rest (the rank within the digit) and *held (its count) in
+// every thread.
 __device__ inline bool ncut_find(unsigned* __restrict__ hist, unsigned k, unsigned* s_wave, unsigned* s_pick,
-                                 unsigned* digit, unsigned* rest) {
+                                 unsigned* digit, unsigned* rest, unsigned* held) {
   constexpr int kPer = kNcutBins / kNcutThreads;
   const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
   unsigned h[kPer], sum = 0;
@@ -415,41 +399,48 @@ __device__ inline bool ncut_find(unsigned* __restrict__ hist, unsigned k, unsign
     if (before < k && before + h[j] >= k) {
       s_pick[0] = (unsigned)(kNcutBins - 1 - (kPer * t + j));
       s_pick[1] = k - before;
+      s_pick[2] = h[j];
     }
     before += h[j];
   }
   __syncthreads();
   *digit = s_pick[0];
   *rest = s_pick[1];
+  *held = s_pick[2];
   return s_pick[0] != 0xffffffffu;
 }
 
-__device__ inline u64 ncut_count(const Counters* ctr, u64 n_host) {
-  return ctr ? __hip_atomic_load(&ctr->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : n_host;
+// Stored and alive entries after gate `gate` of a chain (ctr set), or n_host.
+__device__ inline u64 ncut_count(const Counters* ctr, unsigned gate, u64 cap, u64 n_host, u64* alive) {
+  u64 n = n_host;
+  *alive = n_host;
+  if (ctr) live_load(&ctr->live[live_slot(gate)], cap, &n, alive);
+  return n;
 }
 
 template <int PASS>
 __global__ void __launch_bounds__(kNcutThreads)
 k_ncut_hist(const double* __restrict__ amps, u64 stride_y, u64 n_host, const Counters* __restrict__ ctr,
-            NcutSelect* __restrict__ sel_y, unsigned ncut) {
+            unsigned gate, u64 cap, NcutSelect* __restrict__ sel_y, unsigned ncut) {
   __shared__ unsigned h[kNcutBins];
-  __shared__ unsigned s_wave[kNcutThreads / 64], s_pick[2];
+  __shared__ unsigned s_wave[kNcutThreads / 64], s_pick[3];
   __shared__ bool s_last;
   NcutSelect* sel = sel_y + blockIdx.y;
   const double* __restrict__ a_y = amps + stride_y * blockIdx.y;
+  u64 alive;
+  const u64 n = ncut_count(ctr, gate, cap, n_host, &alive);
   if (PASS == 0) {
     // nothing to drop: every block sees the same counters (no block of this
     // launch changes them)
     if (ctr && ((__hip_atomic_load(&ctr->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFlagStopped) ||
-                __hip_atomic_load(&ctr->alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= ncut)) {
+                alive <= ncut)) {
       if (blockIdx.x == 0 && threadIdx.x == 0) sel->skip = 1;
       return;
     }
-  } else if (sel->skip) {
+  } else if (sel->skip || sel->narrow) {
     return;
   }
   for (int t = threadIdx.x; t < kNcutBins; t += kNcutThreads) h[t] = 0;
-  const u64 n = ncut_count(ctr, n_host);
   const unsigned first = PASS ? sel->prefix : 0u;
   __syncthreads();
   for (u64 i = (u64)blockIdx.x * kNcutThreads + threadIdx.x; i < n; i += (u64)gridDim.x * kNcutThreads) {
@@ -457,19 +448,20 @@ k_ncut_hist(const double* __restrict__ amps, u64 stride_y, u64 n_host, const Cou
     if (is_dead(a)) continue;
     const u64 hi = ncut_bits(a);
     if (PASS == 0) atomicAdd(&h[ncut_first(hi)], 1u);
-    else if (ncut_first(hi) == first) atomicAdd(&h[ncut_prefix(hi) & (kNcutBins - 1)], 1u);
+    else if (ncut_first(hi) == first) atomicAdd(&h[ncut_second(hi, first)], 1u);
   }
   __syncthreads();
   unsigned* hist = sel->hist[PASS];
   for (int t = threadIdx.x; t < kNcutBins; t += kNcutThreads)
     if (h[t]) atomicAdd(&hist[t], h[t]);
   if (!ncut_last_block(&sel->ticket, &s_last)) return;
-  unsigned digit, rest;
-  const bool found = ncut_find(hist, PASS ? sel->k : ncut, s_wave, s_pick, &digit, &rest);
+  unsigned digit, rest, held;
+  const bool found = ncut_find(hist, PASS ? sel->k : ncut, s_wave, s_pick, &digit, &rest, &held);
   if (threadIdx.x == 0) {
     sel->ticket = 0;
     sel->skip = found ? 0u : 1u;  // fewer than ncut alive (first pass): everything stays
-    sel->prefix = PASS ? (first << kNcutBits) | digit : digit;
+    sel->prefix = PASS ? first << kNcutBits | digit : digit;
+    sel->narrow = PASS == 0 && held <= kNcutRank ? 1u : 0u;
     sel->k = rest;
   }
 }
@@ -482,28 +474,37 @@ __device__ inline bool ncut_less(const NcutValue& x, const NcutValue& y) {
   return x.hi < y.hi || (x.hi == y.hi && x.lo < y.lo);
 }
 
-constexpr unsigned kNcutRank = 1024;  // candidates ordered by counting in LDS
-
 __global__ void __launch_bounds__(kNcutThreads)
 k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ keys, u64 n_host,
-            Counters* __restrict__ ctr, NcutSelect* __restrict__ sel_y, unsigned* __restrict__ cand_y, u64 cand_stride) {
+            Counters* __restrict__ ctr, unsigned gate, u64 cap, NcutSelect* __restrict__ sel_y,
+            unsigned* __restrict__ cand_y, u64 cand_stride) {
   __shared__ NcutValue s_val[kNcutRank];
   __shared__ unsigned s_hist[256], s_pick[2];
   __shared__ bool s_last;
+  __shared__ unsigned s_drop;
   NcutSelect* sel = sel_y + blockIdx.y;
   if (sel->skip) return;
+  if (threadIdx.x == 0) s_drop = 0;
+  __syncthreads();
   double* __restrict__ a_y = amps + stride_y * blockIdx.y;
   unsigned* __restrict__ cand = cand_y + cand_stride * blockIdx.y;
-  const u64 n = ncut_count(ctr, n_host);
+  u64 alive_in;
+  const u64 n = ncut_count(ctr, gate, cap, n_host, &alive_in);
   const unsigned prefix = sel->prefix;
+  const bool narrow = sel->narrow != 0;
   const int lane = (int)(threadIdx.x & 63u);
-  unsigned long long dropped = 0;
+  unsigned dropped = 0;
   const u64 step = (u64)gridDim.x * kNcutThreads;
   for (u64 base = (u64)blockIdx.x * kNcutThreads; base < n; base += step) {  // same trips in the whole block
     const u64 i = base + threadIdx.x;
     const double a = i < n ? a_y[i] : dead_value();
     const bool alive = !is_dead(a);
-    const unsigned p = alive ? ncut_prefix(ncut_bits(a)) : 0u;
+    unsigned p = 0;
+    if (alive) {
+      const u64 hi = ncut_bits(a);
+      p = ncut_first(hi);
+      if (!narrow) p = p << kNcutBits | ncut_second(hi, p);
+    }
     if (alive && p < prefix) {
       a_y[i] = dead_value();
       ++dropped;
@@ -519,11 +520,17 @@ k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ key
                            __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  auto count_drops = [&]() {
+  auto count_drops = [&]() {  // one add of the block
     if (!ctr) return;
-    unsigned long long d = dropped;
+    unsigned d = (unsigned)dropped;
     for (int off = 32; off > 0; off >>= 1) d += __shfl_xor(d, off);
-    if (lane == 0 && d) atomicAdd(&ctr->alive, (u64)(0ULL - d));
+    if (lane == 0 && d) atomicAdd(&s_drop, d);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_drop) {
+      atomicAdd((unsigned long long*)&ctr->live[live_slot(gate)].dalive, (unsigned long long)(0ULL - (u64)s_drop));
+      s_drop = 0;
+    }
+    __syncthreads();
   };
   count_drops();
   if (!ncut_last_block(&sel->ticket, &s_last)) return;
@@ -552,18 +559,18 @@ k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ key
       }
     }
   } else if (k < nc) {
-    // many entries share 24 bits (equal amplitudes): radix select over the
-    // candidates, eight bits at a time from the 39 low bits of |c| to the key
-    NcutValue want{(u64)prefix << 39, 0}, mask{~0ULL << 39, 0};
-    for (int d = 0; d < 13; ++d) {
-      const int sh = d < 5 ? 32 - 8 * d : 56 - 8 * (d - 5);  // 39 bits of |c| as 7 + 4 x 8
+    // many entries share both digits (equal amplitudes): radix select over the
+    // candidates, eight bits at a time from |c| to the key
+    NcutValue want{0, 0}, mask{0, 0};
+    for (int d = 0; d < 16; ++d) {
+      const int sh = 56 - 8 * (d & 7);
       for (int t = threadIdx.x; t < 256; t += kNcutThreads) s_hist[t] = 0;
       __syncthreads();
       for (unsigned c = threadIdx.x; c < nc; c += kNcutThreads) {
         u64 at;
         const NcutValue v = value(c, &at);
         if ((v.hi & mask.hi) != want.hi || (v.lo & mask.lo) != want.lo) continue;
-        atomicAdd(&s_hist[((d < 5 ? v.hi : v.lo) >> sh) & (d == 0 ? 127u : 255u)], 1u);
+        atomicAdd(&s_hist[((d < 8 ? v.hi : v.lo) >> sh) & 255u], 1u);
       }
       __syncthreads();
       if (threadIdx.x < 64) {  // four bins a lane, from the largest
@@ -591,9 +598,9 @@ k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ key
       __syncthreads();
       const u64 digit = s_pick[0];
       k = s_pick[1];
-      if (d < 5) {
+      if (d < 8) {
         want.hi |= digit << sh;
-        mask.hi |= (d == 0 ? 127ULL : 255ULL) << sh;
+        mask.hi |= 255ULL << sh;
       } else {
         want.lo |= digit << sh;
         mask.lo |= 255ULL << sh;
@@ -625,12 +632,22 @@ __global__ void k_reset_reference(u64* __restrict__ keys, double* __restrict__ a
     amps[0] = 1.0;
     ctr->n = 1;
     ctr->alive = 1;
-    ctr->app = 0;
-    ctr->dalive = 0;
-    ctr->ticket = 0;
     ctr->flags = 0;
     ctr->stop_gate = 0;
   }
+}
+
+__global__ void k_live_begin(Counters* __restrict__ ctr, unsigned g) {
+  if (threadIdx.x != 0) return;
+  for (int j = 0; j < 3; ++j) ctr->live[j] = LiveCounts{0, 0, 0, 0};
+  ctr->live[live_before(g)].n = ctr->n;
+  ctr->live[live_before(g)].alive = ctr->alive;
+}
+
+__global__ void k_live_end(Counters* __restrict__ ctr, u64 cap, unsigned M) {
+  if (threadIdx.x != 0) return;
+  const unsigned g = (ctr->flags & kFlagStopped) ? (unsigned)ctr->stop_gate : M;
+  live_load(&ctr->live[live_before(g)], cap, &ctr->n, &ctr->alive);
 }
 
 // Same, with the entry count read from the device counters.
@@ -652,10 +669,11 @@ __global__ void k_mark_dead_range(double* amps, u64 lo, u64 hi) {
 // chain that starts from a caller-supplied state, whose untouched entries
 // have not been tested against eps yet).  Skipped if the chain has stopped.
 __global__ void __launch_bounds__(256)
-k_prune_all(double* __restrict__ amps, Counters* __restrict__ ctr, double eps) {
+k_prune_all(double* __restrict__ amps, Counters* __restrict__ ctr, unsigned gate, u64 cap, double eps) {
   if (__hip_atomic_load(&ctr->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFlagStopped)
     return;
-  const u64 n = __hip_atomic_load(&ctr->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  u64 n, alive;
+  live_load(&ctr->live[live_slot(gate)], cap, &n, &alive);
   unsigned long long dropped = 0;
   const u64 stride = (u64)gridDim.x * blockDim.x;
   for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -670,17 +688,19 @@ k_prune_all(double* __restrict__ amps, Counters* __restrict__ ctr, double eps) {
     // wave sum of dropped, then one atomic per wave
     unsigned long long s = dropped;
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (__lane_id() == 0) atomicAdd(&ctr->alive, (u64)(0ULL - s));
+    if (__lane_id() == 0)
+      atomicAdd((unsigned long long*)&ctr->live[live_slot(gate)].dalive, (unsigned long long)(0ULL - s));
   }
 }
 
-// Copy amps[0, n) of the current state to dst and record n, unless the chain
+// Copy amps[0, n) of the state before a gate to dst and record n, unless the chain
 // has stopped (the host re-enqueues the copy when it resumes).
-__global__ void k_ckpt_save(const double* __restrict__ amps, const Counters* __restrict__ ctr,
-                            double* __restrict__ dst, u64* __restrict__ dst_n) {
+__global__ void k_ckpt_save(const double* __restrict__ amps, const Counters* __restrict__ ctr, unsigned gate,
+                            u64 cap, double* __restrict__ dst, u64* __restrict__ dst_n) {
   if (__hip_atomic_load(&ctr->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFlagStopped)
     return;
-  const u64 n = __hip_atomic_load(&ctr->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  u64 n, alive;
+  live_load(&ctr->live[live_before(gate)], cap, &n, &alive);
   const u64 stride = (u64)gridDim.x * blockDim.x;
   for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = amps[i];
   if (blockIdx.x == 0 && threadIdx.x == 0) *dst_n = n;
@@ -729,15 +749,15 @@ hipError_t launch_filter_build(const DeviceState& st, u64 n, int grid, hipStream
 
 size_t ncut_select_bytes() { return sizeof(NcutSelect); }
 
-hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Counters* ctr, void* select,
+hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Counters* ctr, unsigned gate, u64 cap, void* select,
                        unsigned* cand, u64 cand_stride, unsigned ncut, u64 n_most, int states, hipStream_t stream) {
   // one block per compute unit at most: every block adds its nonzero bins to
   // the same few addresses
   const dim3 grid((unsigned)grid_for(n_most, kNcutThreads, 256), (unsigned)states);
   NcutSelect* sel = (NcutSelect*)select;
-  hipLaunchKernelGGL(k_ncut_hist<0>, grid, dim3(kNcutThreads), 0, stream, amps, stride, n_host, ctr, sel, ncut);
-  hipLaunchKernelGGL(k_ncut_hist<1>, grid, dim3(kNcutThreads), 0, stream, amps, stride, n_host, ctr, sel, ncut);
-  hipLaunchKernelGGL(k_ncut_mark, grid, dim3(kNcutThreads), 0, stream, amps, stride, keys, n_host, ctr, sel, cand,
+  hipLaunchKernelGGL(k_ncut_hist<0>, grid, dim3(kNcutThreads), 0, stream, amps, stride, n_host, ctr, gate, cap, sel, ncut);
+  hipLaunchKernelGGL(k_ncut_hist<1>, grid, dim3(kNcutThreads), 0, stream, amps, stride, n_host, ctr, gate, cap, sel, ncut);
+  hipLaunchKernelGGL(k_ncut_mark, grid, dim3(kNcutThreads), 0, stream, amps, stride, keys, n_host, ctr, gate, cap, sel, cand,
                      cand_stride);
   return hipGetLastError();
 }
@@ -754,21 +774,21 @@ hipError_t launch_hash_build_dev(const DeviceState& st, int grid, hipStream_t st
 }
 
 hipError_t launch_gate(const DeviceState& st, const OpDesc& op, double c, double sn, double eps,
-                       u64* gate_n_in, int check_cap, unsigned gate_index, u64 max_keys, int grid,
+                       u64* gate_n_in, unsigned gate_index, u64 max_keys, int grid,
                        hipStream_t stream, u64* gate_n_act) {
   if (st.cap >= kGateWideCap)
     hipLaunchKernelGGL(k_gate<kGateScanWide>, dim3(grid), dim3(kGateThreads), 0, stream, st.keys, st.amps,
-                       st.hash, st.hmask, st.cap, st.ctr, op, c, sn, eps, gate_n_in, check_cap, gate_index,
+                       st.hash, st.hmask, st.cap, st.ctr, op, c, sn, eps, gate_n_in, gate_index,
                        max_keys, gate_n_act);
   else
     hipLaunchKernelGGL(k_gate<kGateScanNarrow>, dim3(grid), dim3(kGateThreads), 0, stream, st.keys, st.amps,
-                       st.hash, st.hmask, st.cap, st.ctr, op, c, sn, eps, gate_n_in, check_cap, gate_index,
+                       st.hash, st.hmask, st.cap, st.ctr, op, c, sn, eps, gate_n_in, gate_index,
                        max_keys, gate_n_act);
   return hipGetLastError();
 }
 
-hipError_t launch_prune_all(const DeviceState& st, double eps, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL(k_prune_all, dim3(grid), dim3(256), 0, stream, st.amps, st.ctr, eps);
+hipError_t launch_prune_all(const DeviceState& st, double eps, unsigned gate, int grid, hipStream_t stream) {
+  hipLaunchKernelGGL(k_prune_all, dim3(grid), dim3(256), 0, stream, st.amps, st.ctr, gate, st.cap, eps);
   return hipGetLastError();
 }
 
@@ -795,9 +815,19 @@ hipError_t launch_adjoint_rec(const PairRec* log, const u64* log_count, double* 
   return hipGetLastError();
 }
 
-hipError_t launch_ckpt_save(const DeviceState& st, double* dst, u64* dst_n, int grid,
+hipError_t launch_live_begin(const DeviceState& st, unsigned g, hipStream_t stream) {
+  hipLaunchKernelGGL(k_live_begin, dim3(1), dim3(64), 0, stream, st.ctr, g);
+  return hipGetLastError();
+}
+
+hipError_t launch_live_end(const DeviceState& st, unsigned M, hipStream_t stream) {
+  hipLaunchKernelGGL(k_live_end, dim3(1), dim3(64), 0, stream, st.ctr, st.cap, M);
+  return hipGetLastError();
+}
+
+hipError_t launch_ckpt_save(const DeviceState& st, unsigned gate, double* dst, u64* dst_n, int grid,
                             hipStream_t stream) {
-  hipLaunchKernelGGL(k_ckpt_save, dim3(grid), dim3(256), 0, stream, st.amps, st.ctr, dst, dst_n);
+  hipLaunchKernelGGL(k_ckpt_save, dim3(grid), dim3(256), 0, stream, st.amps, st.ctr, gate, st.cap, dst, dst_n);
   return hipGetLastError();
 }
 

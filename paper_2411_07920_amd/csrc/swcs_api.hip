@@ -620,11 +620,12 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
       int r = ncut_reserve(c, 1, c->st.cap);
       if (r) return r;
     }
+    HIP_TRY(c, launch_live_begin(c->st, (unsigned)g0, c->stream), "counters");
     for (int64_t g = g0; g < M; ++g) {
       if (ckpt && g % c->seg == 0) {
         const int j = (int)(g / c->seg);
         HIP_TRY(c, c->ckpt[j].ensure(c->st.cap * sizeof(double)), "alloc checkpoint");
-        HIP_TRY(c, launch_ckpt_save(c->st, c->ckpt[j].as<double>(), c->ckpt_n.as<u64>() + j,
+        HIP_TRY(c, launch_ckpt_save(c->st, (unsigned)g, c->ckpt[j].as<double>(), c->ckpt_n.as<u64>() + j,
                                     grid_blocks(c, c->st.cap / 4, 256), c->stream), "checkpoint");
       }
       const OpDesc& op = c->ops_host[op_idx[g]];
@@ -633,7 +634,7 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
                                    grid_blocks(c, c->st.cap / 2, 256), c->stream, c->gate_n_act.as<u64>() + g),
                 "generator gate");
       else
-        TIMED(c, SWCS_K_GATE, launch_gate(c->st, op, cs[g], sn[g], eps, c->gate_n_in.as<u64>() + g, 1,
+        TIMED(c, SWCS_K_GATE, launch_gate(c->st, op, cs[g], sn[g], eps, c->gate_n_in.as<u64>() + g,
                                (unsigned)g, c->sector, gate_grid(c, c->st.cap / 2, gate_scan_tile(c->st.cap)), c->stream,
                                c->gate_n_act.as<u64>() + g),
                 "gate");
@@ -641,11 +642,12 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
       // state that were never tested against eps are pruned once, after the
       // first gate, so every later state is exactly P(U psi).
       if (g == 0 && eps > 0.0)
-        HIP_TRY(c, launch_prune_all(c->st, eps, grid_blocks(c, c->st.cap / 2, 256), c->stream), "prune");
+        HIP_TRY(c, launch_prune_all(c->st, eps, (unsigned)g, grid_blocks(c, c->st.cap / 2, 256), c->stream), "prune");
       if (ncut)
-        HIP_TRY(c, launch_ncut(c->st.amps, 0, c->st.keys, 0, c->st.ctr, c->ncut_state.p, c->ncut_cand.as<unsigned>(), 0,
+        HIP_TRY(c, launch_ncut(c->st.amps, 0, c->st.keys, 0, c->st.ctr, (unsigned)g, c->st.cap, c->ncut_state.p, c->ncut_cand.as<unsigned>(), 0,
                                ncut, c->st.cap, 1, c->stream), "ncut");
     }
+    HIP_TRY(c, launch_live_end(c->st, (unsigned)M, c->stream), "counters");
     hipError_t e;
     Counters h = read_counters(c, &e);
     if (e != hipSuccess) return hip_fail(c, e, "read counters");
@@ -2344,7 +2346,7 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
           TIMED(c, SWCS_K_GATE_REPLAY, launch_gate_replay(c->st, W, n, gates, eps_r, G, t, segs,
                                                           gate_grid(c, n, kReplayTile), c->stream), "replay");
         if (c->a_ncut)
-          HIP_TRY(c, launch_ncut(W, n, c->st.keys, n, nullptr, c->ncut_state.p, c->ncut_cand.as<unsigned>(), n,
+          HIP_TRY(c, launch_ncut(W, n, c->st.keys, n, nullptr, 0, n, c->ncut_state.p, c->ncut_cand.as<unsigned>(), n,
                                  (unsigned)c->a_ncut, n, segs, c->stream), "ncut");
       }
       // Gates of few records are walked back by one workgroup, the others by a

@@ -140,18 +140,82 @@ __device__ inline bool acc_find(const AccSlot* __restrict__ tab, u64 mask, u64 k
   return false;
 }
 
-// Device counters of the state.  n: stored entries (alive or dead);
-// alive: entries that are part of the state; app / dalive / ticket: per-gate
-// scratch folded in by the last block of each gate launch; flags: error bits.
-struct Counters {
+// kFlagOverflow: an append or table insert found no room (a bug guard: the
+// host sizes buffers so it cannot happen).  kFlagStopped: a gate found too
+// little capacity and did nothing; later gates of the chain skip too.
+enum : unsigned int { kFlagOverflow = 1u, kFlagStopped = 2u };
+
+// Entry counts of a chain that runs one launch per gate: n stored and alive ones
+// of them before the gate, and what the gate adds, by atomics.
+struct LiveCounts {
   u64 n;
   u64 alive;
   u64 app;
   long long dalive;
-  unsigned int ticket;
-  unsigned int flags;
-  u64 stop_gate;
 };
+
+// Device counters of the state.  n: stored entries (alive or dead);
+// alive: entries that are part of the state; flags: error bits.
+// live: within a chain, three counts in rotation: gate g reads slot g - 1, adds
+// to slot g and clears slot g + 1, so that no block has to be the last one and
+// fold the sums in (gate launch at 40,000 entries 7.4 -> 7.0 us; what is left is
+// the chain from counts and keys over index probe and partner to the append).
+// k_live_begin fills the slot before the first gate, k_live_end leaves n and alive.
+struct Counters {
+  u64 n;
+  u64 alive;
+  unsigned int flags;
+  unsigned int pad;
+  u64 stop_gate;
+  LiveCounts live[3];
+};
+
+__host__ __device__ inline unsigned live_slot(unsigned gate) { return gate % 3u; }
+__host__ __device__ inline unsigned live_before(unsigned gate) { return (gate + 2u) % 3u; }
+__host__ __device__ inline unsigned live_after(unsigned gate) { return (gate + 1u) % 3u; }
+
+// Stored and alive entries by a slot that no block of the launch changes: plain
+// loads, which a whole launch serves from its caches (loads that bypass them,
+// by every wavefront of some hundred blocks, queued up at one memory channel).
+__device__ inline void live_load(const LiveCounts* L, u64 cap, u64* n, u64* alive) {
+  const u64 n0 = L->n, app = L->app;
+  *n = n0 + (app < cap - n0 ? app : cap - n0);
+  *alive = (u64)((long long)L->alive + L->dalive);
+}
+
+// Start of a gate, the same in every thread of the launch: whether it runs, and
+// the entry counts.  A stopped chain skips every later gate; the host resumes it
+// after growing.  Appends are bounded by `grow` times the alive sources and by
+// the number of keys not yet stored (max_keys = size of the electron-number
+// sector), so n_in + min(grow alive_in, max_keys - n_in) <= cap guarantees the
+// gate fits.  Nothing has been modified when it stops.
+__device__ inline bool gate_begin(Counters* ctr, unsigned gate, u64 cap, u64 max_keys, unsigned grow, u64* n_in,
+                                  u64* gate_n_in) {
+  const unsigned fl = ctr->flags;
+  u64 n, alive;
+  live_load(&ctr->live[live_before(gate)], cap, &n, &alive);
+  *n_in = n;
+  if (fl & kFlagStopped) return false;
+  const u64 room = max_keys > n ? max_keys - n : 0, most = grow * alive;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (n + (most < room ? most : room) > cap) {
+    if (first) {
+      ctr->stop_gate = gate;
+      atomicOr(&ctr->flags, kFlagStopped);
+    }
+    return false;
+  }
+  if (first) {
+    LiveCounts& own = ctr->live[live_slot(gate)];
+    __hip_atomic_store(&own.n, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&own.alive, alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    LiveCounts& next = ctr->live[live_after(gate)];
+    __hip_atomic_store(&next.app, (u64)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&next.dalive, 0LL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (gate_n_in) *gate_n_in = alive;
+  }
+  return true;
+}
 
 // Waits until this wavefront's device-scope atomics (and its other memory
 // operations) are done.  Before a ticket that announces only such atomics this
@@ -167,11 +231,6 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-
-// kFlagOverflow: an append or table insert found no room (a bug guard: the
-// host sizes buffers so it cannot happen).  kFlagStopped: a gate found too
-// little capacity and did nothing; later gates of the chain skip too.
-enum : unsigned int { kFlagOverflow = 1u, kFlagStopped = 2u };
 
 // Integrals on the device, spin-free spatial arrays.
 struct Ints {
@@ -343,6 +402,10 @@ struct StarRec;
 hipError_t launch_gen_gate(const DeviceState& st, const GenGate& g, double eps, u64* gate_n_in,
                            unsigned gate_index, u64 max_keys, int grid, hipStream_t stream,
                            u64* gate_n_act = nullptr);
+// The counts before gate g of a chain, from the state's; the state's counts after
+// the chain's gates up to M, or up to the one that stopped it.
+hipError_t launch_live_begin(const DeviceState& st, unsigned g, hipStream_t stream);
+hipError_t launch_live_end(const DeviceState& st, unsigned M, hipStream_t stream);
 struct ReplayGroup;
 hipError_t launch_gen_replay(const DeviceState& st, double* work, u64 n, const GenGate* gens, double eps,
                              const ReplayGroup& G, int step, int segs, int grid, hipStream_t stream);
@@ -356,9 +419,9 @@ hipError_t launch_nan_if_flag(const Counters* ctr, unsigned bit, double* out, lo
 hipError_t launch_hash_clear(HashSlot* tab, u64 slots, hipStream_t stream);
 hipError_t launch_hash_build(const DeviceState& st, u64 n, hipStream_t stream);
 hipError_t launch_gate(const DeviceState& st, const OpDesc& op, double c, double sn, double eps,
-                       u64* gate_n_in, int check_cap, unsigned gate_index, u64 max_keys, int grid,
+                       u64* gate_n_in, unsigned gate_index, u64 max_keys, int grid,
                        hipStream_t stream, u64* gate_n_act = nullptr);
-hipError_t launch_prune_all(const DeviceState& st, double eps, int grid, hipStream_t stream);
+hipError_t launch_prune_all(const DeviceState& st, double eps, unsigned gate, int grid, hipStream_t stream);
 hipError_t launch_hash_build_dev(const DeviceState& st, int grid, hipStream_t stream);
 hipError_t launch_filter_build(const DeviceState& st, u64 n, int grid, hipStream_t stream);
 hipError_t launch_reset_reference(const DeviceState& st, u64 ref, hipStream_t stream);
@@ -367,7 +430,7 @@ hipError_t launch_reset_reference(const DeviceState& st, u64 ref, hipStream_t st
 // use; cand room for one index per entry (cand_stride apart).  n_most bounds
 // the stored entries for the launch grid.
 size_t ncut_select_bytes();
-hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Counters* ctr, void* select,
+hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Counters* ctr, unsigned gate, u64 cap, void* select,
                        unsigned* cand, u64 cand_stride, unsigned ncut, u64 n_most, int states, hipStream_t stream);
 int lds_chain_capacity();
 hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, int g0, int M, double eps,
@@ -388,7 +451,7 @@ hipError_t launch_adjoint_walk(const ReplayGroup& G, const GateDesc* gates, cons
                                double* mu, double* partial, u64 pstride, hipStream_t stream);
 hipError_t launch_adjoint_rec(const PairRec* log, const u64* log_count, double* mu, double c,
                               double sn, double* partial, int grid, hipStream_t stream);
-hipError_t launch_ckpt_save(const DeviceState& st, double* dst, u64* dst_n, int grid,
+hipError_t launch_ckpt_save(const DeviceState& st, unsigned gate, double* dst, u64* dst_n, int grid,
                             hipStream_t stream);
 hipError_t launch_restore(double* work, const double* const* ckpt, const u64* ckpt_n, int seg0, int segs, u64 n,
                           hipStream_t stream);
