@@ -3,8 +3,11 @@
 // kLdsCap determinants (16 B of keys and amplitudes plus 8 B of hash index
 // each) fits the 160 KB LDS of one CU; the gates then cost LDS latency
 // instead of one kernel launch each.  The per-entry arithmetic is shared
-// with the HBM kernels (gate_ops.h), so results are identical bit for bit.
-#include "gate_ops.h"
+// with the HBM kernels (gate_ops.h, gen_ops.h), so results are identical bit for
+// bit.  Chains with overlapping generators have instances of their own (their
+// gate needs more registers): 21 generators of 8 orbitals, 750 determinants, with
+// gradients 841 us gate by gate in HBM, 357 here.
+#include "gen_ops.h"
 
 namespace swcs {
 
@@ -77,12 +80,13 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
 // moved into LDS for the duration.  Checkpoints (amplitudes before gate g
 // for g % seg == 0) and the per-gate input sizes are written to HBM.  If a
 // gate might not fit, the kernel stops before it: the state is written back
-// and ctr->stop_gate / kFlagStopped tell the host where to continue.
-template <int CAP>
+// and ctr->stop_gate / kFlagStopped tell the host where to continue.  STAR:
+// gates with kinds[g] set are overlapping generators gens[g].
+template <int CAP, bool STAR>
 __global__ void __launch_bounds__(kChainThreads)
 k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restrict__ ctr,
-            const GateDesc* __restrict__ gates, int g0, int M, double eps, int prune_first,
-            double* const* __restrict__ ckpt, u64* __restrict__ ckpt_n, int seg,
+            const GateDesc* __restrict__ gates, const int* __restrict__ kinds, const GenGate* __restrict__ gens,
+            int g0, int M, double eps, int prune_first, double* const* __restrict__ ckpt, u64* __restrict__ ckpt_n, int seg,
             u64* __restrict__ gate_n_in, u64 max_keys, unsigned ncut) {
   __shared__ NcutState nst;
   __shared__ u64 skeys[CAP];
@@ -96,6 +100,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
   __shared__ int s_dal[3];
   __shared__ unsigned s_n0, s_alive0;
   __shared__ GateDesc sg[kGateChunk];
+  __shared__ int sk[STAR ? kGateChunk : 1];
   const int tid = threadIdx.x;
   if (tid == 0) {
     s_n0 = (unsigned)ctr->n;
@@ -127,9 +132,13 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
     // Every earlier read of sg and every write of the previous gate happened
     // before the previous gate's barrier (or the index build's).
     if ((g - g0) % kGateChunk == 0) {
-      for (int t = tid; t < kGateChunk && g + t < M; t += kChainThreads) sg[t] = gates[g + t];
+      for (int t = tid; t < kGateChunk && g + t < M; t += kChainThreads) {
+        sg[t] = gates[g + t];
+        if (STAR) sk[t] = kinds[g + t];
+      }
       __syncthreads();
     }
+    const bool star = STAR && sk[(g - g0) % kGateChunk] != 0;  // uniform
     if (ckpt && g % seg == 0) {
       double* dst = ckpt[g / seg];
       for (unsigned i = tid; i < n; i += kChainThreads) dst[i] = samps[i];
@@ -137,22 +146,34 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
       __syncthreads();  // the copy precedes the gate's updates
     }
     const u64 room = max_keys > n ? max_keys - n : 0;
-    if ((u64)n + ((u64)alive < room ? (u64)alive : room) > (u64)CAP) {
+    const u64 most = star ? 2 * (u64)alive : (u64)alive;
+    if ((u64)n + (most < room ? most : room) > (u64)CAP) {
       stop = g;
       break;  // uniform: every thread holds the same n and alive
     }
     const int slot = g % 3;
-    const GateDesc gd = sg[(g - g0) % kGateChunk];
     int dal = 0;
-    for (unsigned i = tid; i < n; i += kChainThreads) {
-      const GateOut o = gate_entry(S, i, gd.op, gd.c, gd.s, eps);
-      dal += (int)o.dalive;
-      if (o.append) {
-        const unsigned idx = n + atomicAdd(&s_app[slot], 1u);
-        skeys[idx] = o.key;
-        samps[idx] = o.val;
-        __threadfence_block();
-        S.insert(o.key, (int)idx);
+    auto append = [&](u64 key, double val) {
+      const unsigned idx = n + atomicAdd(&s_app[slot], 1u);
+      skeys[idx] = key;
+      samps[idx] = val;
+      __threadfence_block();
+      S.insert(key, (int)idx);
+    };
+    if (star) {
+      const GenGate gg = gens[g];
+      for (unsigned i = tid; i < n; i += kChainThreads) {
+        const GenOut o = gen_entry(S, i, gg, eps);
+        dal += (int)o.dalive;
+        if (o.napp > 0) append(o.key[0], o.val[0]);
+        if (o.napp > 1) append(o.key[1], o.val[1]);
+      }
+    } else {
+      const GateDesc gd = sg[(g - g0) % kGateChunk];
+      for (unsigned i = tid; i < n; i += kChainThreads) {
+        const GateOut o = gate_entry(S, i, gd.op, gd.c, gd.s, eps);
+        dal += (int)o.dalive;
+        if (o.append) append(o.key, o.val);
       }
     }
     if (dal) atomicAdd(&s_dal[slot], dal);
@@ -210,18 +231,20 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
 constexpr int kMaxSeg = 256;  // gate descriptors a segment stages in LDS at a time
 constexpr int kWaves = kChainThreads / 64;
 
-template <int CAP>
+template <int CAP, bool STAR>
 __global__ void __launch_bounds__(kChainThreads)
 k_adjoint_replay_lds(const u64* __restrict__ keys, unsigned n, const GateDesc* __restrict__ gates,
+                     const int* __restrict__ kinds, const GenGate* __restrict__ gens,
                      int M, int seg, double eps, const double* const* __restrict__ ckpt,
-                     const u64* __restrict__ ckpt_n, PairRec* __restrict__ logbuf,
+                     const u64* __restrict__ ckpt_n, char* __restrict__ logbuf, size_t log_bytes,
                      unsigned* __restrict__ logcnt, unsigned* __restrict__ flags, unsigned ncut) {
   __shared__ NcutState nst;
   __shared__ u64 skeys[CAP];
   __shared__ double sW[CAP];
   __shared__ int sslots[2 * CAP];
   __shared__ GateDesc sg[kMaxSeg];
-  __shared__ unsigned s_cnt;
+  __shared__ int sk[STAR ? kMaxSeg : 1];
+  __shared__ unsigned s_cnt, s_star;
   const int tid = threadIdx.x;
   const int j = blockIdx.x;
   const int g_lo = j * seg;
@@ -233,7 +256,7 @@ k_adjoint_replay_lds(const u64* __restrict__ keys, unsigned n, const GateDesc* _
     skeys[i] = keys[i];
     sW[i] = (i < nj) ? src[i] : dead_value();
   }
-  if (tid == 0) s_cnt = 0;
+  if (tid == 0) s_cnt = s_star = 0;
   __syncthreads();
   LdsStore L{skeys, sW, sslots, 2u * CAP - 1u};
   for (unsigned i = tid; i < n; i += kChainThreads) L.insert(skeys[i], (int)i);
@@ -242,11 +265,34 @@ k_adjoint_replay_lds(const u64* __restrict__ keys, unsigned n, const GateDesc* _
   for (int g = g_lo; g < g_hi; ++g) {
     if ((g - g_lo) % kMaxSeg == 0) {
       __syncthreads();
-      for (int t = tid; t < kMaxSeg && g + t < g_hi; t += kChainThreads) sg[t] = gates[g + t];
+      for (int t = tid; t < kMaxSeg && g + t < g_hi; t += kChainThreads) {
+        sg[t] = gates[g + t];
+        if (STAR) sk[t] = kinds[g + t];
+      }
     }
     __syncthreads();
     const GateDesc gd = sg[(g - g_lo) % kMaxSeg];
-    PairRec* lg = logbuf + (size_t)g * n;
+    PairRec* lg = (PairRec*)(logbuf + (size_t)g * log_bytes);
+    if (STAR && sk[(g - g_lo) % kMaxSeg]) {  // uniform
+      const GenGate gg = gens[g];
+      StarRec* ls = (StarRec*)(lg + n);
+      for (unsigned i0 = 0; i0 < n; i0 += kChainThreads) {
+        const unsigned i = i0 + tid;
+        GenOut o;
+        o.napp = 0;
+        o.kind = 0;
+        if (i < n) o = gen_entry(L, i, gg, eps);
+        if (o.napp) atomicOr(flags, kFlagOverflow);  // cannot happen: all keys are stored
+        const u64 mp = __ballot(o.kind == 1), ms = __ballot(o.kind == 2);
+        unsigned bp = 0, bs = 0;
+        if (lane == 0 && mp) bp = atomicAdd(&s_cnt, (unsigned)__popcll(mp));
+        if (lane == 0 && ms) bs = atomicAdd(&s_star, (unsigned)__popcll(ms));
+        bp = __shfl(bp, 0);
+        bs = __shfl(bs, 0);
+        if (o.kind == 1) lg[bp + (unsigned)__popcll(mp & below)] = o.pr;
+        if (o.kind == 2) ls[bs + (unsigned)__popcll(ms & below)] = o.sr;
+      }
+    } else
     for (unsigned i0 = 0; i0 < n; i0 += kChainThreads) {
       const unsigned i = i0 + tid;
       GateOut o{false, 0ULL, 0.0, 0, false, kNoEntry, kNoEntry, 0.0, 0.0, 0};
@@ -264,16 +310,18 @@ k_adjoint_replay_lds(const u64* __restrict__ keys, unsigned n, const GateDesc* _
     __syncthreads();
     if (tid == 0) {
       logcnt[g] = s_cnt;
-      s_cnt = 0;
+      if (STAR) logcnt[M + g] = s_star;
+      s_cnt = s_star = 0;
     }
     if (ncut) lds_ncut(sW, skeys, n, ncut, nst);
   }
 }
 
-template <int CAP>
+template <int CAP, bool STAR>
 __global__ void __launch_bounds__(kChainThreads)
-k_adjoint_reverse_lds(unsigned n, const GateDesc* __restrict__ gates, int M,
-                      const double* __restrict__ mu_init, const PairRec* __restrict__ logbuf,
+k_adjoint_reverse_lds(unsigned n, const GateDesc* __restrict__ gates, const int* __restrict__ kinds,
+                      const GenGate* __restrict__ gens, int M,
+                      const double* __restrict__ mu_init, const char* __restrict__ logbuf, size_t log_bytes,
                       const unsigned* __restrict__ logcnt, double* __restrict__ dE_part,
                       double* __restrict__ dE) {
   __shared__ double smu[CAP];
@@ -283,13 +331,14 @@ k_adjoint_reverse_lds(unsigned n, const GateDesc* __restrict__ gates, int M,
   LdsMu mu{smu};
   // The first record of this thread, the count and the descriptor of the
   // next (earlier) gate are loaded while the current gate is processed.
+  auto log_of = [&](int g) { return (const PairRec*)(logbuf + (size_t)g * log_bytes); };
   PairRec cur{};
   unsigned c_cur = 0;
   GateDesc gd_cur{};
   if (M > 0) {
     gd_cur = gates[M - 1];
     c_cur = logcnt[M - 1];
-    if ((unsigned)tid < n) cur = logbuf[(size_t)(M - 1) * n + tid];
+    if ((unsigned)tid < n) cur = log_of(M - 1)[tid];
   }
   __syncthreads();
   for (int g = M - 1; g >= 0; --g) {
@@ -299,13 +348,19 @@ k_adjoint_reverse_lds(unsigned n, const GateDesc* __restrict__ gates, int M,
     if (g > 0) {
       gd_nxt = gates[g - 1];
       c_nxt = logcnt[g - 1];
-      if ((unsigned)tid < n) nxt = logbuf[(size_t)(g - 1) * n + tid];
+      if ((unsigned)tid < n) nxt = log_of(g - 1)[tid];
     }
     double acc = 0.0;
     if ((unsigned)tid < c_cur) acc += adjoint_pair(cur, mu, gd_cur.c, gd_cur.s);
-    const PairRec* lg = logbuf + (size_t)g * n;
+    const PairRec* lg = log_of(g);
     for (unsigned r = tid + kChainThreads; r < c_cur; r += kChainThreads)
       acc += adjoint_pair(lg[r], mu, gd_cur.c, gd_cur.s);
+    if (STAR && kinds[g]) {  // uniform
+      const GenGate gg = gens[g];
+      const unsigned ns = logcnt[M + g];
+      const StarRec* ls = (const StarRec*)(lg + n);
+      for (unsigned r = tid; r < ns; r += kChainThreads) acc += adjoint_star(ls[r], mu, gg);
+    }
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
     if (lane == 0) dE_part[(size_t)g * kWaves + wave] = acc;
     __syncthreads();  // every mu update of gate g precedes gate g - 1
@@ -323,33 +378,43 @@ k_adjoint_reverse_lds(unsigned n, const GateDesc* __restrict__ gates, int M,
 
 int lds_chain_capacity() { return kLdsCap; }
 
-hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, int g0, int M, double eps,
-                            int prune_first, double* const* ckpt, u64* ckpt_n, int seg,
+hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, const int* kinds, const GenGate* gens,
+                            int g0, int M, double eps, int prune_first, double* const* ckpt, u64* ckpt_n, int seg,
                             u64* gate_n_in, u64 max_keys, unsigned ncut, hipStream_t stream) {
-  hipLaunchKernelGGL(k_chain_lds<kLdsCap>, dim3(1), dim3(kChainThreads), 0, stream, st.keys,
-                     st.amps, st.ctr, gates, g0, M, eps, prune_first, ckpt, ckpt_n, seg, gate_n_in,
-                     max_keys, ncut);
+  if (kinds)
+    hipLaunchKernelGGL((k_chain_lds<kLdsCap, true>), dim3(1), dim3(kChainThreads), 0, stream, st.keys, st.amps, st.ctr,
+                       gates, kinds, gens, g0, M, eps, prune_first, ckpt, ckpt_n, seg, gate_n_in, max_keys, ncut);
+  else
+    hipLaunchKernelGGL((k_chain_lds<kLdsCap, false>), dim3(1), dim3(kChainThreads), 0, stream, st.keys, st.amps, st.ctr,
+                       gates, kinds, gens, g0, M, eps, prune_first, ckpt, ckpt_n, seg, gate_n_in, max_keys, ncut);
   return hipGetLastError();
 }
 
-hipError_t launch_adjoint_replay_lds(const u64* keys, unsigned n, const GateDesc* gates, int M,
-                                     int seg, double eps, const double* const* ckpt,
-                                     const u64* ckpt_n, PairRec* logbuf, unsigned* logcnt,
+hipError_t launch_adjoint_replay_lds(const u64* keys, unsigned n, const GateDesc* gates, const int* kinds,
+                                     const GenGate* gens, int M, int seg, double eps, const double* const* ckpt,
+                                     const u64* ckpt_n, char* logbuf, size_t log_bytes, unsigned* logcnt,
                                      unsigned* flags, unsigned ncut, hipStream_t stream) {
   if (M <= 0) return hipSuccess;
   const int nseg = (M + seg - 1) / seg;
-  hipLaunchKernelGGL(k_adjoint_replay_lds<kLdsCap>, dim3(nseg), dim3(kChainThreads), 0, stream, keys,
-                     n, gates, M, seg, eps, ckpt, ckpt_n, logbuf, logcnt, flags, ncut);
+  if (kinds)
+    hipLaunchKernelGGL((k_adjoint_replay_lds<kLdsCap, true>), dim3(nseg), dim3(kChainThreads), 0, stream, keys, n, gates,
+                       kinds, gens, M, seg, eps, ckpt, ckpt_n, logbuf, log_bytes, logcnt, flags, ncut);
+  else
+    hipLaunchKernelGGL((k_adjoint_replay_lds<kLdsCap, false>), dim3(nseg), dim3(kChainThreads), 0, stream, keys, n,
+                       gates, kinds, gens, M, seg, eps, ckpt, ckpt_n, logbuf, log_bytes, logcnt, flags, ncut);
   return hipGetLastError();
 }
 
-hipError_t launch_adjoint_reverse_lds(unsigned n, const GateDesc* gates, int M,
-                                      const double* mu_init, const PairRec* logbuf,
-                                      const unsigned* logcnt, double* dE_part, double* dE,
-                                      hipStream_t stream) {
+hipError_t launch_adjoint_reverse_lds(unsigned n, const GateDesc* gates, const int* kinds, const GenGate* gens, int M,
+                                      const double* mu_init, const char* logbuf, size_t log_bytes,
+                                      const unsigned* logcnt, double* dE_part, double* dE, hipStream_t stream) {
   if (M <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_adjoint_reverse_lds<kLdsCap>, dim3(1), dim3(kChainThreads), 0, stream, n,
-                     gates, M, mu_init, logbuf, logcnt, dE_part, dE);
+  if (kinds)
+    hipLaunchKernelGGL((k_adjoint_reverse_lds<kLdsCap, true>), dim3(1), dim3(kChainThreads), 0, stream, n, gates, kinds,
+                       gens, M, mu_init, logbuf, log_bytes, logcnt, dE_part, dE);
+  else
+    hipLaunchKernelGGL((k_adjoint_reverse_lds<kLdsCap, false>), dim3(1), dim3(kChainThreads), 0, stream, n, gates, kinds,
+                       gens, M, mu_init, logbuf, log_bytes, logcnt, dE_part, dE);
   return hipGetLastError();
 }
 

@@ -551,6 +551,19 @@ int ncut_reserve(swcs_ctx* c, int states, u64 n) {
   return SWCS_OK;
 }
 
+// Generators and kinds of a chain with overlapping generators, in device memory.
+int upload_generators(swcs_ctx* c, const GenGate* gen, const int* kind, int64_t M, const GenGate** d_gens,
+                      const int** d_kinds) {
+  HIP_TRY(c, c->gen_tab.ensure((size_t)M * (sizeof(GenGate) + sizeof(int))), "alloc generator table");
+  int* kinds = (int*)((char*)c->gen_tab.p + (size_t)M * sizeof(GenGate));
+  HIP_TRY(c, hipMemcpyAsync(c->gen_tab.p, gen, (size_t)M * sizeof(GenGate), hipMemcpyHostToDevice, c->stream),
+          "copy generators");
+  HIP_TRY(c, hipMemcpyAsync(kinds, kind, (size_t)M * sizeof(int), hipMemcpyHostToDevice, c->stream), "copy generators");
+  *d_gens = c->gen_tab.as<GenGate>();
+  *d_kinds = kinds;
+  return SWCS_OK;
+}
+
 // Apply gates [0, M) of (ops, c, s) to the current state, with checkpoints
 // every `seg` gates when ckpt is requested.  A state that starts with at
 // most lds_chain_capacity() entries runs in one single-workgroup launch
@@ -591,13 +604,18 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     int r = upload_ckpt_table(c, nck);
     if (r) return r;
   }
-  // overlapping generators have no single-workgroup kernel: such chains run
-  // in HBM from the first gate.  The arrays have to hold what the kernel may
-  // write back: the LDS capacity, or a whole sector smaller than that (12
-  // spin-orbitals: 225 determinants, 30 gates 163 us in HBM, 32 here)
-  if (!has_star && n_start <= (u64)lds_chain_capacity() &&
+  const GenGate* gens = nullptr;
+  const int* kinds = nullptr;
+  if (has_star) {
+    int r = upload_generators(c, gen, kind, M, &gens, &kinds);
+    if (r) return r;
+  }
+  // The arrays have to hold what the single-workgroup kernel may write back: the
+  // LDS capacity, or a whole sector smaller than that (12 spin-orbitals: 225
+  // determinants, 30 gates 163 us in HBM, 32 here)
+  if (n_start <= (u64)lds_chain_capacity() &&
       c->st.cap >= std::min((u64)lds_chain_capacity(), c->sector) && M <= (int64_t)1 << 30) {
-    TIMED(c, SWCS_K_CHAIN_LDS, launch_chain_lds(c->st, c->gate_tab.as<GateDesc>(), 0, (int)M, eps, eps > 0.0 ? 1 : 0,
+    TIMED(c, SWCS_K_CHAIN_LDS, launch_chain_lds(c->st, c->gate_tab.as<GateDesc>(), kinds, gens, 0, (int)M, eps, eps > 0.0 ? 1 : 0,
                                 ckpt ? c->ckpt_ptrs.as<double*>() : nullptr, c->ckpt_n.as<u64>(),
                                 c->seg, c->gate_n_in.as<u64>(), c->sector, ncut, c->stream), "chain");
     HIP_TRY(c, launch_hash_clear(c->st.hash, c->st.hmask + 1, c->stream), "hash clear");
@@ -2267,7 +2285,13 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   const int grid = grid_blocks(c, n, 256);
   HIP_TRY(c, c->mu.ensure(n * 8), "alloc mu");
   HIP_TRY(c, c->gbuf.ensure((size_t)M * 8), "alloc dE");
-  const bool lds = !c->a_has_star && n <= (u64)lds_chain_capacity();
+  const bool lds = n <= (u64)lds_chain_capacity();
+  const GenGate* gens = nullptr;
+  const int* kinds = nullptr;
+  if (c->a_has_star) {
+    r = upload_generators(c, c->a_gen.data(), c->a_kind.data(), M, &gens, &kinds);
+    if (r) return r;
+  }
   // Pair logs: at most one record per stored entry per gate, for every gate
   // (single-workgroup path, all segments replayed at once) or for a group of
   // segments at a time (HBM path); with overlapping generators each gate's
@@ -2281,15 +2305,15 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
     int r2 = upload_ckpt_table(c, nseg);
     if (r2) return r2;
     HIP_TRY(c, c->seg_states.ensure((size_t)M * gate_log_bytes), "alloc pair logs");
-    PairRec* logs = c->seg_states.as<PairRec>();
-    HIP_TRY(c, c->ctr_r.ensure((size_t)M * sizeof(unsigned)), "alloc log counters");
+    char* logs = (char*)c->seg_states.p;
+    HIP_TRY(c, c->ctr_r.ensure((size_t)2 * M * sizeof(unsigned)), "alloc log counters");
     HIP_TRY(c, c->partial2.ensure(adjoint_lds_part_elems((int)M) * sizeof(double)), "alloc partials");
-    TIMED(c, SWCS_K_ADJOINT_REPLAY_LDS, launch_adjoint_replay_lds(c->st.keys, (unsigned)n, c->gate_tab.as<GateDesc>(), (int)M, seg,
+    TIMED(c, SWCS_K_ADJOINT_REPLAY_LDS, launch_adjoint_replay_lds(c->st.keys, (unsigned)n, c->gate_tab.as<GateDesc>(), kinds, gens, (int)M, seg,
                                           c->a_ncut ? 0.0 : c->a_eps, c->ckpt_ptrs.as<double*>(), c->ckpt_n.as<u64>(),
-                                          logs, c->ctr_r.as<unsigned>(), &c->st.ctr->flags, (unsigned)c->a_ncut,
+                                          logs, gate_log_bytes, c->ctr_r.as<unsigned>(), &c->st.ctr->flags, (unsigned)c->a_ncut,
                                           c->stream), "adjoint replay");
-    TIMED(c, SWCS_K_ADJOINT_LDS, launch_adjoint_reverse_lds((unsigned)n, c->gate_tab.as<GateDesc>(), (int)M, c->mu.as<double>(),
-                                  logs, c->ctr_r.as<unsigned>(), c->partial2.as<double>(), c->gbuf.as<double>(),
+    TIMED(c, SWCS_K_ADJOINT_LDS, launch_adjoint_reverse_lds((unsigned)n, c->gate_tab.as<GateDesc>(), kinds, gens, (int)M, c->mu.as<double>(),
+                                  logs, gate_log_bytes, c->ctr_r.as<unsigned>(), c->partial2.as<double>(), c->gbuf.as<double>(),
                                   c->stream), "adjoint");
   } else {
     // Per group of segments, the last first: restore the checkpoints into
@@ -2309,18 +2333,6 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
     if (c->a_ncut) {
       r = ncut_reserve(c, gsegs, n);
       if (r) return r;
-    }
-    const GenGate* gens = nullptr;
-    const int* kinds = nullptr;
-    if (c->a_has_star) {
-      HIP_TRY(c, c->gen_tab.ensure((size_t)M * (sizeof(GenGate) + sizeof(int))), "alloc generator table");
-      int* d_kinds = (int*)((char*)c->gen_tab.p + (size_t)M * sizeof(GenGate));
-      HIP_TRY(c, hipMemcpyAsync(c->gen_tab.p, c->a_gen.data(), (size_t)M * sizeof(GenGate), hipMemcpyHostToDevice,
-                                c->stream), "copy generators");
-      HIP_TRY(c, hipMemcpyAsync(d_kinds, c->a_kind.data(), (size_t)M * sizeof(int), hipMemcpyHostToDevice, c->stream),
-              "copy generators");
-      gens = c->gen_tab.as<GenGate>();
-      kinds = d_kinds;
     }
     double* W = c->work.as<double>();
     const double eps_r = c->a_ncut ? 0.0 : c->a_eps;

@@ -433,17 +433,16 @@ size_t ncut_select_bytes();
 hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Counters* ctr, unsigned gate, u64 cap, void* select,
                        unsigned* cand, u64 cand_stride, unsigned ncut, u64 n_most, int states, hipStream_t stream);
 int lds_chain_capacity();
-hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, int g0, int M, double eps,
-                            int prune_first, double* const* ckpt, u64* ckpt_n, int seg,
+hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, const int* kinds, const GenGate* gens,
+                            int g0, int M, double eps, int prune_first, double* const* ckpt, u64* ckpt_n, int seg,
                             u64* gate_n_in, u64 max_keys, unsigned ncut, hipStream_t stream);
-hipError_t launch_adjoint_replay_lds(const u64* keys, unsigned n, const GateDesc* gates, int M,
-                                     int seg, double eps, const double* const* ckpt,
-                                     const u64* ckpt_n, PairRec* logbuf, unsigned* logcnt,
+hipError_t launch_adjoint_replay_lds(const u64* keys, unsigned n, const GateDesc* gates, const int* kinds,
+                                     const GenGate* gens, int M, int seg, double eps, const double* const* ckpt,
+                                     const u64* ckpt_n, char* logbuf, size_t log_bytes, unsigned* logcnt,
                                      unsigned* flags, unsigned ncut, hipStream_t stream);
-hipError_t launch_adjoint_reverse_lds(unsigned n, const GateDesc* gates, int M,
-                                      const double* mu_init, const PairRec* logbuf,
-                                      const unsigned* logcnt, double* dE_part, double* dE,
-                                      hipStream_t stream);
+hipError_t launch_adjoint_reverse_lds(unsigned n, const GateDesc* gates, const int* kinds, const GenGate* gens, int M,
+                                      const double* mu_init, const char* logbuf, size_t log_bytes,
+                                      const unsigned* logcnt, double* dE_part, double* dE, hipStream_t stream);
 size_t adjoint_lds_part_elems(int M);
 hipError_t launch_gate_replay(const DeviceState& st, double* work, u64 n, const GateDesc* gates, double eps,
                              const ReplayGroup& G, int step, int segs, int grid, hipStream_t stream);

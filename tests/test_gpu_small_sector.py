@@ -44,3 +44,37 @@ def test_against_oracle(n, na, nb, M):
             dE_ref, _ = orc.param_gradients(pool, ops, theta, eps, ref, ncut=cut)
             assert abs(E - orc.energy(st)[0]) < 1e-10 and np.abs(dE - dE_ref).max() < 1e-10
     c.close()
+
+
+@pytest.mark.parametrize("n,ne,M", [(3, 2, 12), (4, 4, 40), (5, 6, 60), (7, 6, 90)])
+def test_generators_against_oracle(n, ne, M):
+    """Overlapping spin-complemented generators in the single-workgroup chain
+    and its adjoint: every generator of the smallest pools, then sectors of up
+    to 1,225 determinants filled through stars."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2411_07920_amd import spin, swcs
+    h, eri = make_integrals(n, n, 90 + n)
+    pool = enumerate_pool(n)
+    gp = spin.spin_complemented(pool)
+    ref = (1 << ne) - 1
+    rng = np.random.default_rng(91 + n)
+    over = np.flatnonzero(gp.overlap)
+    gens = rng.integers(0, len(gp), M)
+    gens[::2] = rng.choice(over, len(gens[::2]))
+    theta = rng.uniform(-0.8, 0.8, M)
+    rows = spin.gen_rows(gp, gens)
+    orc = oracle.Oracle(n, ne // 2, ne // 2, h, eri)
+    c = swcs.make_context(n, ne // 2, ne // 2, h, eri, pool, ref)
+    for eps, cut in ((0.0, 0), (2e-2, 0), (0.0, 5)):
+        print(f"[small] generators {n} {ne} eps {eps} cut {cut}", flush=True)
+        st = oracle.Oracle.apply_gen_ansatz(pool, rows, theta, eps, ref, cut)
+        assert c.apply_generators(rows, theta, eps, cut) == len(st)
+        k, a = c.get_state()
+        k_ref, a_ref = st.export()
+        assert np.array_equal(k, k_ref) and np.array_equal(a, a_ref)
+        dE, E = c.param_gradients(M)
+        dE_ref, E_ref = orc.gen_param_gradients(pool, rows, theta, eps, ref, cut)
+        assert abs(E - E_ref) < 1e-10 and np.abs(dE - dE_ref).max() < 1e-10
+    c.close()
