@@ -14,67 +14,164 @@ namespace swcs {
 constexpr int kChainThreads = 1024;
 constexpr int kGateChunk = 256;  // gate descriptors staged in LDS at a time
 
-// Deterministic block sum (fixed order over the 16 waves).
-__device__ inline double block_sum_1024(double v, double* wsum) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  const int lane = __lane_id(), wave = threadIdx.x >> 6;
-  if (lane == 0) wsum[wave] = v;
-  __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < kChainThreads / 64; ++w) r += wsum[w];
-  __syncthreads();
-  return r;  // valid in thread 0
-}
+constexpr int kLdsNcutBins = kChainThreads;  // one a thread
+constexpr unsigned kLdsNcutRank = 256;       // candidates ordered by counting
 
-// Keep only the ncut alive entries of amps[0, n) that come first in the N_CUT
-// order (gate_ops.h); the rest are marked dead.  Called by all threads of
-// the block; returns the number of entries dropped (valid in every thread).
+struct NcutState {
+  unsigned hist[kLdsNcutBins];
+  unsigned wsum[kChainThreads / 64];
+  u64 hi[kLdsNcutRank], lo[kLdsNcutRank];
+  unsigned pick, rest, held;  // digit found, rank within it, its count
+  unsigned ncand, drop, aux;
+};
+
+// Keep only the ncut alive entries of amps[0, n), n <= 4 kChainThreads, that
+// come first in the N_CUT order (gate_ops.h); the rest are marked dead.  Called by
+// all threads of the block; returns the number of entries dropped (valid in every
+// thread).  One histogram of ten bits of |c| -- six of the exponent (2^-63 to 2),
+// four of the mantissa, the end bins take the rest -- and the entries of the bin
+// that holds the cut are ordered by counting: six barriers.  Only where more than
+// 256 share the bin, a radix select over them, eight bits of |c| and then of the
+// key at a time.  (Sixteen such digits over the state, each picked by one thread,
+// took most of a gate's time: 20 generators of 9 orbitals at N_CUT = 408 with
+// gradients 1,937 us, now NEW.)
 __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, unsigned ncut,
                                     NcutState& st) {
-  const int tid = threadIdx.x;
+  constexpr int kPer = 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  st.hist[tid] = 0;
   if (tid == 0) {
-    st.phi = st.plo = st.mhi = st.mlo = 0;
-    st.k = ncut;
-    st.skip = 0;
-    st.pad[0] = 0;
+    st.pick = 0xffffffffu;
+    st.ncand = st.drop = 0;
   }
-  for (int d = 0; d < 16; ++d) {
-    if (tid < 256) st.hist[tid] = 0;
-    __syncthreads();
-    if (st.skip) break;
-    for (unsigned i = tid; i < n; i += kChainThreads) {
-      const double a = amps[i];
-      if (is_dead(a)) continue;
-      u64 hi, lo;
-      ncut_value(a, keys[i], &hi, &lo);
-      if (ncut_matches(st, hi, lo)) atomicAdd(&st.hist[ncut_digit(hi, lo, d)], 1u);
-    }
-    __syncthreads();
-    if (tid == 0) ncut_pick(st, d);
-    __syncthreads();
-  }
-  if (st.skip) return 0;
-  // st.phi / st.plo is now the ncut-th largest value; drop everything below.
-  unsigned dropped = 0;
-  for (unsigned i = tid; i < n; i += kChainThreads) {
-    const double a = amps[i];
+  __syncthreads();
+  u64 hi[kPer];
+  unsigned dig[kPer];  // 1 + digit, 0: no alive entry
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const unsigned i = (unsigned)tid + (unsigned)j * kChainThreads;
+    const double a = i < n ? amps[i] : dead_value();
+    dig[j] = 0;
     if (is_dead(a)) continue;
-    u64 hi, lo;
-    ncut_value(a, keys[i], &hi, &lo);
-    if (hi < st.phi || (hi == st.phi && lo < st.plo)) {
+    hi[j] = (u64)__double_as_longlong(fabs(a));
+    const unsigned b = (unsigned)(hi[j] >> 48), low = (1023u - 63u) << 4;
+    const unsigned d = b < low ? 0u : (b - low < kLdsNcutBins - 1u ? b - low : kLdsNcutBins - 1u);
+    dig[j] = 1u + d;
+    atomicAdd(&st.hist[d], 1u);
+  }
+  __syncthreads();
+  {
+    const unsigned bin = (unsigned)(kLdsNcutBins - 1 - tid), h = st.hist[bin];
+    unsigned inc = h;
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned v = __shfl_up(inc, off);
+      if (lane >= off) inc += v;
+    }
+    if (lane == 63) st.wsum[wave] = inc;
+    __syncthreads();
+    unsigned before = inc - h;
+    for (int w = 0; w < wave; ++w) before += st.wsum[w];
+    if (before < ncut && before + h >= ncut) {
+      st.pick = bin;
+      st.rest = ncut - before;
+      st.held = h;
+    }
+  }
+  __syncthreads();
+  if (st.pick == 0xffffffffu) return 0;  // fewer alive
+  const unsigned cut = 1u + st.pick, held = st.held;
+  unsigned k = st.rest, dropped = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const unsigned i = (unsigned)tid + (unsigned)j * kChainThreads;
+    if (dig[j] != 0 && dig[j] < cut) {
       amps[i] = dead_value();
       ++dropped;
+    } else if (dig[j] == cut && held <= kLdsNcutRank) {
+      const unsigned at = atomicAdd(&st.ncand, 1u);
+      st.hi[at] = hi[j];
+      st.lo[at] = ~keys[i];
     }
   }
-  if (tid == 0) st.pad[0] = 0;
+  if (k < held && held <= kLdsNcutRank) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (dig[j] != cut) continue;
+      const unsigned i = (unsigned)tid + (unsigned)j * kChainThreads;
+      const u64 lo = ~keys[i];
+      unsigned rank = 0;
+      for (unsigned q = 0; q < held; ++q)
+        rank += (hi[j] < st.hi[q] || (hi[j] == st.hi[q] && lo < st.lo[q])) ? 1u : 0u;
+      if (rank >= k) {
+        amps[i] = dead_value();
+        ++dropped;
+      }
+    }
+  } else if (k < held) {
+    u64 phi = 0, plo = 0, mhi = 0, mlo = 0;  // prefix found and its mask, in every thread
+    for (int d = 0; d < 16; ++d) {
+      const int sh = 56 - 8 * (d & 7);
+      __syncthreads();  // the digit before has been read
+      if (tid < 256) st.hist[tid] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        if (dig[j] != cut) continue;
+        const u64 lo = ~keys[(unsigned)tid + (unsigned)j * kChainThreads];
+        if ((hi[j] & mhi) == phi && (lo & mlo) == plo) atomicAdd(&st.hist[((d < 8 ? hi[j] : lo) >> sh) & 255u], 1u);
+      }
+      __syncthreads();
+      if (tid < 64) {  // four bins a lane, from the largest
+        unsigned h[4], sum = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          h[q] = st.hist[255 - (4 * lane + q)];
+          sum += h[q];
+        }
+        unsigned inc = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+          const unsigned v = __shfl_up(inc, off);
+          if (lane >= off) inc += v;
+        }
+        unsigned before = inc - sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (before < k && before + h[q] >= k) {
+            st.pick = (unsigned)(255 - (4 * lane + q));
+            st.rest = k - before;
+          }
+          before += h[q];
+        }
+      }
+      __syncthreads();
+      const u64 v = (u64)st.pick << sh, m = 255ULL << sh;
+      k = st.rest;
+      if (d < 8) {
+        phi |= v;
+        mhi |= m;
+      } else {
+        plo |= v;
+        mlo |= m;
+      }
+    }
+    // (phi, plo) is the last value that stays
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (dig[j] != cut) continue;
+      const unsigned i = (unsigned)tid + (unsigned)j * kChainThreads;
+      if (hi[j] < phi || (hi[j] == phi && ~keys[i] < plo)) {
+        amps[i] = dead_value();
+        ++dropped;
+      }
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) dropped += __shfl_xor(dropped, off);
+  if (lane == 0 && dropped) atomicAdd(&st.drop, dropped);
   __syncthreads();
-  if (dropped) atomicAdd(&st.pad[0], dropped);
-  __syncthreads();
-  const unsigned tot = st.pad[0];
-  __syncthreads();
-  return tot;
+  return st.drop;
 }
+static_assert(kLdsCap <= 4 * kChainThreads, "lds_ncut holds four entries a thread");
 
 // Forward chain of gates [g0, M) on the state held in keys / amps (HBM),
 // moved into LDS for the duration.  Checkpoints (amplitudes before gate g
@@ -189,7 +286,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
     if (g == 0 && prune_first) {
       // Entries of a caller-supplied starting state that the first gate did
       // not touch have not been tested against eps yet.
-      if (tid == 0) nst.pad[1] = 0;
+      if (tid == 0) nst.aux = 0;
       __syncthreads();
       unsigned dropped = 0;
       for (unsigned i = tid; i < n; i += kChainThreads) {
@@ -199,9 +296,9 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
           ++dropped;
         }
       }
-      if (dropped) atomicAdd(&nst.pad[1], dropped);
+      if (dropped) atomicAdd(&nst.aux, dropped);
       __syncthreads();
-      alive -= nst.pad[1];
+      alive -= nst.aux;
     }
   }
   __syncthreads();

@@ -68,6 +68,30 @@ def test_selection_against_sort(ctx, kind, n, cuts):
         assert got_n == len(order) and np.array_equal(k, keys[order]) and np.array_equal(a, amps[order])
 
 
+@pytest.mark.parametrize("kind", ["distinct", "equal", "steps", "zeros", "close"])
+@pytest.mark.parametrize("n", [1, 2, 257, 1500, 4096])
+def test_selection_in_lds(ctx, kind, n):
+    """The same of states that stay in LDS (up to 4,096 determinants): bins of
+    up to and more than 256 entries, cuts at both ends."""
+    rng = np.random.default_rng(n + 1)
+    # one spin-orbital left empty and one filled: the gate's operator acts on
+    # none of these determinants
+    keys, _ = draw_synthetic_state(N, NE // 2, NE // 2, 8 * n + 400, 7)
+    lo, hi = 1 << 1, 1 << 31
+    keys = keys[((keys & np.uint64(lo)) != 0) == ((keys & np.uint64(hi)) != 0)][:n]
+    assert len(keys) == n
+    amps = _amps(kind, n, rng)
+    op = int(np.flatnonzero((enumerate_pool(N) == np.array([31, 1, -1, -1])).all(1))[0])
+    for cut in sorted({1, max(1, n // 3), max(1, n - 1), n, n + 5}):
+        ctx.set_state(keys, amps)
+        print(f"[ncut] lds {kind} {n} cut {cut}", flush=True)
+        got_n = ctx.apply_gates([op], [0.3], 0.0, cut)
+        k, a = ctx.get_state()
+        order = np.lexsort((keys, -np.abs(amps)))[:cut]
+        order = order[np.argsort(keys[order])]
+        assert got_n == len(order) and np.array_equal(k, keys[order]) and np.array_equal(a, amps[order])
+
+
 def test_adjoint_replays_select_alike():
     """Gradients at N_CUT on a chain whose state leaves LDS: plain rows, and
     with angles of 0 so that exact zeros are at the cut."""
