@@ -34,7 +34,7 @@ struct NcutState {
 // 256 share the bin, a radix select over them, eight bits of |c| and then of the
 // key at a time.  (Sixteen such digits over the state, each picked by one thread,
 // took most of a gate's time: 20 generators of 9 orbitals at N_CUT = 408 with
-// gradients 1,937 us, now NEW.)
+// gradients 1,937 us, now 412.)
 __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, unsigned ncut,
                                     NcutState& st) {
   constexpr int kPer = 4;

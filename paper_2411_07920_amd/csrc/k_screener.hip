@@ -79,24 +79,35 @@ __device__ inline f32x4 mma4(float a, float b, f32x4 acc) {
 // "row = l / 16" pattern.
 constexpr int kStrideRowLane = kH + 4;
 constexpr int kStrideColLane = kH + 16;
-constexpr int kFwdRows = 64;       // rows per block iteration, 16 per wavefront
+constexpr int kMlpThreads = 512;   // two wavefronts per SIMD: one's LDS and memory latency under the other's MFMA
+constexpr int kMlpWaves = kMlpThreads / 64;
+constexpr int kFwdRows = 16 * kMlpWaves;  // rows per block iteration, 16 per wavefront
 constexpr int kBwdRows = 32;       // rows per block iteration of the backward pass
 constexpr int kMlpMaxBlocks = 256;
 
 // Forward pass: a1 = relu(x W1 + b1), a2 = relu(a1 W2 + b2), y = a2 W3 + b3;
 // act (optional) receives [a1 | a2] per row for the backward pass.  Each
 // wavefront computes 16 rows: 8 column tiles of 16, 4 k-steps for layer 1 and
-// 32 for layer 2; the weights are staged in LDS once per block.
-__global__ void __launch_bounds__(256)
+// 32 for layer 2; the weights are staged in LDS once per block (152 KB with the
+// wavefronts' own a1 tiles, so one block a CU), and nothing else is shared: the
+// wavefronts run on without block barriers, the next rows' inputs loaded ahead.
+// 288 MFMA of 32 cycles per 16 rows are 71 us for 301,600 rows and 15 for 65,536;
+// both calls took 228 us with four wavefronts and two barriers per 64 rows, 148
+// now.
+__global__ void __launch_bounds__(kMlpThreads)
 k_mlp_forward(const float* __restrict__ W, const float* __restrict__ x, long long B,
               float* __restrict__ y, float* __restrict__ act) {
-  __shared__ float w1s[kIn][kStrideColLane];
-  __shared__ float w2s[kH][kStrideColLane];
-  __shared__ float a1t[4][16][kStrideRowLane];
+  __shared__ __align__(16) float w1s[kIn][kStrideColLane];
+  __shared__ __align__(16) float w2s[kH][kStrideColLane];
+  __shared__ float a1t[kMlpWaves][16][kStrideRowLane];
   __shared__ float b1s[kH], b2s[kH], w3s[kH];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
-  for (int t = tid; t < kIn * kH; t += 256) w1s[t / kH][t % kH] = W[oW1 + t];
-  for (int t = tid; t < kH * kH; t += 256) w2s[t / kH][t % kH] = W[oW2 + t];
+  for (int t = tid; t < kIn * kH; t += kMlpThreads) w1s[t / kH][t % kH] = W[oW1 + t];
+#pragma unroll
+  for (int j = 0; j < kH * kH / kMlpThreads; ++j) {
+    const int t = tid + j * kMlpThreads;
+    w2s[t / kH][t % kH] = W[oW2 + t];
+  }
   if (tid < kH) {
     b1s[tid] = W[ob1 + tid];
     b2s[tid] = W[ob2 + tid];
@@ -105,20 +116,23 @@ k_mlp_forward(const float* __restrict__ W, const float* __restrict__ x, long lon
   const float b3 = W[ob3];
   __syncthreads();
   const long long groups = (B + kFwdRows - 1) / kFwdRows;
+  float xa[4];
+  auto load_x = [&](long long g) {
+    const long long ra = g * kFwdRows + 16 * wave + li;
+    for (int s = 0; s < 4; ++s) xa[s] = (ra < B) ? x[ra * kIn + 4 * s + lk] : 0.0f;
+  };
+  load_x(blockIdx.x);
   for (long long g = blockIdx.x; g < groups; g += gridDim.x) {
     const long long r0 = g * kFwdRows + 16 * wave;
-    {
-      const long long ra = r0 + li;
-      float xa[4];
-      for (int s = 0; s < 4; ++s) xa[s] = (ra < B) ? x[ra * kIn + 4 * s + lk] : 0.0f;
-      for (int t = 0; t < 8; ++t) {
-        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int s = 0; s < 4; ++s) acc = mma4(xa[s], w1s[4 * s + lk][16 * t + li], acc);
-        for (int r = 0; r < 4; ++r)
-          a1t[wave][4 * lk + r][16 * t + li] = fmaxf(acc[r] + b1s[16 * t + li], 0.0f);
-      }
+    wave_sync();  // this wavefront is done with its a1 tile
+    for (int t = 0; t < 8; ++t) {
+      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int s = 0; s < 4; ++s) acc = mma4(xa[s], w1s[4 * s + lk][16 * t + li], acc);
+      for (int r = 0; r < 4; ++r)
+        a1t[wave][4 * lk + r][16 * t + li] = fmaxf(acc[r] + b1s[16 * t + li], 0.0f);
     }
-    __syncthreads();
+    wave_sync();
+    load_x(g + gridDim.x);
     f32x4 acc[8];
     for (int t = 0; t < 8; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     for (int s = 0; s < kH / 4; ++s) {
@@ -153,123 +167,145 @@ k_mlp_forward(const float* __restrict__ W, const float* __restrict__ x, long lon
         }
       }
     }
-    __syncthreads();
   }
 }
 
 // Per-block partial gradient of sum_b dy_b y_b into partial[block][P].  Per
 // group of 32 rows:
 //   dz2 = dy W3^T [a2 > 0]               (elementwise, thread per column)
-//   dz1 = (dz2 W2^T) [a1 > 0]            (matrix cores, wavefront w: columns 32w..32w+31)
-//   dW2 += a1^T dz2, dW1 += x^T dz1      (matrix cores, wavefront w: rows 32w.. of dW2,
-//                                         columns 32w.. of dW1; accumulators in registers)
-// plus the column sums for b1, b2, W3 and b3.  Fixed summation order.
-__global__ void __launch_bounds__(256)
+//   dz1 = (dz2 W2^T) [a1 > 0]            (matrix cores, wavefront w: columns 16w..16w+15)
+//   dW2 += a1^T dz2, dW1 += x^T dz1      (matrix cores, wavefront w: rows 16w.. of dW2,
+//                                         columns 16w.. of dW1; accumulators in registers)
+// plus the column sums for b1, b2, W3 and b3.  Fixed summation order.  The next
+// group's activations are loaded while this one is worked on: 65,536 rows took
+// 116 us with four wavefronts and loads at the head of each group, 54 now (4.6
+// GFLOP: 30 us at the rate of a large FP32 product).
+__global__ void __launch_bounds__(kMlpThreads)
 k_mlp_backward_partial(const float* __restrict__ W, const float* __restrict__ x,
                        const float* __restrict__ act, const float* __restrict__ dy, long long B,
                        float* __restrict__ partial) {
+  constexpr int kParts = kMlpThreads / kH;          // threads of one column
+  constexpr int kRowsPer = kBwdRows / kParts;       // rows of a thread
+  static_assert(kMlpWaves * 16 == kH && kBwdRows * kIn == kMlpThreads, "one thread per input of a group");
   __shared__ float w2s[kH][kStrideRowLane];
   __shared__ float a1s[kBwdRows][kStrideColLane];
   __shared__ float dz2s[kBwdRows][kStrideRowLane];
   __shared__ float dz1s[kBwdRows][kStrideColLane];
   __shared__ float xs[kBwdRows][kIn];
-  __shared__ float dys[kBwdRows];
-  __shared__ float red[3][2][kH];
+  __shared__ float red[3][kParts][kH];
+  __shared__ float redb[kBwdRows];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
-  const int u = tid & (kH - 1), half = tid >> 7;
-  for (int t = tid; t < kH * kH; t += 256) w2s[t / kH][t % kH] = W[oW2 + t];
+  const int u = tid & (kH - 1), part = tid / kH;
+#pragma unroll
+  for (int j = 0; j < kH * kH / kMlpThreads; ++j) {
+    const int t = tid + j * kMlpThreads;
+    w2s[t / kH][t % kH] = W[oW2 + t];
+  }
   const float w3u = W[oW3 + u];
-  f32x4 acc2[2][8], acc1[2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 8; ++j) acc2[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  acc1[0] = acc1[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 acc2[8], acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int j = 0; j < 8; ++j) acc2[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   float gW3 = 0.0f, gb2 = 0.0f, gb1 = 0.0f, gb3 = 0.0f;
   const long long groups = (B + kBwdRows - 1) / kBwdRows;
-  for (long long g = blockIdx.x; g < groups; g += gridDim.x) {
+  float a1v[kRowsPer], a2v[kRowsPer], dv[kRowsPer], xv, db;
+  auto load = [&](long long g) {  // rows past the end count as zero
     const long long r0 = g * kBwdRows;
-    __syncthreads();  // previous group consumed; w2s staged
-    for (int t = tid; t < kBwdRows * kIn; t += 256) {
-      const long long r = r0 + t / kIn;
-      xs[t / kIn][t % kIn] = (r < B) ? x[r * kIn + t % kIn] : 0.0f;
-    }
-    if (tid < kBwdRows) dys[tid] = (r0 + tid < B) ? dy[r0 + tid] : 0.0f;
-    for (int r = half; r < kBwdRows; r += 2) {
-      const long long row = r0 + r;
+#pragma unroll
+    for (int j = 0; j < kRowsPer; ++j) {
+      const long long row = r0 + part + kParts * j;
       const bool ok = row < B;
-      const float a1v = ok ? act[row * (2 * kH) + u] : 0.0f;
-      const float a2v = ok ? act[row * (2 * kH) + kH + u] : 0.0f;
-      const float d = ok ? dy[row] : 0.0f;
-      const float z = (a2v > 0.0f) ? d * w3u : 0.0f;
-      a1s[r][u] = a1v;
-      dz2s[r][u] = z;
-      gW3 += a2v * d;
+      a1v[j] = ok ? act[row * (2 * kH) + u] : 0.0f;
+      a2v[j] = ok ? act[row * (2 * kH) + kH + u] : 0.0f;
+      dv[j] = ok ? dy[row] : 0.0f;
+    }
+    xv = r0 * kIn + tid < B * kIn ? x[r0 * kIn + tid] : 0.0f;
+    db = tid < kBwdRows && r0 + tid < B ? dy[r0 + tid] : 0.0f;
+  };
+  load(blockIdx.x);
+  for (long long g = blockIdx.x; g < groups; g += gridDim.x) {
+    __syncthreads();  // previous group consumed; w2s staged
+    xs[tid / kIn][tid % kIn] = xv;
+    gb3 += db;
+#pragma unroll
+    for (int j = 0; j < kRowsPer; ++j) {
+      const float z = (a2v[j] > 0.0f) ? dv[j] * w3u : 0.0f;
+      a1s[part + kParts * j][u] = a1v[j];
+      dz2s[part + kParts * j][u] = z;
+      gW3 += a2v[j] * dv[j];
       gb2 += z;
     }
     __syncthreads();
-    if (tid == 0)
-      for (int r = 0; r < kBwdRows; ++r) gb3 += dys[r];
+    load(g + gridDim.x);
     {
-      f32x4 acc[2][2];
-      for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      f32x4 acc[2];
+      acc[0] = acc[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       for (int s = 0; s < kH / 4; ++s) {
-        const float a0 = dz2s[li][4 * s + lk], a1 = dz2s[16 + li][4 * s + lk];
-        for (int t = 0; t < 2; ++t) {
-          const float b = w2s[32 * wave + 16 * t + li][4 * s + lk];
-          acc[0][t] = mma4(a0, b, acc[0][t]);
-          acc[1][t] = mma4(a1, b, acc[1][t]);
-        }
+        const float b = w2s[16 * wave + li][4 * s + lk];
+        acc[0] = mma4(dz2s[li][4 * s + lk], b, acc[0]);
+        acc[1] = mma4(dz2s[16 + li][4 * s + lk], b, acc[1]);
       }
       for (int i = 0; i < 2; ++i)
-        for (int t = 0; t < 2; ++t)
-          for (int r = 0; r < 4; ++r) {
-            const int row = 16 * i + 4 * lk + r, col = 32 * wave + 16 * t + li;
-            dz1s[row][col] = (a1s[row][col] > 0.0f) ? acc[i][t][r] : 0.0f;
-          }
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * i + 4 * lk + r, col = 16 * wave + li;
+          dz1s[row][col] = (a1s[row][col] > 0.0f) ? acc[i][r] : 0.0f;
+        }
     }
     __syncthreads();
-    for (int r = half; r < kBwdRows; r += 2) gb1 += dz1s[r][u];
+#pragma unroll
+    for (int j = 0; j < kRowsPer; ++j) gb1 += dz1s[part + kParts * j][u];
     for (int s = 0; s < kBwdRows / 4; ++s) {
       const int rr = 4 * s + lk;
-      const float a0 = a1s[rr][32 * wave + li], a1 = a1s[rr][32 * wave + 16 + li];
-      for (int j = 0; j < 8; ++j) {
-        const float b = dz2s[rr][16 * j + li];
-        acc2[0][j] = mma4(a0, b, acc2[0][j]);
-        acc2[1][j] = mma4(a1, b, acc2[1][j]);
-      }
-      const float ax = xs[rr][li];
-      for (int t = 0; t < 2; ++t) acc1[t] = mma4(ax, dz1s[rr][32 * wave + 16 * t + li], acc1[t]);
+      const float a0 = a1s[rr][16 * wave + li];
+      for (int j = 0; j < 8; ++j) acc2[j] = mma4(a0, dz2s[rr][16 * j + li], acc2[j]);
+      acc1 = mma4(xs[rr][li], dz1s[rr][16 * wave + li], acc1);
     }
   }
-  red[0][half][u] = gW3;
-  red[1][half][u] = gb2;
-  red[2][half][u] = gb1;
+  red[0][part][u] = gW3;
+  red[1][part][u] = gb2;
+  red[2][part][u] = gb1;
+  if (tid < kBwdRows) redb[tid] = gb3;
   __syncthreads();
   float* out = partial + (size_t)blockIdx.x * kMlpParams;
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 8; ++j)
-      for (int r = 0; r < 4; ++r)
-        out[oW2 + (32 * wave + 16 * i + 4 * lk + r) * kH + 16 * j + li] = acc2[i][j][r];
-  for (int t = 0; t < 2; ++t)
-    for (int r = 0; r < 4; ++r) out[oW1 + (4 * lk + r) * kH + 32 * wave + 16 * t + li] = acc1[t][r];
-  if (tid < kH) {
-    out[oW3 + tid] = red[0][0][tid] + red[0][1][tid];
-    out[ob2 + tid] = red[1][0][tid] + red[1][1][tid];
-    out[ob1 + tid] = red[2][0][tid] + red[2][1][tid];
+  for (int j = 0; j < 8; ++j)
+    for (int r = 0; r < 4; ++r) out[oW2 + (16 * wave + 4 * lk + r) * kH + 16 * j + li] = acc2[j][r];
+  for (int r = 0; r < 4; ++r) out[oW1 + (4 * lk + r) * kH + 16 * wave + li] = acc1[r];
+  if (tid < 3 * kH) {
+    const int which = tid / kH;
+    float v = 0.0f;
+    for (int j = 0; j < kParts; ++j) v += red[which][j][u];
+    out[(which == 0 ? oW3 : which == 1 ? ob2 : ob1) + u] = v;
   }
-  if (tid == 0) out[ob3] = gb3;
+  if (tid == 0) {
+    float v = 0.0f;
+    for (int r = 0; r < kBwdRows; ++r) v += redb[r];
+    out[ob3] = v;
+  }
 }
 
-__global__ void k_sum_partials_f32(const float* __restrict__ partial, long long rows, long long P,
-                                   float* __restrict__ out) {
-  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= P) return;
+// Column sums of partial[rows][P]: 64 columns a block, four groups of rows side
+// by side, eight loads in flight a thread, then the four sums (one thread per
+// column over all rows: 62 us for 256 rows of 18,945, now 6).
+constexpr int kSumParts = 4;
+__global__ void __launch_bounds__(64 * kSumParts)
+k_sum_partials_f32(const float* __restrict__ partial, long long rows, long long P, float* __restrict__ out) {
+  __shared__ float red[kSumParts][64];
+  const int c = (int)(threadIdx.x & 63u), part = (int)(threadIdx.x >> 6);
+  const long long p = (long long)blockIdx.x * 64 + c, q = p < P ? p : P - 1;
+  const long long per = (rows + kSumParts - 1) / kSumParts, b0 = part * per, b1 = b0 + per < rows ? b0 + per : rows;
   float s = 0.0f;
-  for (long long b = 0; b < rows; ++b) s += partial[b * P + p];
-  out[p] = s;
+  for (long long b = b0; b < b1; b += 8) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = partial[(b + j < b1 ? b + j : b1 - 1) * P + q];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s += b + j < b1 ? v[j] : 0.0f;
+  }
+  red[part][c] = s;
+  __syncthreads();
+  if (part == 0 && p < P) out[p] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
 }
 
 // Mean squared error and its gradient dy = 2 (y - t) / B: per-block partial
-// sums of squares, then one block adds them in block order.
+// sums of squares, then one wavefront adds them.
 __global__ void __launch_bounds__(256)
 k_mse_partial(const float* __restrict__ y, const float* __restrict__ t, long long B,
               float* __restrict__ dy, float* __restrict__ partial) {
@@ -292,10 +328,10 @@ k_mse_partial(const float* __restrict__ y, const float* __restrict__ t, long lon
 
 __global__ void k_mse_finish(const float* __restrict__ partial, int nblocks, long long B,
                              float* __restrict__ loss) {
-  if (threadIdx.x != 0) return;
-  float s = 0.0f;
-  for (int b = 0; b < nblocks; ++b) s += partial[b];
-  *loss = s / (float)B;
+  float s = 0.0f;  // one wavefront
+  for (int b = threadIdx.x; b < nblocks; b += 64) s += partial[b];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if (threadIdx.x == 0) *loss = s / (float)B;
 }
 
 // Screener targets t = log10(|g| + 1e-12) (float64 arithmetic, float32 result).
@@ -346,7 +382,7 @@ hipError_t launch_mlp_forward(const float* W, const float* x, long long B, float
   if (B == 0) return hipSuccess;
   const long long groups = (B + kFwdRows - 1) / kFwdRows;
   const unsigned grid = (unsigned)(groups < kMlpMaxBlocks ? groups : kMlpMaxBlocks);
-  hipLaunchKernelGGL(k_mlp_forward, dim3(grid), dim3(256), 0, stream, W, x, B, y, act);
+  hipLaunchKernelGGL(k_mlp_forward, dim3(grid), dim3(kMlpThreads), 0, stream, W, x, B, y, act);
   return hipGetLastError();
 }
 
@@ -361,9 +397,9 @@ hipError_t launch_mlp_backward(const float* W, const float* x, const float* act,
   const long long blocks = mlp_backward_partial_rows(B);
   if (blocks > partial_rows) return hipErrorInvalidValue;
   if (B > 0)
-    hipLaunchKernelGGL(k_mlp_backward_partial, dim3((unsigned)blocks), dim3(256), 0, stream, W, x,
+    hipLaunchKernelGGL(k_mlp_backward_partial, dim3((unsigned)blocks), dim3(kMlpThreads), 0, stream, W, x,
                        act, dy, B, partial);
-  hipLaunchKernelGGL(k_sum_partials_f32, dim3((unsigned)((kMlpParams + 255) / 256)), dim3(256), 0,
+  hipLaunchKernelGGL(k_sum_partials_f32, dim3((unsigned)((kMlpParams + 63) / 64)), dim3(64 * kSumParts), 0,
                      stream, partial, blocks, (long long)kMlpParams, dW);
   return hipGetLastError();
 }

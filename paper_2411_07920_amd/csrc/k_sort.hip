@@ -9,7 +9,7 @@
 #include <initializer_list>
 #include <type_traits>
 
-#include "swcs_internal.h"
+#include "select_ops.h"
 
 namespace swcs {
 
@@ -466,39 +466,6 @@ __device__ inline unsigned float_code(float f) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// Sort keys for the two selection passes; payloads are the operator indices.
-// The LSD sort is stable and inputs are in index order, so ties keep the
-// smaller index first.
-__global__ void k_select_keys_top(const float* __restrict__ score, long long K, u64* __restrict__ keys,
-                                  u64* __restrict__ idx) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < K) {
-    keys[i] = (u64)(~float_code(score[i]));  // larger score first
-    idx[i] = (u64)i;
-  }
-}
-
-__global__ void k_select_mark(const u64* __restrict__ idx_sorted, long long take,
-                              unsigned char* __restrict__ flags) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < take) flags[idx_sorted[i]] = 1;
-}
-
-__global__ void k_select_keys_rand(const uint32_t* __restrict__ rnd,
-                                   const unsigned char* __restrict__ flags, long long K,
-                                   u64* __restrict__ keys, u64* __restrict__ idx) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < K) {
-    keys[i] = ((u64)flags[i] << 32) | (u64)rnd[i];  // already chosen ones last
-    idx[i] = (u64)i;
-  }
-}
-
-__global__ void k_select_clear(unsigned char* flags, long long K) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < K) flags[i] = 0;
-}
-
 // Whole selection in one workgroup (pools up to kSelectBlockMax operators).
 // Each choice is a radix select of the kth largest 64-bit key, most
 // significant 8 bits first: top key = (score order, complemented index), so
@@ -506,7 +473,10 @@ __global__ void k_select_clear(unsigned char* flags, long long K) {
 // operators not already chosen and 0 for chosen ones, so the smallest
 // (rand, index) pairs rank first.  Keys are distinct, so after eight passes
 // the prefix is the kth largest key itself and "key >= it" selects exactly k.
-constexpr long long kSelectBlockMax = 1 << 17;
+// One workgroup takes 79 us for 16,000 operators, 205 for 50,000 and 484 for
+// 131,072; the launch per digit some 50, and 69 for 1,000,000.
+constexpr long long kSelectBlockMax = 1 << 14;
+static_assert(kSelectBlockMax <= 32 * 1024, "one mask word a thread");
 
 __device__ inline u64 select_key_top(const float* score, long long k) {
   return ((u64)float_code(score[k]) << 32) | (u64)(0xffffffffu - (unsigned)k);
@@ -673,27 +643,22 @@ k_select_block(const float* __restrict__ score, const uint32_t* __restrict__ rnd
     if (chosen_top(k)) return true;
     return n_rand > 0 && select_key_rand(rnd, k, false) >= t_rand && t_rand != 0ULL;
   };
-  // ascending output: contiguous index ranges per thread (at most 128
-  // entries, K <= kSelectBlockMax), flags evaluated kSelBatch at a time into
-  // two 64-bit masks, block scan of counts
+  // ascending output: contiguous index ranges per thread (at most 16 entries,
+  // K <= kSelectBlockMax), flags evaluated kSelBatch at a time into a mask, block
+  // scan of counts
   const long long per = (K + blockDim.x - 1) / blockDim.x;
   const long long lo = (long long)threadIdx.x * per;
   const long long hi = (lo + per < K) ? lo + per : K;
-  u64 f0 = 0, f1 = 0;
-  unsigned long long cnt = 0;
+  unsigned f = 0;
   for (long long j0 = 0; j0 < per; j0 += kSelBatch) {
     bool c[kSelBatch];
 #pragma unroll
     for (int j = 0; j < kSelBatch; ++j) c[j] = (lo + j0 + j < hi) && chosen(lo + j0 + j);
 #pragma unroll
-    for (int j = 0; j < kSelBatch; ++j) {
-      if (!c[j]) continue;
-      const long long jj = j0 + j;
-      if (jj < 64) f0 |= 1ULL << jj;
-      else f1 |= 1ULL << (jj - 64);
-      ++cnt;
-    }
+    for (int j = 0; j < kSelBatch; ++j)
+      if (c[j]) f |= 1u << (unsigned)(j0 + j);
   }
+  const unsigned long long cnt = (unsigned long long)__popc(f);
   part[threadIdx.x] = cnt;
   __syncthreads();
   for (int off = 1; off < 1024; off <<= 1) {
@@ -703,63 +668,166 @@ k_select_block(const float* __restrict__ score, const uint32_t* __restrict__ rnd
     __syncthreads();
   }
   long long pos = (long long)(part[threadIdx.x] - cnt);
-  while (f0) {
-    idx[pos++] = (int)(lo + __ffsll((long long)f0) - 1);
-    f0 &= f0 - 1;
-  }
-  while (f1) {
-    idx[pos++] = (int)(lo + 64 + __ffsll((long long)f1) - 1);
-    f1 &= f1 - 1;
+  while (f) {
+    idx[pos++] = (int)(lo + __ffs((int)f) - 1);
+    f &= f - 1;
   }
 }
 
-// Ascending list of flagged indices: per-tile counts, scan, ordered scatter.
-__global__ void __launch_bounds__(kSortThreads)
-k_flag_count(const unsigned char* __restrict__ flags, long long K, u64* __restrict__ counts) {
-  __shared__ unsigned c;
-  if (threadIdx.x == 0) c = 0;
-  __syncthreads();
-  const u64 base = (u64)blockIdx.x * kSortTile;
-  unsigned mine = 0;
-  for (int r = 0; r < kSortRows; ++r) {
-    const u64 i = base + (u64)r * kSortThreads + threadIdx.x;
-    if (i < (u64)K && flags[i]) ++mine;
+// The same choices of larger pools: one launch per digit of up to eleven bits
+// over the score or random code (three) and the index bits in use (ties), each
+// with a histogram of its own in which the next launch finds the digit
+// (select_ops.h); once a digit settles a choice, its later ones are not counted.
+// Then the ascending list: per-tile counts, scan, ordered scatter.  (Two sorts of
+// (key, index) pairs and their marks took 178 us for 301,600 operators; 54
+// now.)
+constexpr int kSelWideBits = 11;
+constexpr int kSelWideBins = 1 << kSelWideBits;
+constexpr int kSelWideThreads = 1024;
+constexpr int kSelWideSteps = 12;  // three digits of the code and up to three of the index, twice
+
+// Before a step counts: the smallest key that the top choice takes, the digits
+// found of the running choice's kth largest key, its rank among the keys that
+// have them, and whether it is settled (every key of the prefix and above taken).
+struct SelectStep {
+  u64 top, prefix;
+  unsigned need, done;
+};
+
+struct SelectWide {
+  SelectStep step[kSelWideSteps + 1];
+  unsigned hist[kSelWideSteps][kSelWideBins];
+};
+
+// Digits of a step: [shift, shift + bits) of the keys that agree with the prefix
+// from bit `match` on (64: all); ones: key bits above an index digit that all keys
+// have set.
+struct SelectDigit {
+  int shift, bits, match;
+  int begin;  // first digit of a choice: 1 top, 2 random with a top choice before it, 3 without
+  unsigned kth;
+  u64 ones;
+};
+
+// State before step p (the digit of step p - 1 found), in every thread.
+template <int THREADS>
+__device__ inline SelectStep select_resolve(const SelectWide* __restrict__ st, int p, const SelectDigit& prev, int begin,
+                                            unsigned kth, unsigned* s_wave, unsigned* s_pick) {
+  SelectStep s{0, 0, 0, 0};
+  if (p > 0) {
+    s = st->step[p - 1];
+    if (!s.done) {  // uniform
+      unsigned digit, rest, held;
+      (void)hist_find<kSelWideBins, THREADS>(st->hist[p - 1], s.need, s_wave, s_pick, &digit, &rest, &held);
+      s.prefix |= prev.ones | (u64)digit << prev.shift;
+      s.need = rest;
+      s.done = held == rest ? 1u : 0u;
+    }
   }
-  atomicAdd(&c, mine);
+  if (begin) {
+    if (begin == 2) s.top = s.prefix;
+    s.prefix = 0;
+    s.need = kth;
+    s.done = 0;
+  }
+  return s;
+}
+
+__global__ void __launch_bounds__(kSelWideThreads)
+k_select_digit(const float* __restrict__ score, const uint32_t* __restrict__ rnd, long long K, int p, SelectDigit prev,
+               SelectDigit cur, int rand_pass, bool have_top, SelectWide* __restrict__ st) {
+  __shared__ unsigned h[kSelWideBins];
+  __shared__ unsigned s_wave[kSelWideThreads / 64], s_pick[3];
+  const SelectStep s = select_resolve<kSelWideThreads>(st, p, prev, cur.begin, cur.kth, s_wave, s_pick);
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->step[p] = s;
+  if (s.done) return;
+  const unsigned mask = (1u << cur.bits) - 1u;
+  for (int t = threadIdx.x; t < kSelWideBins; t += kSelWideThreads) h[t] = 0;
+  __syncthreads();
+  const long long stride = (long long)gridDim.x * kSelWideThreads;
+  for (long long k0 = (long long)blockIdx.x * kSelWideThreads + threadIdx.x; k0 < K; k0 += 4 * stride) {
+    u64 key[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const long long k = k0 + j * stride < K ? k0 + j * stride : K - 1;  // clamped: the loads issue together
+      key[j] = rand_pass ? select_key_rand(rnd, k, have_top && select_key_top(score, k) >= s.top)
+                         : select_key_top(score, k);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (k0 + j * stride < K && (cur.match == 64 || (key[j] >> cur.match) == (s.prefix >> cur.match)))
+        atomicAdd(&h[(unsigned)(key[j] >> cur.shift) & mask], 1u);
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < kSelWideBins; t += kSelWideThreads)
+    if (h[t]) atomicAdd(&st->hist[p][t], h[t]);
+}
+
+// Thresholds of the choices that are made.
+struct SelectCut {
+  u64 top, ran;
+  bool has_top, has_ran;
+};
+__device__ inline bool select_chosen(const float* score, const uint32_t* rnd, long long k, const SelectCut& c) {
+  if (c.has_top && select_key_top(score, k) >= c.top) return true;
+  return c.has_ran && select_key_rand(rnd, k, false) >= c.ran;
+}
+
+__global__ void __launch_bounds__(kSortThreads)
+k_select_count(const float* __restrict__ score, const uint32_t* __restrict__ rnd, long long K, int steps, SelectDigit prev,
+               bool has_top, bool has_ran, SelectWide* __restrict__ st, u64* __restrict__ counts) {
+  __shared__ unsigned c;
+  __shared__ unsigned s_wave[kSortThreads / 64], s_pick[3];
+  if (threadIdx.x == 0) c = 0;
+  SelectStep s = select_resolve<kSortThreads>(st, steps, prev, 0, 0, s_wave, s_pick);
+  if (!has_ran) s.top = s.prefix;  // the last choice was the top one
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->step[kSelWideSteps] = s;
+  const SelectCut cut{s.top, s.prefix, has_top, has_ran};
+  __syncthreads();
+  const long long base = (long long)blockIdx.x * kSortTile;
+  unsigned mine = 0;
+#pragma unroll
+  for (int r = 0; r < kSortRows; ++r) {
+    const long long i = base + r * kSortThreads + threadIdx.x, k = i < K ? i : K - 1;
+    mine += (i < K && select_chosen(score, rnd, k, cut)) ? 1u : 0u;
+  }
+  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+  if (__lane_id() == 0) atomicAdd(&c, mine);
   __syncthreads();
   if (threadIdx.x == 0) counts[blockIdx.x] = c;
 }
 
+// A wavefront takes 1,024 consecutive operators, sixteen rows of 64.
 __global__ void __launch_bounds__(kSortThreads)
-k_flag_scatter(const unsigned char* __restrict__ flags, long long K, const u64* __restrict__ offsets,
-               int* __restrict__ idx) {
-  __shared__ unsigned wave_cnt[4];
-  __shared__ unsigned running;
-  const int lane = __lane_id();
-  const int wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) running = 0;
-  const u64 base = (u64)blockIdx.x * kSortTile;
-  const u64 off = offsets[blockIdx.x];
-  for (int r = 0; r < kSortRows; ++r) {
-    const u64 i = base + (u64)r * kSortThreads + threadIdx.x;
-    const bool f = i < (u64)K && flags[i];
-    const u64 m = __ballot(f);
-    if (lane == 0) wave_cnt[wave] = (unsigned)__popcll(m);
-    __syncthreads();
-    if (f) {
-      unsigned pos = running + (unsigned)__popcll(m & ((1ULL << lane) - 1ULL));
-      for (int w = 0; w < wave; ++w) pos += wave_cnt[w];
-      idx[off + pos] = (int)i;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) running += wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-    __syncthreads();
+k_select_scatter(const float* __restrict__ score, const uint32_t* __restrict__ rnd, long long K, bool has_top,
+                 bool has_ran, const SelectWide* __restrict__ st, const u64* __restrict__ offsets, int* __restrict__ idx) {
+  __shared__ unsigned wave_cnt[kSortThreads / 64];
+  constexpr int kRows = kSortTile / kSortThreads;
+  const SelectCut cut{st->step[kSelWideSteps].top, st->step[kSelWideSteps].prefix, has_top, has_ran};
+  const int lane = __lane_id(), wave = (int)(threadIdx.x >> 6);
+  const long long base = (long long)blockIdx.x * kSortTile + (long long)wave * (64 * kRows);
+  u64 m[kRows];
+  unsigned mine = 0;
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    const long long i = base + 64 * r + lane, k = i < K ? i : K - 1;
+    m[r] = __ballot(i < K && select_chosen(score, rnd, k, cut));
+    mine += (unsigned)__popcll(m[r]);
+  }
+  if (lane == 0) wave_cnt[wave] = mine;
+  __syncthreads();
+  u64 at = offsets[blockIdx.x];
+  for (int w = 0; w < wave; ++w) at += wave_cnt[w];
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    if ((m[r] >> lane) & 1ULL) idx[at + (u64)__popcll(m[r] & ((1ULL << lane) - 1ULL))] = (int)(base + 64 * r + lane);
+    at += (u64)__popcll(m[r]);
   }
 }
 
 u64 select_scratch_elems(long long K) {
-  // keys, idx, tmp keys, tmp idx, flags (bytes, rounded up), sort scratch
-  return 4 * (u64)K + ((u64)K + 7) / 8 + radix_sort_scratch_elems((u64)K) + 8;
+  const u64 tiles = ((u64)K + kSortTile - 1) / kSortTile;
+  return (sizeof(SelectWide) + 7) / 8 + tiles + scan_scratch_elems(tiles);
 }
 
 hipError_t launch_select(const float* score, const uint32_t* rnd, long long K, long long n_top,
@@ -771,34 +839,45 @@ hipError_t launch_select(const float* score, const uint32_t* rnd, long long K, l
     return hipGetLastError();
   }
   if (scratch_elems < select_scratch_elems(K)) return hipErrorInvalidValue;
-  u64* keys = scratch;
-  u64* ids = scratch + K;
-  u64* tk = scratch + 2 * K;
-  u64* ti = scratch + 3 * K;
-  unsigned char* flags = (unsigned char*)(scratch + 4 * K);
-  u64* hist = scratch + 4 * K + (K + 7) / 8;
-  const u64 hist_elems = radix_sort_scratch_elems((u64)K);
-  const unsigned g = (unsigned)((K + 255) / 256);
-  hipLaunchKernelGGL(k_select_clear, dim3(g), dim3(256), 0, stream, flags, K);
-  if (n_top > 0) {
-    hipLaunchKernelGGL(k_select_keys_top, dim3(g), dim3(256), 0, stream, score, K, keys, ids);
-    hipError_t e = radix_sort_pairs(keys, ids, tk, ti, (u64)K, 32, hist, hist_elems, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_select_mark, dim3((unsigned)((n_top + 255) / 256)), dim3(256), 0, stream,
-                       ids, n_top, flags);
+  SelectWide* st = (SelectWide*)scratch;
+  u64* counts = scratch + (sizeof(SelectWide) + 7) / 8;
+  hipError_t e = launch_fill_u32(scratch, 0u, sizeof(SelectWide) / 4, stream);
+  if (e != hipSuccess) return e;
+  const unsigned grid = (unsigned)std::min<long long>(256, (K + 4 * kSelWideThreads - 1) / (4 * kSelWideThreads));
+  int ib = 1;  // index bits in use
+  while (ib < 32 && ((u64)(K - 1) >> ib) != 0) ++ib;
+  const u64 ones = (0xffffffffULL >> ib) << ib;
+  SelectDigit prev{};
+  int p = 0;
+  for (int which = 0; which < 2; ++which) {
+    const long long kth = which ? n_rand : n_top;
+    if (kth == 0) continue;
+    int match = 64;
+    auto digit = [&](int shift, int bits, u64 fill) {
+      const int begin = match != 64 ? 0 : which == 0 ? 1 : n_top > 0 ? 2 : 3;
+      const SelectDigit cur{shift, bits, match, begin, (unsigned)kth, fill};
+      hipLaunchKernelGGL(k_select_digit, dim3(grid), dim3(kSelWideThreads), 0, stream, score, rnd, K, p, prev, cur, which,
+                         n_top > 0, st);
+      match = shift;
+      prev = cur;
+      ++p;
+    };
+    digit(53, 11, 0);
+    digit(42, 11, 0);
+    digit(32, 10, 0);
+    for (int left = ib; left > 0;) {
+      const int bits = std::min(kSelWideBits, left);
+      left -= bits;
+      digit(left, bits, ones);
+    }
   }
-  if (n_rand > 0) {
-    hipLaunchKernelGGL(k_select_keys_rand, dim3(g), dim3(256), 0, stream, rnd, flags, K, keys, ids);
-    hipError_t e = radix_sort_pairs(keys, ids, tk, ti, (u64)K, 33, hist, hist_elems, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_select_mark, dim3((unsigned)((n_rand + 255) / 256)), dim3(256), 0, stream,
-                       ids, n_rand, flags);
-  }
-  const int nblocks = (int)((K + kSortTile - 1) / kSortTile);
-  hipLaunchKernelGGL(k_flag_count, dim3(nblocks), dim3(kSortThreads), 0, stream, flags, K, hist);
-  scan_exclusive(hist, (u64)nblocks, hist + nblocks, stream);
-  hipLaunchKernelGGL(k_flag_scatter, dim3(nblocks), dim3(kSortThreads), 0, stream, flags, K, hist,
-                     idx);
+  if (p == 0) return hipGetLastError();  // nothing asked for
+  const int tiles = (int)((K + kSortTile - 1) / kSortTile);
+  hipLaunchKernelGGL(k_select_count, dim3(tiles), dim3(kSortThreads), 0, stream, score, rnd, K, p, prev, n_top > 0,
+                     n_rand > 0, st, counts);
+  scan_exclusive(counts, (u64)tiles, counts + tiles, stream);
+  hipLaunchKernelGGL(k_select_scatter, dim3(tiles), dim3(kSortThreads), 0, stream, score, rnd, K, n_top > 0,
+                     n_rand > 0, st, counts, idx);
   return hipGetLastError();
 }
 
