@@ -213,18 +213,26 @@ __device__ inline PairRec make_rec(const GateOut& o) {
 // unsigned; "keep the ncut largest" keeps the entries whose value is >= the
 // ncut-th largest.
 
+// Value of an entry in the N_CUT order.
+struct NcutValue {
+  u64 hi, lo;
+};
+
 // The selection of a state in HBM (k_state.hip): 12-bit digits of |c|.
-// Zeroed before its first use; every selection leaves hist, ncand and ticket
-// zero again.
+// Zeroed before its first use; every selection leaves hist[0] and ticket zero
+// again.
+constexpr unsigned kNcutRank = 1024;  // candidates ordered by counting in LDS
 struct NcutSelect {
-  unsigned skip;    // 1: keep everything (fewer than ncut alive, or chain stopped)
-  unsigned k;       // rank still to find inside the current prefix
-  unsigned prefix;  // digits of |c| found so far
-  unsigned ncand;   // entries with the whole prefix
-  unsigned ticket;  // blocks of the current launch that are done
-  unsigned narrow;  // 1: the first digit left so few that the second is not looked at
-  unsigned pad[2];
+  unsigned skip;    // 1: nothing to do (no more than ncut alive, or chain stopped)
+  unsigned none;    // 1: fewer than ncut were counted
+  unsigned first;   // first digit of the ncut-th largest |c|
+  unsigned k;       // its rank among the entries with this digit
+  unsigned narrow;  // 1: these are at most kNcutRank; their values are in cand
+  unsigned ncand;   // entries with the digits found
+  unsigned ticket;  // blocks of the marking pass that are done
+  unsigned pad;
   unsigned hist[2][4096];
+  NcutValue cand[kNcutRank];
 };
 
 // ---------------------------------------------------------------- stores

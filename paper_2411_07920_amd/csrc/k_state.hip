@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "gate_ops.h"
+#include "select_ops.h"
 
 namespace swcs {
 
@@ -326,19 +327,20 @@ __global__ void k_filter_set(const u64* __restrict__ keys, const double* __restr
 
 // N_CUT pruning of a state in HBM: a radix select of the ncut-th largest value
 // in the N_CUT order (gate_ops.h) in three launches -- two histograms of twelve
-// bits of |c| each, whose last block to finish picks the digit, and a marking
-// pass that drops everything below the digits found, collects the entries that
-// have them, and leaves their order (all of |c|, then the key) to its last
-// block.  Where the first digit leaves few entries the second histogram does
-// nothing (2.5 us instead of 7).  With 8-bit digits, a launch per histogram and
-// one per pick the selection was 34 launches a gate: 100 us at 10,000 to 40,000
-// entries (evaluation of 100 generators at N_CUT = 10,000: 50.1 -> 6.9 ms in all).
-// blockIdx.y is one of several states of the same keys.  With ctr the counts are
-// those after gate `gate` of a chain; otherwise n_host entries are scanned.
+// bits of |c| each, in which the next launch finds its digit (select_ops.h), and
+// a marking pass that drops everything below the digits found, collects the
+// entries that have them, and leaves their order (all of |c|, then the key) to
+// its last block.  Where the first digit leaves few entries these are listed
+// instead of counted, and every block of the marking pass finds the last one that
+// stays by ordering them.  With 8-bit digits, a launch per histogram and one per pick the
+// selection was 34 launches a gate: 100 us at 10,000 to 40,000 entries; the three
+// take 14 us (evaluation of 100 generators at N_CUT = 10,000: 50.1 -> 6.1 ms in
+// all).  blockIdx.y is one of several states of the same keys.  With ctr the
+// counts are those after gate `gate` of a chain; otherwise n_host entries are
+// scanned.
 constexpr int kNcutThreads = 1024;
 constexpr int kNcutBits = 12;
 constexpr int kNcutBins = 1 << kNcutBits;
-constexpr unsigned kNcutRank = 1024;  // candidates ordered by counting in LDS
 
 __device__ inline u64 ncut_bits(double a) { return (u64)__double_as_longlong(fabs(a)); }
 // First digit: six bits of the exponent (2^-63 to 2) and six of the mantissa, so
@@ -368,48 +370,6 @@ __device__ inline bool ncut_last_block(unsigned* ticket, bool* s_last) {
   return *s_last;
 }
 
-// Digit that holds rank k (from the largest) of a histogram in memory, which is
-// cleared; returns false when fewer than k values were counted.  Called by a
-// whole block; *digit, *rest (the rank within the digit) and *held (its count) in
-// every thread.
-__device__ inline bool ncut_find(unsigned* __restrict__ hist, unsigned k, unsigned* s_wave, unsigned* s_pick,
-                                 unsigned* digit, unsigned* rest, unsigned* held) {
-  constexpr int kPer = kNcutBins / kNcutThreads;
-  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
-  unsigned h[kPer], sum = 0;
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    unsigned* at = &hist[kNcutBins - 1 - (kPer * t + j)];
-    h[j] = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *at = 0;
-    sum += h[j];
-  }
-  unsigned inc = sum;
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned v = __shfl_up(inc, off);
-    if (lane >= off) inc += v;
-  }
-  if (lane == 63) s_wave[wave] = inc;
-  if (t == 0) s_pick[0] = 0xffffffffu;
-  __syncthreads();
-  unsigned before = inc - sum;
-  for (int w = 0; w < wave; ++w) before += s_wave[w];
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    if (before < k && before + h[j] >= k) {
-      s_pick[0] = (unsigned)(kNcutBins - 1 - (kPer * t + j));
-      s_pick[1] = k - before;
-      s_pick[2] = h[j];
-    }
-    before += h[j];
-  }
-  __syncthreads();
-  *digit = s_pick[0];
-  *rest = s_pick[1];
-  *held = s_pick[2];
-  return s_pick[0] != 0xffffffffu;
-}
-
 // Stored and alive entries after gate `gate` of a chain (ctr set), or n_host.
 __device__ inline u64 ncut_count(const Counters* ctr, unsigned gate, u64 cap, u64 n_host, u64* alive) {
   u64 n = n_host;
@@ -418,58 +378,77 @@ __device__ inline u64 ncut_count(const Counters* ctr, unsigned gate, u64 cap, u6
   return n;
 }
 
-template <int PASS>
+// First digit.  Also clears what the second launch adds to.
 __global__ void __launch_bounds__(kNcutThreads)
-k_ncut_hist(const double* __restrict__ amps, u64 stride_y, u64 n_host, const Counters* __restrict__ ctr,
-            unsigned gate, u64 cap, NcutSelect* __restrict__ sel_y, unsigned ncut) {
+k_ncut_first(const double* __restrict__ amps, u64 stride_y, u64 n_host, const Counters* __restrict__ ctr,
+             unsigned gate, u64 cap, NcutSelect* __restrict__ sel_y, unsigned ncut) {
   __shared__ unsigned h[kNcutBins];
-  __shared__ unsigned s_wave[kNcutThreads / 64], s_pick[3];
-  __shared__ bool s_last;
   NcutSelect* sel = sel_y + blockIdx.y;
   const double* __restrict__ a_y = amps + stride_y * blockIdx.y;
   u64 alive;
   const u64 n = ncut_count(ctr, gate, cap, n_host, &alive);
-  if (PASS == 0) {
-    // nothing to drop: every block sees the same counters (no block of this
-    // launch changes them)
-    if (ctr && ((__hip_atomic_load(&ctr->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFlagStopped) ||
-                alive <= ncut)) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) sel->skip = 1;
-      return;
+  // nothing to drop: the same in every block (no block changes the counters)
+  const bool skip = ctr && ((ctr->flags & kFlagStopped) || alive <= ncut);
+  if (blockIdx.x == 0 && threadIdx.x == 0) sel->skip = skip ? 1u : 0u;
+  if (skip) return;
+  for (int t = threadIdx.x; t < kNcutBins; t += kNcutThreads) h[t] = 0;
+  for (int t = blockIdx.x * kNcutThreads + threadIdx.x; t < kNcutBins; t += gridDim.x * kNcutThreads)
+    sel->hist[1][t] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) sel->ncand = 0;
+  __syncthreads();
+  for (u64 i = (u64)blockIdx.x * kNcutThreads + threadIdx.x; i < n; i += (u64)gridDim.x * kNcutThreads) {
+    const double a = a_y[i];
+    if (!is_dead(a)) atomicAdd(&h[ncut_first(ncut_bits(a))], 1u);
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < kNcutBins; t += kNcutThreads)
+    if (h[t]) atomicAdd(&sel->hist[0][t], h[t]);
+}
+
+// Finds the first digit; lists its entries where they are few, else counts their
+// second digit.
+__global__ void __launch_bounds__(kNcutThreads)
+k_ncut_second(const double* __restrict__ amps, u64 stride_y, const u64* __restrict__ keys, u64 n_host,
+              const Counters* __restrict__ ctr, unsigned gate, u64 cap, NcutSelect* __restrict__ sel_y, unsigned ncut) {
+  __shared__ unsigned h[kNcutBins];
+  __shared__ unsigned s_wave[kNcutThreads / 64], s_pick[3];
+  NcutSelect* sel = sel_y + blockIdx.y;
+  if (sel->skip) return;
+  unsigned first, rest, held;
+  const bool found = hist_find<kNcutBins, kNcutThreads>(sel->hist[0], ncut, s_wave, s_pick, &first, &rest, &held);
+  const bool narrow = found && held <= kNcutRank;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sel->none = found ? 0u : 1u;  // fewer than ncut alive: everything stays
+    sel->first = first;
+    sel->k = rest;
+    sel->narrow = narrow ? 1u : 0u;
+  }
+  if (!found) return;
+  u64 alive;
+  const u64 n = ncut_count(ctr, gate, cap, n_host, &alive);
+  const double* __restrict__ a_y = amps + stride_y * blockIdx.y;
+  if (narrow) {
+    for (u64 i = (u64)blockIdx.x * kNcutThreads + threadIdx.x; i < n; i += (u64)gridDim.x * kNcutThreads) {
+      const double a = a_y[i];
+      if (is_dead(a)) continue;
+      const u64 hi = ncut_bits(a);
+      if (ncut_first(hi) == first) sel->cand[atomicAdd(&sel->ncand, 1u)] = NcutValue{hi, ~keys[i]};
     }
-  } else if (sel->skip || sel->narrow) {
     return;
   }
   for (int t = threadIdx.x; t < kNcutBins; t += kNcutThreads) h[t] = 0;
-  const unsigned first = PASS ? sel->prefix : 0u;
   __syncthreads();
   for (u64 i = (u64)blockIdx.x * kNcutThreads + threadIdx.x; i < n; i += (u64)gridDim.x * kNcutThreads) {
     const double a = a_y[i];
     if (is_dead(a)) continue;
     const u64 hi = ncut_bits(a);
-    if (PASS == 0) atomicAdd(&h[ncut_first(hi)], 1u);
-    else if (ncut_first(hi) == first) atomicAdd(&h[ncut_second(hi, first)], 1u);
+    if (ncut_first(hi) == first) atomicAdd(&h[ncut_second(hi, first)], 1u);
   }
   __syncthreads();
-  unsigned* hist = sel->hist[PASS];
   for (int t = threadIdx.x; t < kNcutBins; t += kNcutThreads)
-    if (h[t]) atomicAdd(&hist[t], h[t]);
-  if (!ncut_last_block(&sel->ticket, &s_last)) return;
-  unsigned digit, rest, held;
-  const bool found = ncut_find(hist, PASS ? sel->k : ncut, s_wave, s_pick, &digit, &rest, &held);
-  if (threadIdx.x == 0) {
-    sel->ticket = 0;
-    sel->skip = found ? 0u : 1u;  // fewer than ncut alive (first pass): everything stays
-    sel->prefix = PASS ? first << kNcutBits | digit : digit;
-    sel->narrow = PASS == 0 && held <= kNcutRank ? 1u : 0u;
-    sel->k = rest;
-  }
+    if (h[t]) atomicAdd(&sel->hist[1][t], h[t]);
 }
 
-// Value of an entry in the N_CUT order.
-struct NcutValue {
-  u64 hi, lo;
-};
 __device__ inline bool ncut_less(const NcutValue& x, const NcutValue& y) {
   return x.hi < y.hi || (x.hi == y.hi && x.lo < y.lo);
 }
@@ -479,19 +458,43 @@ k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ key
             Counters* __restrict__ ctr, unsigned gate, u64 cap, NcutSelect* __restrict__ sel_y,
             unsigned* __restrict__ cand_y, u64 cand_stride) {
   __shared__ NcutValue s_val[kNcutRank];
-  __shared__ unsigned s_hist[256], s_pick[2];
+  __shared__ unsigned s_hist[256], s_pick[3], s_wave[kNcutThreads / 64];
   __shared__ bool s_last;
   __shared__ unsigned s_drop;
   NcutSelect* sel = sel_y + blockIdx.y;
   if (sel->skip) return;
+  // for the next selection
+  for (int t = blockIdx.x * kNcutThreads + threadIdx.x; t < kNcutBins; t += gridDim.x * kNcutThreads)
+    sel->hist[0][t] = 0;
+  if (sel->none) return;
   if (threadIdx.x == 0) s_drop = 0;
-  __syncthreads();
   double* __restrict__ a_y = amps + stride_y * blockIdx.y;
   unsigned* __restrict__ cand = cand_y + cand_stride * blockIdx.y;
   u64 alive_in;
   const u64 n = ncut_count(ctr, gate, cap, n_host, &alive_in);
-  const unsigned prefix = sel->prefix;
   const bool narrow = sel->narrow != 0;
+  unsigned prefix = sel->first, k = sel->k;  // digits found; candidates that stay
+  NcutValue cut{0, 0};  // few candidates: the k-th of them, found by every block
+  if (narrow) {
+    __shared__ NcutValue s_cut;
+    const unsigned nc = sel->ncand;
+    NcutValue v{0, 0};
+    if (threadIdx.x < nc) s_val[threadIdx.x] = v = sel->cand[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x < nc) {
+      unsigned rank = 0;
+      for (unsigned j = 0; j < nc; ++j) rank += ncut_less(v, s_val[j]) ? 1u : 0u;
+      if (rank == k - 1) s_cut = v;  // one thread: the values differ in their keys
+    }
+    __syncthreads();
+    cut = s_cut;
+  } else {
+    unsigned second, rest, held;
+    (void)hist_find<kNcutBins, kNcutThreads>(sel->hist[1], k, s_wave, s_pick, &second, &rest, &held);
+    prefix = prefix << kNcutBits | second;
+    k = rest;
+    __syncthreads();
+  }
   const int lane = (int)(threadIdx.x & 63u);
   unsigned dropped = 0;
   const u64 step = (u64)gridDim.x * kNcutThreads;
@@ -500,15 +503,22 @@ k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ key
     const double a = i < n ? a_y[i] : dead_value();
     const bool alive = !is_dead(a);
     unsigned p = 0;
+    bool below = false;
     if (alive) {
       const u64 hi = ncut_bits(a);
       p = ncut_first(hi);
-      if (!narrow) p = p << kNcutBits | ncut_second(hi, p);
+      if (narrow) {
+        below = p < prefix || (p == prefix && ncut_less(NcutValue{hi, ~keys[i]}, cut));
+      } else {
+        p = p << kNcutBits | ncut_second(hi, p);
+        below = p < prefix;
+      }
     }
-    if (alive && p < prefix) {
+    if (below) {
       a_y[i] = dead_value();
       ++dropped;
     }
+    if (narrow) continue;  // uniform
     const bool tie = alive && p == prefix;
     const u64 m = __ballot(tie);
     if (m) {
@@ -533,10 +543,10 @@ k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ key
     __syncthreads();
   };
   count_drops();
+  if (narrow) return;
   if (!ncut_last_block(&sel->ticket, &s_last)) return;
   dropped = 0;
   const unsigned nc = __hip_atomic_load(&sel->ncand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  unsigned k = sel->k;  // candidates that stay
   auto value = [&](unsigned c, u64* at) {
     const u64 i = __hip_atomic_load(&cand[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *at = i;
@@ -620,7 +630,6 @@ k_ncut_mark(double* __restrict__ amps, u64 stride_y, const u64* __restrict__ key
   count_drops();
   if (threadIdx.x == 0) {
     sel->ticket = 0;
-    sel->ncand = 0;
   }
 }
 
@@ -755,8 +764,8 @@ hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Co
   // the same few addresses
   const dim3 grid((unsigned)grid_for(n_most, kNcutThreads, 256), (unsigned)states);
   NcutSelect* sel = (NcutSelect*)select;
-  hipLaunchKernelGGL(k_ncut_hist<0>, grid, dim3(kNcutThreads), 0, stream, amps, stride, n_host, ctr, gate, cap, sel, ncut);
-  hipLaunchKernelGGL(k_ncut_hist<1>, grid, dim3(kNcutThreads), 0, stream, amps, stride, n_host, ctr, gate, cap, sel, ncut);
+  hipLaunchKernelGGL(k_ncut_first, grid, dim3(kNcutThreads), 0, stream, amps, stride, n_host, ctr, gate, cap, sel, ncut);
+  hipLaunchKernelGGL(k_ncut_second, grid, dim3(kNcutThreads), 0, stream, amps, stride, keys, n_host, ctr, gate, cap, sel, ncut);
   hipLaunchKernelGGL(k_ncut_mark, grid, dim3(kNcutThreads), 0, stream, amps, stride, keys, n_host, ctr, gate, cap, sel, cand,
                      cand_stride);
   return hipGetLastError();
