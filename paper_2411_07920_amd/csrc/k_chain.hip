@@ -44,7 +44,7 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
     st.pick = 0xffffffffu;
     st.ncand = st.drop = 0;
   }
-  __syncthreads();
+  lds_barrier();
   u64 hi[kPer];
   unsigned dig[kPer];  // 1 + digit, 0: no alive entry
 #pragma unroll
@@ -59,7 +59,7 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
     dig[j] = 1u + d;
     atomicAdd(&st.hist[d], 1u);
   }
-  __syncthreads();
+  lds_barrier();
   {
     const unsigned bin = (unsigned)(kLdsNcutBins - 1 - tid), h = st.hist[bin];
     unsigned inc = h;
@@ -68,7 +68,7 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
       if (lane >= off) inc += v;
     }
     if (lane == 63) st.wsum[wave] = inc;
-    __syncthreads();
+    lds_barrier();
     unsigned before = inc - h;
     for (int w = 0; w < wave; ++w) before += st.wsum[w];
     if (before < ncut && before + h >= ncut) {
@@ -77,7 +77,7 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
       st.held = h;
     }
   }
-  __syncthreads();
+  lds_barrier();
   if (st.pick == 0xffffffffu) return 0;  // fewer alive
   const unsigned cut = 1u + st.pick, held = st.held;
   unsigned k = st.rest, dropped = 0;
@@ -94,7 +94,7 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
     }
   }
   if (k < held && held <= kLdsNcutRank) {
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       if (dig[j] != cut) continue;
@@ -112,16 +112,16 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
     u64 phi = 0, plo = 0, mhi = 0, mlo = 0;  // prefix found and its mask, in every thread
     for (int d = 0; d < 16; ++d) {
       const int sh = 56 - 8 * (d & 7);
-      __syncthreads();  // the digit before has been read
+      lds_barrier();  // the digit before has been read
       if (tid < 256) st.hist[tid] = 0;
-      __syncthreads();
+      lds_barrier();
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         if (dig[j] != cut) continue;
         const u64 lo = ~keys[(unsigned)tid + (unsigned)j * kChainThreads];
         if ((hi[j] & mhi) == phi && (lo & mlo) == plo) atomicAdd(&st.hist[((d < 8 ? hi[j] : lo) >> sh) & 255u], 1u);
       }
-      __syncthreads();
+      lds_barrier();
       if (tid < 64) {  // four bins a lane, from the largest
         unsigned h[4], sum = 0;
 #pragma unroll
@@ -144,7 +144,7 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
           before += h[q];
         }
       }
-      __syncthreads();
+      lds_barrier();
       const u64 v = (u64)st.pick << sh, m = 255ULL << sh;
       k = st.rest;
       if (d < 8) {
@@ -168,7 +168,7 @@ __device__ inline unsigned lds_ncut(double* amps, const u64* keys, unsigned n, u
   }
   for (int off = 32; off > 0; off >>= 1) dropped += __shfl_xor(dropped, off);
   if (lane == 0 && dropped) atomicAdd(&st.drop, dropped);
-  __syncthreads();
+  lds_barrier();
   return st.drop;
 }
 static_assert(kLdsCap <= 4 * kChainThreads, "lds_ncut holds four entries a thread");
@@ -208,7 +208,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
     s_dal[tid] = 0;
   }
   for (int t = tid; t < 2 * CAP; t += kChainThreads) sslots[t] = 0;
-  __syncthreads();
+  lds_barrier();
   unsigned n = s_n0, alive = s_alive0;  // block-uniform, kept in every thread
   if (n > (unsigned)CAP) {
     if (tid == 0) {
@@ -221,7 +221,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
     skeys[i] = keys[i];
     samps[i] = amps[i];
   }
-  __syncthreads();
+  lds_barrier();
   LdsStore S{skeys, samps, sslots, 2u * CAP - 1u};
   for (unsigned i = tid; i < n; i += kChainThreads) S.insert(skeys[i], (int)i);
   int stop = -1;
@@ -233,14 +233,14 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
         sg[t] = gates[g + t];
         if (STAR) sk[t] = kinds[g + t];
       }
-      __syncthreads();
+      lds_barrier();
     }
     const bool star = STAR && sk[(g - g0) % kGateChunk] != 0;  // uniform
     if (ckpt && g % seg == 0) {
       double* dst = ckpt[g / seg];
       for (unsigned i = tid; i < n; i += kChainThreads) dst[i] = samps[i];
       if (tid == 0) ckpt_n[g / seg] = n;
-      __syncthreads();  // the copy precedes the gate's updates
+      lds_barrier();  // the copy precedes the gate's updates
     }
     const u64 room = max_keys > n ? max_keys - n : 0;
     const u64 most = star ? 2 * (u64)alive : (u64)alive;
@@ -254,7 +254,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
       const unsigned idx = n + atomicAdd(&s_app[slot], 1u);
       skeys[idx] = key;
       samps[idx] = val;
-      __threadfence_block();
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // before the slot that shows it
       S.insert(key, (int)idx);
     };
     if (star) {
@@ -274,7 +274,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
       }
     }
     if (dal) atomicAdd(&s_dal[slot], dal);
-    __syncthreads();
+    lds_barrier();
     if (tid == 0) {
       if (gate_n_in) gate_n_in[g] = alive;
       s_app[(g + 2) % 3] = 0;
@@ -287,7 +287,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
       // Entries of a caller-supplied starting state that the first gate did
       // not touch have not been tested against eps yet.
       if (tid == 0) nst.aux = 0;
-      __syncthreads();
+      lds_barrier();
       unsigned dropped = 0;
       for (unsigned i = tid; i < n; i += kChainThreads) {
         const double a = samps[i];
@@ -297,11 +297,11 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
         }
       }
       if (dropped) atomicAdd(&nst.aux, dropped);
-      __syncthreads();
+      lds_barrier();
       alive -= nst.aux;
     }
   }
-  __syncthreads();
+  lds_barrier();
   for (unsigned i = tid; i < n; i += kChainThreads) {
     keys[i] = skeys[i];
     amps[i] = samps[i];
@@ -354,20 +354,20 @@ k_adjoint_replay_lds(const u64* __restrict__ keys, unsigned n, const GateDesc* _
     sW[i] = (i < nj) ? src[i] : dead_value();
   }
   if (tid == 0) s_cnt = s_star = 0;
-  __syncthreads();
+  lds_barrier();
   LdsStore L{skeys, sW, sslots, 2u * CAP - 1u};
   for (unsigned i = tid; i < n; i += kChainThreads) L.insert(skeys[i], (int)i);
   const int lane = tid & 63;
   const u64 below = (1ULL << lane) - 1ULL;
   for (int g = g_lo; g < g_hi; ++g) {
     if ((g - g_lo) % kMaxSeg == 0) {
-      __syncthreads();
+      lds_barrier();
       for (int t = tid; t < kMaxSeg && g + t < g_hi; t += kChainThreads) {
         sg[t] = gates[g + t];
         if (STAR) sk[t] = kinds[g + t];
       }
     }
-    __syncthreads();
+    lds_barrier();
     const GateDesc gd = sg[(g - g_lo) % kMaxSeg];
     PairRec* lg = (PairRec*)(logbuf + (size_t)g * log_bytes);
     if (STAR && sk[(g - g_lo) % kMaxSeg]) {  // uniform
@@ -404,7 +404,7 @@ k_adjoint_replay_lds(const u64* __restrict__ keys, unsigned n, const GateDesc* _
         if (o.active) lg[b + (unsigned)__popcll(m & below)] = make_rec(o);
       }
     }
-    __syncthreads();
+    lds_barrier();
     if (tid == 0) {
       logcnt[g] = s_cnt;
       if (STAR) logcnt[M + g] = s_star;
@@ -426,46 +426,49 @@ k_adjoint_reverse_lds(unsigned n, const GateDesc* __restrict__ gates, const int*
   const int lane = tid & 63, wave = tid >> 6;
   for (unsigned i = tid; i < n; i += kChainThreads) smu[i] = mu_init[i];
   LdsMu mu{smu};
-  // The first record of this thread, the count and the descriptor of the
-  // next (earlier) gate are loaded while the current gate is processed.
+  // The first record of this thread, the count and the angle of the next four
+  // (earlier) gates are on their way while a gate is processed.
+  constexpr int kAhead = 4;
   auto log_of = [&](int g) { return (const PairRec*)(logbuf + (size_t)g * log_bytes); };
-  PairRec cur{};
-  unsigned c_cur = 0;
-  GateDesc gd_cur{};
-  if (M > 0) {
-    gd_cur = gates[M - 1];
-    c_cur = logcnt[M - 1];
-    if ((unsigned)tid < n) cur = log_of(M - 1)[tid];
-  }
-  __syncthreads();
-  for (int g = M - 1; g >= 0; --g) {
-    PairRec nxt{};
-    unsigned c_nxt = 0;
-    GateDesc gd_nxt{};
-    if (g > 0) {
-      gd_nxt = gates[g - 1];
-      c_nxt = logcnt[g - 1];
-      if ((unsigned)tid < n) nxt = log_of(g - 1)[tid];
+  PairRec rec[kAhead];
+  unsigned cnt[kAhead];
+  double cs[kAhead], sn[kAhead];
+  auto load = [&](int j, int g) {
+    cnt[j] = 0;
+    if (g < 0) return;
+    cs[j] = gates[g].c;
+    sn[j] = gates[g].s;
+    cnt[j] = logcnt[g];
+    if ((unsigned)tid < n) rec[j] = log_of(g)[tid];
+  };
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) load(j, M - 1 - j);
+  lds_barrier();
+  for (int g0 = M - 1; g0 >= 0; g0 -= kAhead) {
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int g = g0 - j;
+      if (g < 0) break;  // uniform
+      double acc = 0.0;
+      if ((unsigned)tid < cnt[j]) acc += adjoint_pair(rec[j], mu, cs[j], sn[j]);
+      const PairRec* lg = log_of(g);
+      for (unsigned r = tid + kChainThreads; r < cnt[j]; r += kChainThreads)
+        acc += adjoint_pair(lg[r], mu, cs[j], sn[j]);
+      bool any = (unsigned)(64 * wave) < cnt[j];
+      if (STAR && kinds[g]) {  // uniform
+        const GenGate gg = gens[g];
+        const unsigned ns = logcnt[M + g];
+        const StarRec* ls = (const StarRec*)(lg + n);
+        for (unsigned r = tid; r < ns; r += kChainThreads) acc += adjoint_star(ls[r], mu, gg);
+        any = true;
+      }
+      load(j, g - kAhead);
+      if (any) acc = wave_sum63(acc);
+      if (lane == 63) dE_part[(size_t)g * kWaves + wave] = acc;
+      lds_barrier();  // every mu update of gate g precedes gate g - 1
     }
-    double acc = 0.0;
-    if ((unsigned)tid < c_cur) acc += adjoint_pair(cur, mu, gd_cur.c, gd_cur.s);
-    const PairRec* lg = log_of(g);
-    for (unsigned r = tid + kChainThreads; r < c_cur; r += kChainThreads)
-      acc += adjoint_pair(lg[r], mu, gd_cur.c, gd_cur.s);
-    if (STAR && kinds[g]) {  // uniform
-      const GenGate gg = gens[g];
-      const unsigned ns = logcnt[M + g];
-      const StarRec* ls = (const StarRec*)(lg + n);
-      for (unsigned r = tid; r < ns; r += kChainThreads) acc += adjoint_star(ls[r], mu, gg);
-    }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (lane == 0) dE_part[(size_t)g * kWaves + wave] = acc;
-    __syncthreads();  // every mu update of gate g precedes gate g - 1
-    cur = nxt;
-    c_cur = c_nxt;
-    gd_cur = gd_nxt;
   }
-  __syncthreads();
+  __syncthreads();  // dE_part is read by other threads
   for (int g = tid; g < M; g += kChainThreads) {
     double t = 0.0;
     for (int w = 0; w < kWaves; ++w) t += dE_part[(size_t)g * kWaves + w];

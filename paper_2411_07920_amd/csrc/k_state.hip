@@ -248,51 +248,97 @@ k_adjoint_rec(const PairRec* __restrict__ log, const u64* __restrict__ log_count
 // Reverse steps of the gates [g_lo, g_hi) of a group, last first, by one
 // workgroup: for gates of a few thousand pairs a step is a handful of loads per
 // thread, and a barrier orders it before the next one where a launch per gate
-// takes 3.2 us (300 gates of 40,000 determinants: 0.95 -> 0.60 ms).  The first
-// record of each thread, the count and the angle of the next two gates are
-// loaded ahead.  Each wavefront's share of dE/dtheta_g goes to
-// partial[g pstride + wavefront].
+// takes 3.2 us (300 gates of 40,000 determinants: 0.95 -> 0.60 ms).  Storage
+// positions only grow along a chain, so before a checkpoint of at most kWalkLds
+// entries every other one is yet to come, and its mu is 0 (the step back over the
+// gate that appended it left that): from there on mu lies in LDS, the barrier
+// waits for LDS only, and the records loaded ahead stay in flight (these 300
+// gates 600 -> 456 us).  The first record of each thread, the count and the angle
+// of the next three gates are loaded ahead.  Each wavefront's share of dE/dtheta_g
+// goes to partial[g pstride + wavefront].
 constexpr int kWalkThreads = 1024;
-struct WalkAhead {
-  PairRec rec;
-  u64 cnt;
-  double c, sn;
+constexpr unsigned kWalkLds = 16384;  // 128 KB
+
+struct WalkMu {
+  double* p;
+  unsigned n;  // entries from here on have mu = 0 (pairs with an entry of a later gate)
+  __device__ double get(u64 i) const { return i < n ? p[i] : 0.0; }
+  __device__ void set(u64 i, double v) {
+    if (i < n) p[i] = v;
+  }
 };
-__device__ inline WalkAhead walk_load(const ReplayGroup& G, const GateDesc* __restrict__ gates, int g, int g_lo) {
-  WalkAhead w{};
-  if (g < g_lo) return w;
-  w.cnt = G.counts[g - G.g0];
-  w.c = gates[g].c;
-  w.sn = gates[g].s;
-  if ((u64)threadIdx.x < G.n) w.rec = G.pairs(g)[threadIdx.x];  // a log has room for n records
-  return w;
+
+template <bool LDS, class Mu>
+__device__ inline void walk_gates(const ReplayGroup& G, const GateDesc* __restrict__ gates,
+                                  const GenGate* __restrict__ gens, int g_lo, int g_hi, Mu& m,
+                                  double* __restrict__ partial, u64 pstride) {
+  constexpr int kAhead = 3;
+  const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
+  PairRec rec[kAhead];
+  unsigned cnt[kAhead];
+  double cs[kAhead], sn[kAhead];
+  auto load = [&](int j, int g) {
+    cnt[j] = 0;
+    if (g < g_lo) return;
+    cnt[j] = (unsigned)G.counts[g - G.g0];
+    cs[j] = gates[g].c;
+    sn[j] = gates[g].s;
+    if ((u64)threadIdx.x < G.n) rec[j] = G.pairs(g)[threadIdx.x];  // a log has room for n records
+  };
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) load(j, g_hi - 1 - j);
+  for (int g0 = g_hi - 1; g0 >= g_lo; g0 -= kAhead) {
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int g = g0 - j;
+      if (g < g_lo) break;  // uniform
+      double acc = 0.0;
+      if (threadIdx.x < cnt[j]) acc += adjoint_pair(rec[j], m, cs[j], sn[j]);
+      const PairRec* __restrict__ log = G.pairs(g);
+      for (unsigned r = threadIdx.x + kWalkThreads; r < cnt[j]; r += kWalkThreads)
+        acc += adjoint_pair(log[r], m, cs[j], sn[j]);
+      if (G.star(g)) {  // uniform
+        const GenGate gg = gens[g];
+        const StarRec* __restrict__ sl = G.stars(g);
+        const unsigned ns = (unsigned)G.star_counts[g - G.g0];
+        for (unsigned r = threadIdx.x; r < ns; r += kWalkThreads) acc += adjoint_star(sl[r], m, gg);
+      }
+      load(j, g - kAhead);
+      acc = wave_sum63(acc);
+      if (lane == 63) partial[(u64)g * pstride + wave] = acc;
+      // every mu update of gate g precedes gate g - 1
+      if (LDS) lds_barrier();
+      else __syncthreads();
+    }
+  }
 }
 
 __global__ void __launch_bounds__(kWalkThreads)
 k_adjoint_walk(ReplayGroup G, const GateDesc* __restrict__ gates, const GenGate* __restrict__ gens, int g_lo, int g_hi,
-               double* __restrict__ mu, double* __restrict__ partial, u64 pstride) {
-  GlobalMu m{mu};
-  const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
-  WalkAhead cur = walk_load(G, gates, g_hi - 1, g_lo), nx1 = walk_load(G, gates, g_hi - 2, g_lo);
-  for (int g = g_hi - 1; g >= g_lo; --g) {
-    const WalkAhead nx2 = walk_load(G, gates, g - 2, g_lo);
-    double acc = 0.0;
-    if ((u64)threadIdx.x < cur.cnt) acc += adjoint_pair(cur.rec, m, cur.c, cur.sn);
-    const PairRec* __restrict__ log = G.pairs(g);
-    for (u64 r = (u64)threadIdx.x + kWalkThreads; r < cur.cnt; r += kWalkThreads)
-      acc += adjoint_pair(log[r], m, cur.c, cur.sn);
-    if (G.star(g)) {  // uniform
-      const GenGate gg = gens[g];
-      const StarRec* __restrict__ sl = G.stars(g);
-      const u64 ns = G.star_counts[g - G.g0];
-      for (u64 r = threadIdx.x; r < ns; r += kWalkThreads) acc += adjoint_star(sl[r], m, gg);
-    }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (lane == 0) partial[(u64)g * pstride + wave] = acc;
-    __syncthreads();  // every mu update of gate g precedes gate g - 1
-    cur = nx1;
-    nx1 = nx2;
-  }
+               double* __restrict__ mu, double* __restrict__ partial, u64 pstride, const u64* __restrict__ ckpt_n,
+               int nseg) {
+  extern __shared__ double s_mu[];  // kWalkLds
+  __shared__ int s_seg;
+  // last checkpoint of at most kWalkLds entries (the first one has one)
+  if (threadIdx.x == 0) s_seg = 0;
+  __syncthreads();
+  for (int j = threadIdx.x; j < nseg; j += kWalkThreads)
+    if (ckpt_n[j] <= kWalkLds) atomicMax(&s_seg, j);
+  __syncthreads();
+  const bool all = G.n <= kWalkLds;
+  const long long cut = all ? (long long)g_hi : (long long)s_seg * G.seg;
+  const int g_cut = (int)(cut < g_lo ? g_lo : cut < g_hi ? cut : g_hi);
+  GlobalMu gm{mu};
+  walk_gates<false>(G, gates, gens, g_cut, g_hi, gm, partial, pstride);
+  if (g_cut == g_lo) return;
+  const unsigned n = (unsigned)(all ? G.n : ckpt_n[s_seg]);
+  __syncthreads();
+  for (unsigned i = threadIdx.x; i < n; i += kWalkThreads) s_mu[i] = mu[i];
+  __syncthreads();
+  WalkMu lm{s_mu, n};
+  walk_gates<true>(G, gates, gens, g_lo, g_cut, lm, partial, pstride);
+  __syncthreads();
+  for (unsigned i = threadIdx.x; i < n; i += kWalkThreads) mu[i] = s_mu[i];
 }
 
 __global__ void k_hash_clear(HashSlot* tab, u64 slots) {
@@ -809,11 +855,15 @@ hipError_t launch_gate_replay(const DeviceState& st, double* work, u64 n, const 
 }
 
 hipError_t launch_adjoint_walk(const ReplayGroup& G, const GateDesc* gates, const GenGate* gens, int g_lo, int g_hi,
-                               double* mu, double* partial, u64 pstride, hipStream_t stream) {
+                               double* mu, double* partial, u64 pstride, const u64* ckpt_n, int nseg,
+                               hipStream_t stream) {
   if (g_hi <= g_lo) return hipSuccess;
   if (pstride < (u64)kWalkThreads / 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_adjoint_walk, dim3(1), dim3(kWalkThreads), 0, stream, G, gates, gens, g_lo, g_hi, mu, partial,
-                     pstride);
+  const size_t bytes = kWalkLds * sizeof(double);
+  hipError_t e = hipFuncSetAttribute((const void*)k_adjoint_walk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_adjoint_walk, dim3(1), dim3(kWalkThreads), bytes, stream, G, gates, gens, g_lo, g_hi, mu, partial,
+                     pstride, ckpt_n, nseg);
   return hipGetLastError();
 }
 

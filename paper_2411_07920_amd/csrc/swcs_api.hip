@@ -2371,7 +2371,8 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
         while (first > g_lo && records(first - 1) <= kWalkMaxRecords) --first;
         if (first < g) {
           TIMED(c, SWCS_K_ADJOINT_REC, launch_adjoint_walk(G, gates, gens, first, g, c->mu.as<double>(),
-                                                           c->partial2.as<double>(), pstride, c->stream), "reverse");
+                                                           c->partial2.as<double>(), pstride, c->ckpt_n.as<u64>(), nseg,
+                                                           c->stream), "reverse");
           g = first;
           continue;
         }

@@ -224,6 +224,35 @@ __device__ inline bool gate_begin(Counters* ctr, unsigned gate, u64 cap, u64 max
 // many blocks tens.
 __device__ inline void device_atomics_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Sum over the wavefront, in lane 63: row steps and row broadcasts in the vector
+// units (six shuffles through LDS take some 700 cycles, and are most of a step
+// where one workgroup walks a chain back).  Every lane of the wavefront calls it.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ inline double wave_sum63(double v) {
+  v = dpp_add<0xb1, 0xf>(v);   // quad_perm 1, 0, 3, 2
+  v = dpp_add<0x4e, 0xf>(v);   // quad_perm 2, 3, 0, 1
+  v = dpp_add<0x141, 0xf>(v);  // row_half_mirror
+  v = dpp_add<0x140, 0xf>(v);  // row_mirror: every lane of a row of 16 has its sum
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
+// Barrier of a block that shares nothing but LDS between its threads: waits for
+// LDS operations only, so loads made ahead and stores that no thread of the block
+// reads stay in flight across it (__syncthreads waits for them: a microsecond
+// where they go to memory).
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Orders a wavefront's own LDS accesses (its LDS operations execute in order;
 // this keeps the compiler from moving or reusing them across the point).
 __device__ inline void wave_sync() {
@@ -447,7 +476,8 @@ size_t adjoint_lds_part_elems(int M);
 hipError_t launch_gate_replay(const DeviceState& st, double* work, u64 n, const GateDesc* gates, double eps,
                              const ReplayGroup& G, int step, int segs, int grid, hipStream_t stream);
 hipError_t launch_adjoint_walk(const ReplayGroup& G, const GateDesc* gates, const GenGate* gens, int g_lo, int g_hi,
-                               double* mu, double* partial, u64 pstride, hipStream_t stream);
+                               double* mu, double* partial, u64 pstride, const u64* ckpt_n, int nseg,
+                               hipStream_t stream);
 hipError_t launch_adjoint_rec(const PairRec* log, const u64* log_count, double* mu, double c,
                               double sn, double* partial, int grid, hipStream_t stream);
 hipError_t launch_ckpt_save(const DeviceState& st, unsigned gate, double* dst, u64* dst_n, int grid,
