@@ -1610,27 +1610,29 @@ constexpr double kRdmPairLimit = 1.0;
 constexpr double kRdmRowPairs = 1.0;
 
 // Whether that form is taken where the pairs outnumber the join's records: its
-// measured share per subset record and per pair (both on the safe side), 1.1 ms
+// measured share per subset record and per pair (both on the safe side), 0.85 ms
 // for what does not depend on the state, and 65 ps per join record.  Measured
 // against the join: 100,000 of (12 orbitals, 5 + 6 electrons) 2.6 to 13.6 ms at
-// 1.3 pairs per join record; the full (12, 6 + 6) sector 69 to 118 at 10.4; the
+// 1.3 pairs per join record; the full (12, 6 + 6) sector 69 to 118 at 10.6; the
 // full (10, 5 + 5) sector, 63,504 determinants, is even (4.5).
 static bool rdm_rows_pay(double records, double pairs, double join_records) {
-  return 1.1e-3 + 8e-11 * records + 5e-12 * pairs < 6.5e-11 * join_records;
+  return 0.85e-3 + 8e-11 * records + 5.1e-12 * pairs < 6.5e-11 * join_records;
 }
 
 // Seconds of the density-matrix pass at n orbitals and `records` subset records,
 // `each` seconds a record: fifteen small launches and the sample, the
 // contraction's n^7, and emit, sort and pairs.
 static double rdm_seconds(int n, double records, double each) {
-  return 0.9e-3 + 4e-13 * std::pow((double)n, 7.0) + each * records;
+  return 0.6e-3 + 4e-13 * std::pow((double)n, 7.0) + each * records;
 }
 // Whether AUTO takes it for a whole pool: 55 ps a subset record (the pairs of a
-// crowded state are judged by the sample) against 60 ps a join record.  26
-// orbitals: 4.0 ms against 5.5 at 8.9e7 join records, 3.7 against 2.8 at 4.6e7.
-// Below 3e7 records (2 ms) the launches leave it no lead at any n.
+// crowded state are judged by the sample) against 65 ps a join record.  Matrix
+// against join: 14 orbitals, 4 + 4 electrons 0.5 to 0.9 ms at 1.3e7 join records;
+// 18 orbitals, 5 + 4 electrons 0.6 to 0.8 against 1.3 to 1.4 at 1.8e7; 22
+// orbitals, 6 + 5 electrons 1.6 to 1.9 against 2.0 to 2.2 at 3.2e7; 26 orbitals,
+// 8 + 8 electrons 4.0 against 5.5 at 8.9e7, 3.7 against 2.8 at 4.6e7.
 static bool rdm_pays(int n, double records, double join_records) {
-  return join_records >= 3.0e7 && rdm_seconds(n, records, 5.5e-11) < 6e-11 * join_records;
+  return join_records >= 9.0e6 && rdm_seconds(n, records, 5.5e-11) < 6.5e-11 * join_records;
 }
 // Whether it is taken for a share of the pool.  The screened pass takes 15 to 25
 // ps a join record and 350 to 550 more times the share of the operators (1 to
@@ -1638,7 +1640,7 @@ static bool rdm_pays(int n, double records, double join_records) {
 // the pairs of a clustered state.  26 orbitals, 8 + 8 electrons, 4,392
 // determinants: 4.9 against 8.6 ms at 10 %, 4.8 against 3.2 at 3 %.
 static bool rdm_pays_screened(int n, double records, double join_records, double share) {
-  return rdm_seconds(n, records, 1.5e-10) < (1.5e-11 + 3.5e-10 * share) * join_records;
+  return rdm_seconds(n, records, 1.5e-10) + 0.3e-3 < (1.5e-11 + 3.5e-10 * share) * join_records;
 }
 
 // Pool gradients of the `count` operators d_subset (NULL: the whole pool) into
