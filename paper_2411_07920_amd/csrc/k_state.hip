@@ -916,6 +916,11 @@ __global__ void k_fill_u32(unsigned* __restrict__ p, unsigned v, u64 words) {
   for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += stride) p[i] = v;
 }
 
+__global__ void k_pack_result(double* __restrict__ to, const double* __restrict__ sums, const Counters* __restrict__ ctr) {
+  if (threadIdx.x < 2) to[threadIdx.x] = sums[threadIdx.x];
+  if (threadIdx.x == 2) to[2] = (double)ctr->flags;
+}
+
 __global__ void k_store_counters(Counters* __restrict__ ctr, Counters v) { *ctr = v; }
 
 __global__ void k_clear_flag(Counters* __restrict__ ctr, unsigned bit) {
@@ -926,6 +931,11 @@ hipError_t launch_fill_u32(void* p, unsigned v, u64 words, hipStream_t stream) {
   if (words == 0) return hipSuccess;
   const u64 blocks = std::min<u64>((words + 255) / 256, 4096);
   hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, stream, (unsigned*)p, v, words);
+  return hipGetLastError();
+}
+
+hipError_t launch_pack_result(double* to, const double* sums, const Counters* ctr, hipStream_t stream) {
+  hipLaunchKernelGGL(k_pack_result, dim3(1), dim3(64), 0, stream, to, sums, ctr);
   return hipGetLastError();
 }
 

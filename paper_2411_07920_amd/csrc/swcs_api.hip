@@ -2286,7 +2286,7 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   const int nseg = (int)((M + seg - 1) / seg);
   const int grid = grid_blocks(c, n, 256);
   HIP_TRY(c, c->mu.ensure(n * 8), "alloc mu");
-  HIP_TRY(c, c->gbuf.ensure((size_t)M * 8), "alloc dE");
+  HIP_TRY(c, c->gbuf.ensure((size_t)(M + 3) * 8), "alloc dE");  // and the energy's sums and the flags
   const bool lds = n <= (u64)lds_chain_capacity();
   const GenGate* gens = nullptr;
   const int* kinds = nullptr;
@@ -2390,13 +2390,15 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
     HIP_TRY(c, launch_reduce_partials(c->partial2.as<double>(), (int)pstride, (int)pstride, (int)M, c->gbuf.as<double>(),
                                       c->stream), "reduce");
   }
-  std::vector<double> d_unit((size_t)M);
-  HIP_TRY(c, hipMemcpyAsync(d_unit.data(), c->gbuf.p, (size_t)M * 8, hipMemcpyDeviceToHost, c->stream), "copy dE");
-  double nn_host[2];
-  HIP_TRY(c, hipMemcpyAsync(nn_host, nn, 16, hipMemcpyDeviceToHost, c->stream), "copy energy");
-  Counters hchk = read_counters(c, &e);  // synchronizes
-  if (e != hipSuccess) return hip_fail(c, e, "sync");
-  if (hchk.flags & kFlagOverflow) {
+  // one copy brings derivatives, energy and flags
+  std::vector<double> d_unit((size_t)M + 3);
+  HIP_TRY(c, launch_pack_result(c->gbuf.as<double>() + M, nn, c->st.ctr, c->stream), "pack results");
+  HIP_TRY(c, hipMemcpyAsync(d_unit.data(), c->gbuf.p, (size_t)(M + 3) * 8, hipMemcpyDeviceToHost, c->stream), "copy dE");
+  HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+  const double nn_host[2] = {d_unit[(size_t)M], d_unit[(size_t)M + 1]};
+  if ((unsigned)d_unit[(size_t)M + 2] & kFlagOverflow) {
+    Counters hchk = read_counters(c, &e);
+    if (e != hipSuccess) return hip_fail(c, e, "sync");
     hchk.flags &= ~kFlagOverflow;
     HIP_TRY(c, launch_store_counters(c->st.ctr, hchk, c->stream), "counters");
     c->hc = hchk;

@@ -431,6 +431,8 @@ struct StarRec;
 hipError_t launch_gen_gate(const DeviceState& st, const GenGate& g, double eps, u64* gate_n_in,
                            unsigned gate_index, u64 max_keys, int grid, hipStream_t stream,
                            u64* gate_n_act = nullptr);
+// to[0..2] = the energy's two sums and the error flags.
+hipError_t launch_pack_result(double* to, const double* sums, const Counters* ctr, hipStream_t stream);
 // The counts before gate g of a chain, from the state's; the state's counts after
 // the chain's gates up to M, or up to the one that stopped it.
 hipError_t launch_live_begin(const DeviceState& st, unsigned g, hipStream_t stream);
