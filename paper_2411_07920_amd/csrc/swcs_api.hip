@@ -479,8 +479,16 @@ bool compact_due(const Counters& h) {
   return dead >= kCompactMin && dead > h.alive;
 }
 
-// Reset the state to the single reference determinant.
-int state_reset_to_reference(swcs_ctx* c) {
+// Whether a chain of M gates starts in the single-workgroup kernel.  The arrays
+// have to hold what it may write back: the LDS capacity, or a whole sector smaller
+// than that (12 spin-orbitals: 225 determinants, 30 gates 163 us in HBM, 32 here).
+bool chain_in_lds(swcs_ctx* c, u64 n_start, int64_t M) {
+  return M > 0 && n_start <= (u64)lds_chain_capacity() &&
+         c->st.cap >= std::min((u64)lds_chain_capacity(), c->sector) && M <= (int64_t)1 << 30;
+}
+
+// Reset the state to the single reference determinant, for a chain of M gates.
+int state_reset_to_reference(swcs_ctx* c, int64_t M) {
   u64 cap;
   if (!c->allow_regrow) {
     cap = fixed_capacity(c);
@@ -493,11 +501,13 @@ int state_reset_to_reference(swcs_ctx* c) {
   if (!c->keys.p || c->st.cap != cap) {
     int r = state_reserve(c, cap, 0);
     if (r) return r;
-  } else {
+  } else if (!chain_in_lds(c, 1, M)) {
     HIP_TRY(c, launch_hash_clear(c->st.hash, c->st.hmask + 1, c->stream), "hash clear");
   }
   HIP_TRY(c, launch_reset_reference(c->st, c->ref, c->stream), "reset");
-  HIP_TRY(c, launch_hash_build(c->st, 1, c->stream), "hash build");
+  // the single-workgroup kernel has an index of its own, and this one is built
+  // from its result
+  if (!chain_in_lds(c, 1, M)) HIP_TRY(c, launch_hash_build(c->st, 1, c->stream), "hash build");
   std::memset(&c->hc, 0, sizeof(c->hc));
   c->hc.n = 1;
   c->hc.alive = 1;
@@ -610,11 +620,7 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     int r = upload_generators(c, gen, kind, M, &gens, &kinds);
     if (r) return r;
   }
-  // The arrays have to hold what the single-workgroup kernel may write back: the
-  // LDS capacity, or a whole sector smaller than that (12 spin-orbitals: 225
-  // determinants, 30 gates 163 us in HBM, 32 here)
-  if (n_start <= (u64)lds_chain_capacity() &&
-      c->st.cap >= std::min((u64)lds_chain_capacity(), c->sector) && M <= (int64_t)1 << 30) {
+  if (chain_in_lds(c, n_start, M)) {
     TIMED(c, SWCS_K_CHAIN_LDS, launch_chain_lds(c->st, c->gate_tab.as<GateDesc>(), kinds, gens, 0, (int)M, eps, eps > 0.0 ? 1 : 0,
                                 ckpt ? c->ckpt_ptrs.as<double*>() : nullptr, c->ckpt_n.as<u64>(),
                                 c->seg, c->gate_n_in.as<u64>(), c->sector, ncut, c->stream), "chain");
@@ -1054,8 +1060,6 @@ static int apply_common(swcs_ctx* c, ChainSpec& sp, double eps, int64_t ncut, in
   HIP_TRY(c, launch_fill_u32(c->gate_n_act.p, 0u, (u64)std::max<int64_t>(1, M) * 2, c->stream), "zero stats");
   c->ansatz_valid = false;
   if (from_reference) {
-    int r = state_reset_to_reference(c);
-    if (r) return r;
     c->seg = std::max<int>(1, (int)std::ceil(std::sqrt((double)std::max<int64_t>(1, M))));
     const int nck = (int)((M + c->seg - 1) / c->seg) + 1;
     if ((int)c->ckpt.size() < nck) {
@@ -1063,6 +1067,8 @@ static int apply_common(swcs_ctx* c, ChainSpec& sp, double eps, int64_t ncut, in
       c->bind_buffers();
     }
     HIP_TRY(c, c->ckpt_n.ensure((size_t)nck * sizeof(u64)), "alloc ckpt sizes");
+    int r = state_reset_to_reference(c, M);
+    if (r) return r;
   }
   Counters h;
   u64 n_start = 1;
@@ -1074,6 +1080,11 @@ static int apply_common(swcs_ctx* c, ChainSpec& sp, double eps, int64_t ncut, in
   }
   int r = run_chain(c, sp.ops.data(), sp.cs.data(), sp.sn.data(), M, eps, (unsigned)ncut, from_reference,
                     n_start, &h, sp.kind.data(), sp.gen.data());
+  if (r && from_reference && c->have_state && chain_in_lds(c, 1, M)) {
+    // the chain may have failed before the index it would have left was built
+    (void)launch_hash_clear(c->st.hash, c->st.hmask + 1, c->stream);
+    (void)launch_hash_build_dev(c->st, grid_blocks(c, c->st.cap, 256), c->stream);
+  }
   if (r) return r;
   r = build_filter(c, h.n, h.alive);
   if (r) return r;
