@@ -1252,15 +1252,20 @@ static int export_sorted(swcs_ctx* c, u64 n, u64 alive, const double* vals, uint
                          double* out) {
   HIP_TRY(c, c->exp_keys.ensure(n * 8), "alloc");
   HIP_TRY(c, c->exp_amps.ensure(n * 8), "alloc");
-  HIP_TRY(c, c->exp_tmp_k.ensure(n * 8), "alloc");
-  HIP_TRY(c, c->exp_tmp_v.ensure(n * 8), "alloc");
-  const u64 scr = std::max(radix_sort_scratch_elems(n), compact_scratch_elems(n));
-  HIP_TRY(c, c->sort_scratch.ensure(scr * 8), "alloc");
-  HIP_TRY(c, launch_compact_alive(c->st, n, vals, c->exp_keys.as<u64>(), c->exp_amps.as<double>(),
-                                  c->scalars.as<u64>() + 8, c->sort_scratch.as<u64>(), scr, c->stream), "compact");
-  HIP_TRY(c, radix_sort_pairs(c->exp_keys.as<u64>(), c->exp_amps.as<u64>(), c->exp_tmp_k.as<u64>(),
-                              c->exp_tmp_v.as<u64>(), alive, c->nso, c->sort_scratch.as<u64>(), scr,
-                              c->stream), "sort");
+  if (n <= export_small_max()) {
+    HIP_TRY(c, launch_export_small(c->st, n, alive, vals, c->exp_keys.as<u64>(), c->exp_amps.as<double>(), c->stream),
+            "sorted export");
+  } else {
+    HIP_TRY(c, c->exp_tmp_k.ensure(n * 8), "alloc");
+    HIP_TRY(c, c->exp_tmp_v.ensure(n * 8), "alloc");
+    const u64 scr = std::max(radix_sort_scratch_elems(n), compact_scratch_elems(n));
+    HIP_TRY(c, c->sort_scratch.ensure(scr * 8), "alloc");
+    HIP_TRY(c, launch_compact_alive(c->st, n, vals, c->exp_keys.as<u64>(), c->exp_amps.as<double>(),
+                                    c->scalars.as<u64>() + 8, c->sort_scratch.as<u64>(), scr, c->stream), "compact");
+    HIP_TRY(c, radix_sort_pairs(c->exp_keys.as<u64>(), c->exp_amps.as<u64>(), c->exp_tmp_k.as<u64>(),
+                                c->exp_tmp_v.as<u64>(), alive, c->nso, c->sort_scratch.as<u64>(), scr,
+                                c->stream), "sort");
+  }
   HIP_TRY(c, hipMemcpyAsync(keys, c->exp_keys.p, alive * 8, hipMemcpyDeviceToHost, c->stream), "copy");
   HIP_TRY(c, hipMemcpyAsync(out, c->exp_amps.p, alive * 8, hipMemcpyDeviceToHost, c->stream), "copy");
   HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");

@@ -612,6 +612,10 @@ hipError_t radix_sort_keys(u64* keys, u64* tmp_keys, u64 count, int key_bits, u6
                            u64 scratch_elems, hipStream_t stream, u64** out_keys);
 u64 radix_sort_scratch_elems(u64 count);
 u64 compact_scratch_elems(u64 n);
+// Sorted export of a state of at most export_small_max() stored entries.
+u64 export_small_max();
+hipError_t launch_export_small(const DeviceState& st, u64 n, u64 alive, const double* vals, u64* out_keys,
+                               double* out_vals, hipStream_t stream);
 
 // Screener.
 hipError_t launch_fock(const double* h, const double* eri, int n, int n_occ, double* fock,

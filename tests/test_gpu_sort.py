@@ -37,3 +37,19 @@ def test_export_sorted(ctx, drawn, n):
     k, a = ctx.get_state()
     o = np.argsort(keys)
     assert np.array_equal(k, keys[o]) and np.array_equal(a, amps[o])
+
+
+@pytest.mark.parametrize("n", [3, 1000, 4095, 4096, 4097])
+def test_export_of_pruned_states(ctx, n):
+    """Dead entries among the stored ones, on both sides of the export's switch
+    from one workgroup to the radix sort."""
+    keys = np.random.default_rng(n).permutation(np.asarray(draw_synthetic_state(N, NE // 2, NE // 2, 3 * n, 8)[0]))[:n]
+    amps = np.random.default_rng(n + 1).standard_normal(n)
+    amps[::3] *= 1e-6
+    ctx.set_state(keys, amps)
+    op = int(np.flatnonzero((enumerate_pool(N) == np.array([31, 1, -1, -1])).all(1))[0])
+    ctx.apply_gates([op], [0.0], 1e-3)  # an angle of 0 moves nothing; the threshold prunes
+    k, a = ctx.get_state()
+    keep = np.abs(amps) >= 1e-3
+    o = np.argsort(keys[keep])
+    assert np.array_equal(k, keys[keep][o]) and np.array_equal(a, amps[keep][o])
