@@ -635,15 +635,15 @@ hipError_t launch_join_reduce(const DeviceState& st, const u64* recs, u64 R, con
 // blocks.
 constexpr u64 kJoinTermChunkMax = 1ULL << 20, kJoinTermChunkMin = 1ULL << 12;
 __global__ void __launch_bounds__(kJoinBlock)
-k_join_terms(JoinTerms terms, int per_bin, u64 chunk, double* __restrict__ gacc, long long K) {
-  __shared__ double acc[kJoinTermSlots];
+k_join_terms(JoinTerms terms, int per_bin, u64 chunk, int slots, double* __restrict__ gacc, long long K) {
+  extern __shared__ double acc[];  // slots: operators of a bin
   const int b = (int)(blockIdx.x / (unsigned)per_bin);
   const u64 c = blockIdx.x % (unsigned)per_bin;
   const u64 filled = terms.cursor[b] < terms.cap ? terms.cursor[b] : terms.cap;
   const u64 lo = c * chunk;
   if (lo >= filled) return;  // uniform over the block
   const u64 hi = lo + chunk < filled ? lo + chunk : filled;
-  for (int s = threadIdx.x; s < kJoinTermSlots; s += kJoinBlock) acc[s] = 0.0;
+  for (int s = threadIdx.x; s < slots; s += kJoinBlock) acc[s] = 0.0;
   __syncthreads();
   const double* __restrict__ w = terms.w + (u64)b * terms.cap;
   const unsigned short* __restrict__ j = terms.j + (u64)b * terms.cap;
@@ -655,17 +655,17 @@ k_join_terms(JoinTerms terms, int per_bin, u64 chunk, double* __restrict__ gacc,
   for (u64 q = threadIdx.x; q < n4; q += kJoinBlock) {
     const double2 a = w2[2 * q], bb = w2[2 * q + 1];
     const ushort4 s = j4[q];
-    if (s.x < kJoinTermSlots) atomicAdd(&acc[s.x], a.x);
-    if (s.y < kJoinTermSlots) atomicAdd(&acc[s.y], a.y);
-    if (s.z < kJoinTermSlots) atomicAdd(&acc[s.z], bb.x);
-    if (s.w < kJoinTermSlots) atomicAdd(&acc[s.w], bb.y);
+    if (s.x < slots) atomicAdd(&acc[s.x], a.x);
+    if (s.y < slots) atomicAdd(&acc[s.y], a.y);
+    if (s.z < slots) atomicAdd(&acc[s.z], bb.x);
+    if (s.w < slots) atomicAdd(&acc[s.w], bb.y);
   }
   for (u64 i = lo + 4 * n4 + threadIdx.x; i < hi; i += kJoinBlock) {
     const unsigned s = j[i];
-    if (s < (unsigned)kJoinTermSlots) atomicAdd(&acc[s], w[i]);
+    if (s < (unsigned)slots) atomicAdd(&acc[s], w[i]);
   }
   __syncthreads();
-  for (int s = threadIdx.x; s < kJoinTermSlots; s += kJoinBlock) {
+  for (int s = threadIdx.x; s < slots; s += kJoinBlock) {
     const double v = acc[s];
     const long long k = ((long long)s << terms.lb) | b;
     if (v != 0.0 && k < K) unsafeAtomicAdd(&gacc[k], v);
@@ -680,8 +680,9 @@ hipError_t launch_join_terms(JoinTerms terms, double* gacc, long long K, hipStre
   const u64 per_bin = (terms.cap + chunk - 1) / chunk;
   const u64 grid = per_bin << terms.lb;
   if (per_bin == 0 || grid > 0x7fffffffULL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_join_terms, dim3((unsigned)grid), dim3(kJoinBlock), 0, stream, terms, (int)per_bin, chunk,
-                     gacc, K);
+  const int slots = (int)std::min<long long>(kJoinTermSlots, ((K - 1) >> terms.lb) + 1);
+  hipLaunchKernelGGL(k_join_terms, dim3((unsigned)grid), dim3(kJoinBlock), (size_t)slots * sizeof(double), stream, terms,
+                     (int)per_bin, chunk, slots, gacc, K);
   return hipGetLastError();
 }
 

@@ -174,7 +174,7 @@ struct swcs_ctx {
   DevBuf gacc, selected, ncut_state, ncut_cand, qfilt;
   DevBuf partial, partial2, sigma, mu, work, seg_states, acc_tab, gbuf, subset_buf, scalars,
       exp_keys, exp_amps, exp_tmp_k, exp_tmp_v, sort_scratch, ctr_r, occ, sel_scratch, mlp_partial, mse_partial, hp_key, hp_val, hp_tk, hp_tv, diag, join_src,
-      join_w, join_j, join_bins, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs, rdm_mem,
+      join_w, rdm_g3, rdm_g2, rdm_vtab, rdm_part, rdm_bs, rdm_mem,
       str_rec, str_key, str_val, str_oth, str_tab;
   int sigma_method = SWCS_SIGMA_AUTO;
   int pool_method = SWCS_POOL_AUTO;
@@ -195,8 +195,8 @@ struct swcs_ctx {
                      &partial, &partial2, &sigma, &mu, &work, &seg_states, &acc_tab, &gbuf,
                      &subset_buf, &scalars, &exp_keys, &exp_amps, &exp_tmp_k, &exp_tmp_v,
                      &sort_scratch, &ctr_r, &occ, &sel_scratch, &mlp_partial, &mse_partial,
-                     &hp_key, &hp_val, &hp_tk, &hp_tv, &diag, &qfilt, &join_src, &join_w, &join_j,
-                     &join_bins, &rdm_g3, &rdm_g2, &rdm_vtab, &rdm_part, &rdm_bs, &rdm_mem, &str_rec, &str_key,
+                     &hp_key, &hp_val, &hp_tk, &hp_tv, &diag, &qfilt, &join_src, &join_w,
+                     &rdm_g3, &rdm_g2, &rdm_vtab, &rdm_part, &rdm_bs, &rdm_mem, &str_rec, &str_key,
                      &str_val, &str_oth, &str_tab};
     for (DevBuf* b : all) f(*b);
     for (auto& b : ckpt) f(b);
@@ -332,7 +332,7 @@ size_t avail_bytes(swcs_ctx* c) {
 void release_scratch(swcs_ctx* c) {
   DevBuf* bufs[] = {&c->acc_tab, &c->hp_key, &c->hp_val, &c->hp_tk, &c->hp_tv, &c->sort_scratch,
                     &c->exp_keys, &c->exp_amps, &c->exp_tmp_k, &c->exp_tmp_v, &c->qfilt, &c->join_src, &c->join_w,
-                    &c->join_j, &c->rdm_g3, &c->rdm_part, &c->rdm_mem, &c->seg_states, &c->work, &c->str_rec, &c->str_key,
+                    &c->rdm_g3, &c->rdm_part, &c->rdm_mem, &c->seg_states, &c->work, &c->str_rec, &c->str_key,
                     &c->str_val, &c->str_oth, &c->str_tab};
   for (DevBuf* b : bufs) b->release();
 }
@@ -343,7 +343,7 @@ void release_scratch(swcs_ctx* c) {
 // join of a smaller state earlier does not shrink (and split into batches)
 // the table of a larger one.
 void release_join_scratch(swcs_ctx* c) {
-  DevBuf* bufs[] = {&c->hp_key, &c->hp_tk, &c->join_src, &c->sort_scratch, &c->join_w, &c->join_j};
+  DevBuf* bufs[] = {&c->hp_key, &c->hp_tk, &c->join_src, &c->sort_scratch, &c->join_w};
   size_t held = 0;
   for (DevBuf* b : bufs) held += b->bytes;
   if (held < ((size_t)1 << 30)) return;
@@ -2074,7 +2074,7 @@ static int join_gradients(swcs_ctx* c, const Counters& h, const unsigned char* d
   const u64 list_bytes = n * 16;  // (key, psi) of every stored entry
   const double need = 16.0 * (double)R + 8.0 * (double)scr + (double)list_bytes;
   const double have = (double)(avail_bytes(c) + c->hp_key.bytes + c->hp_tk.bytes + c->sort_scratch.bytes +
-                               c->join_src.bytes + c->join_w.bytes + c->join_j.bytes);
+                               c->join_src.bytes + c->join_w.bytes);
   if (need > 0.5 * have) {
     if (forced) return fail(c, SWCS_E_CAPACITY, "join records exceed half of the free device memory");
     return 1;
@@ -2087,15 +2087,17 @@ static int join_gradients(swcs_ctx* c, const Counters& h, const unsigned char* d
   JoinTerms terms{-1, 0, nullptr, nullptr, nullptr};
   {
     int lb = 0;
+    while (lb < kJoinBinsLog && (u64)c->K_pool > (256ULL << lb)) ++lb;
     while (lb <= kJoinMaxBinsLog && (u64)c->K_pool > ((u64)kJoinTermSlots << lb)) ++lb;
     const u64 cap = ((u64)(1.25 * (double)R / (double)(1ULL << lb)) + 4096 + 7) & ~7ULL;
     const double bin_bytes = 10.0 * (double)cap * (double)(1ULL << lb);
     if (lb <= kJoinMaxBinsLog && need + bin_bytes <= 0.5 * have) {
-      HIP_TRY(c, c->join_w.ensure((size_t)(cap << lb) * 8), "alloc join terms");
-      HIP_TRY(c, c->join_j.ensure((size_t)(cap << lb) * 2), "alloc join terms");
-      HIP_TRY(c, c->join_bins.ensure((size_t)8 << lb), "alloc join bins");
-      HIP_TRY(c, launch_fill_u32(c->join_bins.p, 0u, (u64)2 << lb, c->stream), "zero bins");
-      terms = JoinTerms{lb, cap, c->join_bins.as<u64>(), c->join_w.as<double>(), c->join_j.as<unsigned short>()};
+      // one buffer: the bins' cursors (2 KB kept for them), values, operators
+      const size_t head = (size_t)8 << kJoinMaxBinsLog;
+      HIP_TRY(c, c->join_w.ensure(head + (size_t)(cap << lb) * 10), "alloc join terms");
+      HIP_TRY(c, launch_fill_u32(c->join_w.p, 0u, (u64)2 << lb, c->stream), "zero bins");
+      double* w = (double*)((char*)c->join_w.p + head);
+      terms = JoinTerms{lb, cap, c->join_w.as<u64>(), w, (unsigned short*)(w + (cap << lb))};
     }
   }
   HIP_TRY(c, c->hp_key.ensure(R * 8), "alloc join records");
