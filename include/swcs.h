@@ -199,7 +199,9 @@ int swcs_set_pool(swcs_ctx* ctx, const int32_t* ops, int64_t K);
  * the end, as in step 5 of ADAPT), pruning after every unitary (Fig. 1) with
  * eps (ncut == 0) or ncut (ncut > 0).  op_idx[M], theta[M] are host arrays;
  * M may be 0.  *n_det_out (may be NULL) receives the number of kept
- * determinants.  The run keeps checkpoints for swcs_param_gradients. */
+ * determinants.  The run keeps checkpoints for swcs_param_gradients.  A call
+ * that runs out of device memory after its first gate (here and below) leaves
+ * no current state. */
 int swcs_apply_ansatz(swcs_ctx* ctx, const int32_t* op_idx, const double* theta, int64_t M,
                       double eps, int64_t ncut, int64_t* n_det_out);
 

@@ -639,16 +639,29 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     h.stop_gate = 0;
     HIP_TRY(c, launch_store_counters(c->st.ctr, h, c->stream), "counters");
   }
-  for (int attempt = 0; attempt < 64; ++attempt) {
+  // From its first gate on, a chain that cannot be brought to its end leaves no
+  // state: the counts of gates under way are in the rotating slots, and the
+  // filter is built behind the last gate.
+  bool begun = g0 > 0;
+  auto part_way = [&](int r) {
+    if (begun) c->have_state = false;
+    return r;
+  };
+  // Buffers of the gates from g0 on, allocated before the first is enqueued.
+  auto reserve = [&]() -> int {
     if (ncut) {
       int r = ncut_reserve(c, 1, c->st.cap);
       if (r) return r;
     }
+    for (int64_t j = ckpt ? (g0 + c->seg - 1) / c->seg : M; j * c->seg < M; ++j)
+      HIP_TRY(c, c->ckpt[(size_t)j].ensure(c->st.cap * sizeof(double)), "alloc checkpoint");
+    return SWCS_OK;
+  };
+  auto enqueue = [&]() -> int {
     HIP_TRY(c, launch_live_begin(c->st, (unsigned)g0, c->stream), "counters");
     for (int64_t g = g0; g < M; ++g) {
       if (ckpt && g % c->seg == 0) {
         const int j = (int)(g / c->seg);
-        HIP_TRY(c, c->ckpt[j].ensure(c->st.cap * sizeof(double)), "alloc checkpoint");
         HIP_TRY(c, launch_ckpt_save(c->st, (unsigned)g, c->ckpt[j].as<double>(), c->ckpt_n.as<u64>() + j,
                                     grid_blocks(c, c->st.cap / 4, 256), c->stream), "checkpoint");
       }
@@ -672,9 +685,17 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
                                ncut, c->st.cap, 1, c->stream), "ncut");
     }
     HIP_TRY(c, launch_live_end(c->st, (unsigned)M, c->stream), "counters");
+    return SWCS_OK;
+  };
+  for (int attempt = 0; attempt < 64; ++attempt) {
+    int r = reserve();
+    if (r) return part_way(r);
+    begun = true;
+    r = enqueue();
+    if (r) return part_way(r);
     hipError_t e;
     Counters h = read_counters(c, &e);
-    if (e != hipSuccess) return hip_fail(c, e, "read counters");
+    if (e != hipSuccess) return part_way(hip_fail(c, e, "read counters"));
     if (h.flags & kFlagOverflow) {
       h.flags &= ~(kFlagOverflow | kFlagStopped);
       HIP_TRY(c, launch_store_counters(c->st.ctr, h, c->stream), "counters");
@@ -684,8 +705,8 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     if (!(h.flags & kFlagStopped)) {
       // a chain without checkpoints leaves no record of storage positions
       if (!ckpt && compact_due(h)) {
-        int r = state_compact(c, &h);
-        if (r) return r;
+        r = state_compact(c, &h);
+        if (r) return part_way(r);
       }
       *out = h;
       return SWCS_OK;
@@ -698,8 +719,8 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     // and the arrays grow only if the gate still does not fit.
     const bool star_stop = kind && kind[g0];
     if (!ckpt && h.n - h.alive >= kCompactMin && 4 * (h.n - h.alive) >= h.alive) {
-      int r = state_compact(c, &h);
-      if (r) return r;
+      r = state_compact(c, &h);
+      if (r) return part_way(r);
       const u64 room = c->sector > h.n ? c->sector - h.n : 0;
       const u64 grow_c = star_stop ? 2 * h.alive : h.alive;
       if (h.n + std::min<u64>(grow_c, room) <= c->st.cap) continue;
@@ -721,8 +742,8 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     }
     if (cap > maxc) cap = maxc;
     if (cap < need) return fail(c, SWCS_E_CAPACITY, "state exceeds the maximum capacity");
-    int r = state_reserve(c, cap, h.n);
-    if (r) return r;
+    r = state_reserve(c, cap, h.n);
+    if (r) return part_way(r);
     // Checkpoint of the gate where the chain resumes was skipped if it lies
     // on a segment boundary: the loop above re-enqueues it.
   }

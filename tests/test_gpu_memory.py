@@ -1,0 +1,115 @@
+"""Device memory that runs out part way: an allocator that refuses chosen blocks.
+A call either finds its way with less scratch, with the same results, or fails
+with SWCS_E_OOM and leaves no state that is neither the old nor the new one."""
+import numpy as np
+import pytest
+
+from paper_2411_07920_amd.inputs import enumerate_pool, make_integrals
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def swcs():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2411_07920_amd import swcs as mod
+    mod.load()
+    return mod
+
+
+class Memory:
+    """PyTorch's allocator behind a rule: refuse(nbytes, k) for the k-th request
+    since the rule was set.  sizes: requests since then; held: live blocks."""
+
+    def __init__(self):
+        self.held = {}
+        self.rule(lambda nbytes, k: False)
+
+    def rule(self, refuse):
+        self.refuse = refuse
+        self.sizes = []
+        self.refused = 0
+
+    def alloc(self, nbytes):
+        import torch
+        self.sizes.append(nbytes)
+        if self.refuse(nbytes, len(self.sizes) - 1):
+            self.refused += 1
+            return 0
+        p = torch.cuda.caching_allocator_alloc(nbytes, 0, torch.cuda.current_stream())
+        self.held[p] = nbytes
+        return p
+
+    def free(self, p):
+        import torch
+        del self.held[p]
+        torch.cuda.caching_allocator_delete(p)
+
+
+def _reference(na, nb):
+    return sum(1 << (2 * p) for p in range(na)) | sum(1 << (2 * p + 1) for p in range(nb))
+
+
+def _context(swcs, n, na, nb):
+    h, eri = make_integrals(n, n, 50 + n)
+    ctx = swcs.Context(n, na, nb)
+    mem = Memory()
+    import torch
+    ctx.set_stream(torch.cuda.current_stream())
+    ctx.set_allocator(mem.alloc, mem.free)
+    ctx.set_integrals(h, eri)
+    ctx.set_reference(_reference(na, nb))
+    ctx.set_pool(enumerate_pool(n))
+    return ctx, mem
+
+
+def _excitations(n, na, nb):
+    """Pool rows that act on the reference."""
+    ref, out = _reference(na, nb), []
+    for k, (P, Q, R, S) in enumerate(enumerate_pool(n).tolist()):
+        cre, ann = ([P, Q], [R, S]) if R >= 0 else ([P], [Q])
+        if all(ref >> a & 1 for a in ann) and not any(ref >> a & 1 for a in cre):
+            out.append(k)
+    return np.array(out, dtype=np.int32)
+
+
+def _chain(n=11, na=5, nb=4, M=60):
+    """A chain whose state leaves LDS and grows its arrays several times: 81,571
+    determinants."""
+    rng = np.random.default_rng(3)
+    ops = rng.choice(_excitations(n, na, nb), M, replace=False).astype(np.int32)
+    return n, na, nb, ops, rng.uniform(-0.6, 0.6, M)
+
+
+def test_checkpoint_refused_after_growth(swcs):
+    """The arrays have grown and a checkpoint of the new size is refused.  Its
+    size is that of keys and amplitudes, which are asked for first."""
+    n, na, nb, ops, theta = _chain()
+    ctx, mem = _context(swcs, n, na, nb)
+    ctx.apply_ansatz(ops, theta)
+    asked = list(mem.sizes)
+    want = ctx.get_state()
+    ctx.close()
+    grown = sorted({s for s in asked if s > 8 * 4096 and asked.count(s) > 2})
+    print(f"[memory] blocks of {grown} bytes: {[asked.count(s) for s in grown]}", flush=True)
+    assert grown
+    for size in grown:
+        for which in {2, asked.count(size) - 1}:
+            ctx, mem = _context(swcs, n, na, nb)
+            print(f"[memory] checkpoint {which - 2} of {size} bytes refused", flush=True)
+            mem.rule(lambda nbytes, k: nbytes == size and mem.sizes.count(size) == which + 1)
+            with pytest.raises(swcs.SwcsError) as ei:
+                ctx.apply_ansatz(ops, theta)
+            assert ei.value.code == swcs.SWCS_E_OOM and mem.refused == 1
+            mem.rule(lambda nbytes, k: False)
+            for call in (ctx.get_state, ctx.energy, lambda: ctx.apply_gates(ops[:1], theta[:1])):
+                with pytest.raises(swcs.SwcsError) as ei:
+                    call()
+                assert ei.value.code == swcs.SWCS_E_STATE
+            ctx.apply_ansatz(ops, theta)
+            got = ctx.get_state()
+            assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+            assert abs(np.sum(got[1] ** 2) - 1.0) < 1e-12
+            ctx.close()
