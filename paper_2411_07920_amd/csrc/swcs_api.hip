@@ -393,18 +393,27 @@ u64 fixed_capacity(swcs_ctx* c) {
 }
 
 // (Re)allocate the state arrays with capacity `cap`, preserving the first
-// n_keep entries, and rebuild the hash index.
+// n_keep entries, and rebuild the hash index.  Without room for keys and
+// amplitudes the old arrays stay; without room for the index or the filter
+// behind them (the old index goes first, it is the largest block) there is no
+// state, and the next call that sets one allocates all of it.
 int state_reserve(swcs_ctx* c, u64 cap, u64 n_keep) {
   const u64 hslots = next_pow2(2 * cap);
   DevBuf nk, na;
   nk.cur = &c->alloc;
   na.cur = &c->alloc;
   HIP_TRY(c, nk.ensure(cap * sizeof(u64)), "alloc keys");
-  HIP_TRY(c, na.ensure(cap * sizeof(double)), "alloc amps");
-  if (n_keep > 0) {
-    HIP_TRY(c, hipMemcpyAsync(nk.p, c->keys.p, n_keep * sizeof(u64), hipMemcpyDeviceToDevice, c->stream), "copy keys");
-    HIP_TRY(c, hipMemcpyAsync(na.p, c->amps.p, n_keep * sizeof(double), hipMemcpyDeviceToDevice, c->stream), "copy amps");
-    HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+  hipError_t e = na.ensure(cap * sizeof(double));
+  if (e == hipSuccess && n_keep > 0) {
+    e = hipMemcpyAsync(nk.p, c->keys.p, n_keep * sizeof(u64), hipMemcpyDeviceToDevice, c->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(na.p, c->amps.p, n_keep * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  }
+  if (e != hipSuccess) {
+    nk.release();
+    na.release();
+    return hip_fail(c, e, "alloc amps");
   }
   c->keys.release();
   c->amps.release();
@@ -412,6 +421,10 @@ int state_reserve(swcs_ctx* c, u64 cap, u64 n_keep) {
   c->amps = na;
   nk.p = nullptr;
   na.p = nullptr;
+  const bool had_state = c->have_state;
+  c->have_state = false;
+  c->ansatz_valid = false;
+  c->st.cap = 0;
   if (c->hash.bytes < hslots * sizeof(HashSlot)) {
     c->hash.release();
     HIP_TRY(c, c->hash.ensure(hslots * sizeof(HashSlot)), "alloc hash");
@@ -422,13 +435,14 @@ int state_reserve(swcs_ctx* c, u64 cap, u64 n_keep) {
   c->st.keys = c->keys.as<u64>();
   c->st.amps = c->amps.as<double>();
   c->st.hash = c->hash.as<HashSlot>();
-  c->st.cap = cap;
   c->st.hmask = hslots - 1;
   c->st.filt = c->filt.as<unsigned>();
   c->st.fmask = fbits - 1;
   c->st.ctr = c->ctr.as<Counters>();
   HIP_TRY(c, launch_hash_clear(c->st.hash, hslots, c->stream), "hash clear");
   if (n_keep > 0) HIP_TRY(c, launch_hash_build(c->st, n_keep, c->stream), "hash build");
+  c->st.cap = cap;
+  c->have_state = had_state && n_keep > 0;
   return SWCS_OK;
 }
 

@@ -113,3 +113,52 @@ def test_checkpoint_refused_after_growth(swcs):
             assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
             assert abs(np.sum(got[1] ** 2) - 1.0) < 1e-12
             ctx.close()
+
+
+@pytest.mark.parametrize("start", ["reference", "set_state"])
+def test_every_block_refused_in_turn(swcs, start):
+    """Each block that a chain asks for, in a fresh context: the state arrays, the
+    index and the filter among them.  The context then refuses its state or holds
+    a whole one, takes a new chain, and gives back every block."""
+    n, na, nb, ops, theta = _chain()
+    ops, theta = ops[:48], theta[:48]  # 36,052 determinants
+    ctx, mem = _context(swcs, n, na, nb)
+    ctx.apply_ansatz(ops[:30], theta[:30])
+    first = ctx.get_state()
+    ctx.apply_gates(ops[30:], theta[30:])
+    want = ctx.get_state()
+    ctx.close()
+    assert not mem.held
+    k = 0
+    while True:
+        ctx, mem = _context(swcs, n, na, nb)
+        if start == "set_state":
+            ctx.set_state(*first)
+        print(f"[memory] {start}: block {k} refused", flush=True)
+        mem.rule(lambda nbytes, i: i == k)
+        try:
+            if start == "reference":
+                ctx.apply_ansatz(ops, theta)
+            else:
+                ctx.apply_gates(ops[30:], theta[30:])
+        except swcs.SwcsError as e:
+            assert e.code == swcs.SWCS_E_OOM
+        last = not mem.refused
+        mem.rule(lambda nbytes, i: False)
+        try:
+            assert abs(np.sum(ctx.get_state()[1] ** 2) - 1.0) < 1e-12  # eps = 0: unitary
+        except swcs.SwcsError as e:
+            assert e.code == swcs.SWCS_E_STATE
+        if not last:  # neither chain is on record for the adjoint
+            with pytest.raises(swcs.SwcsError) as ei:
+                ctx.param_gradients(len(ops))
+            assert ei.value.code == swcs.SWCS_E_STATE
+        ctx.apply_ansatz(ops, theta)
+        got = ctx.get_state()
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+        ctx.close()
+        assert not mem.held
+        if last:
+            break
+        k += 1
+    assert k > 10
