@@ -57,6 +57,7 @@ struct DevBuf {
     } else {
       hipError_t e = hipMalloc(&p, want);
       if (e != hipSuccess) {
+        (void)hipGetLastError();  // or the next launch would report it as its own
         p = nullptr;
         return e;
       }
@@ -2306,12 +2307,41 @@ int swcs_pool_gradients(swcs_ctx* c, const int32_t* subset, int64_t n_subset, do
 }
 
 // Segments replayed side by side: as many as fit these bytes of logs and
-// working copies, at least one (a large state's gate fills the device by
-// itself, so there is nothing to gain from holding more).
+// working copies and half of the memory there is, at least one (a large state's
+// gate fills the device by itself, so there is nothing to gain from holding more).
 constexpr size_t kReplayGroupBytes = (size_t)4 << 30;
 // Records of a gate that one workgroup walks back (eight per thread); from
 // there a launch of many blocks is faster.
 constexpr u64 kWalkMaxRecords = 8192;
+
+// Buffers for replaying *segs segments of n entries side by side.  Where a block
+// is refused it is tried with half as many segments, and one segment once more
+// after everything that holds nothing has been given back.
+static int replay_reserve(swcs_ctx* c, u64 n, int nseg, size_t gate_log_bytes, int* segs) {
+  DevBuf* bufs[] = {&c->seg_states, &c->work, &c->ncut_cand, &c->ncut_state};
+  const size_t seg_bytes = (size_t)c->seg * gate_log_bytes + n * 8 + (c->a_ncut ? n * 4 + ncut_select_bytes() : 0);
+  size_t s = std::min<size_t>((size_t)nseg, std::max<size_t>(1, kReplayGroupBytes / seg_bytes));
+  size_t held = 0;
+  for (DevBuf* b : bufs) held += b->bytes;
+  if (s * seg_bytes > held) s = std::min(s, std::max<size_t>(1, (held + avail_bytes(c)) / 2 / seg_bytes));
+  auto take = [&]() -> int {
+    HIP_TRY(c, c->seg_states.ensure(s * c->seg * gate_log_bytes), "alloc pair logs");
+    HIP_TRY(c, c->work.ensure(s * n * 8), "alloc working amplitudes");
+    HIP_TRY(c, c->ctr_r.ensure(2 * s * c->seg * sizeof(u64)), "alloc log counters");
+    return c->a_ncut ? ncut_reserve(c, (int)s, n) : SWCS_OK;
+  };
+  int r = take();
+  for (bool all_given = false; r == SWCS_E_OOM && !all_given; r = take()) {
+    for (DevBuf* b : bufs) b->release();
+    if (s == 1) {
+      release_scratch(c);
+      all_given = true;
+    }
+    s = (s + 1) / 2;
+  }
+  *segs = (int)s;
+  return r;
+}
 
 int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   if (!c) return SWCS_E_INVALID;
@@ -2340,7 +2370,7 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   const int grid = grid_blocks(c, n, 256);
   HIP_TRY(c, c->mu.ensure(n * 8), "alloc mu");
   HIP_TRY(c, c->gbuf.ensure((size_t)(M + 3) * 8), "alloc dE");  // and the energy's sums and the flags
-  const bool lds = n <= (u64)lds_chain_capacity();
+  bool lds = n <= (u64)lds_chain_capacity();
   const GenGate* gens = nullptr;
   const int* kinds = nullptr;
   if (c->a_has_star) {
@@ -2354,12 +2384,16 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   const size_t gate_log_bytes = n * (sizeof(PairRec) + (c->a_has_star ? sizeof(StarRec) : 0));
   HIP_TRY(c, launch_mu_init(c->st, c->sigma.as<double>(), n, nn, c->mu.as<double>(), c->stream), "mu init");
   if (lds) {
+    const hipError_t el = c->seg_states.ensure((size_t)M * gate_log_bytes);
+    if (el != hipSuccess && el != hipErrorOutOfMemory) return hip_fail(c, el, "alloc pair logs");
+    lds = el == hipSuccess;  // without room for every gate's log: in groups of segments
+  }
+  if (lds) {
     // Segments replayed side by side (one workgroup each), then one
     // workgroup walks every gate back with mu in LDS; the gate table of the
     // last apply call is reused.
     int r2 = upload_ckpt_table(c, nseg);
     if (r2) return r2;
-    HIP_TRY(c, c->seg_states.ensure((size_t)M * gate_log_bytes), "alloc pair logs");
     char* logs = (char*)c->seg_states.p;
     HIP_TRY(c, c->ctr_r.ensure((size_t)2 * M * sizeof(unsigned)), "alloc log counters");
     HIP_TRY(c, c->partial2.ensure(adjoint_lds_part_elems((int)M) * sizeof(double)), "alloc partials");
@@ -2375,20 +2409,14 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
     // working copies, replay the segments side by side (one launch per step
     // of a segment) logging the active pairs of every gate, then walk the
     // logs back.
-    const size_t seg_bytes = (size_t)seg * gate_log_bytes + n * 8;
-    const int gsegs = (int)std::min<size_t>((size_t)nseg, std::max<size_t>(1, kReplayGroupBytes / seg_bytes));
+    int gsegs = 1;
+    r = replay_reserve(c, n, nseg, gate_log_bytes, &gsegs);
+    if (r) return r;
     const u64 pstride = (u64)std::max(grid, 16);  // the walk's sixteen wavefronts
-    HIP_TRY(c, c->seg_states.ensure((size_t)gsegs * seg * gate_log_bytes), "alloc pair logs");
     HIP_TRY(c, c->partial2.ensure((size_t)M * pstride * 8), "alloc partials");
     HIP_TRY(c, launch_fill_u32(c->partial2.p, 0u, (u64)M * pstride * 2, c->stream), "zero partials");
-    HIP_TRY(c, c->work.ensure((size_t)gsegs * n * 8), "alloc working amplitudes");
-    HIP_TRY(c, c->ctr_r.ensure((size_t)2 * gsegs * seg * sizeof(u64)), "alloc log counters");
     r = upload_ckpt_table(c, nseg);
     if (r) return r;
-    if (c->a_ncut) {
-      r = ncut_reserve(c, gsegs, n);
-      if (r) return r;
-    }
     double* W = c->work.as<double>();
     const double eps_r = c->a_ncut ? 0.0 : c->a_eps;
     const GateDesc* gates = c->gate_tab.as<GateDesc>();

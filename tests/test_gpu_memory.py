@@ -162,3 +162,58 @@ def test_every_block_refused_in_turn(swcs, start):
             break
         k += 1
     assert k > 10
+
+
+@pytest.mark.parametrize("kind", ["plain", "generators", "ncut", "lds", "lds generators"])
+def test_adjoint_in_groups_of_segments(swcs, kind):
+    """Parameter gradients where the logs of all segments are refused: groups of
+    fewer segments down to one, gates walked back by one workgroup and by a launch
+    each, and states of LDS size by the same groups.  Every gate's arithmetic is the
+    same; only the order of sigma's sums may differ, 1e-15 of it, through rotations."""
+    from paper_2411_07920_amd.spin import gen_rows, spin_complemented
+    n, na, nb, ops, theta = _chain()
+    ncut = 0
+    if kind.startswith("lds"):
+        ops, theta = ops[:30], theta[:30]
+    if kind == "ncut":
+        ncut = 6000
+    if kind.endswith("generators"):
+        pool = enumerate_pool(n).tolist()
+        gp = spin_complemented(enumerate_pool(n))
+        rng = np.random.default_rng(8)
+        acts = set(_excitations(n, na, nb).tolist())
+        rows = gen_rows(gp, np.arange(len(gp)))
+        some = [r for r in rows.tolist() if r[0] in acts and r[1] in acts]
+        count = 12 if kind.startswith("lds") else 30
+        rows = np.array([some[i] for i in rng.choice(len(some), count, replace=False)])
+        theta = rng.uniform(-0.6, 0.6, count)
+        apply = lambda c: c.apply_generators(rows, theta)
+        idx = [set(pool[a]) & set(pool[b]) for a, b, _ in rows]
+        gates = sum(1 if shared else 2 for shared in idx)
+    else:
+        apply = lambda c: c.apply_ansatz(ops, theta, 0.0, ncut)
+        gates = len(ops)
+    M, seg = len(theta), int(np.ceil(np.sqrt(gates)))
+    ctx, mem = _context(swcs, n, na, nb)
+    size = apply(ctx)
+    stored = ctx.state_counts()[0]
+    assert (stored <= 4096) == kind.startswith("lds") and (ncut or stored == size)
+    ctx.energy()
+    mem.rule(lambda nbytes, k: False)
+    dE, E = ctx.param_gradients(M)
+    logs = max(mem.sizes)  # the logs of all segments
+    print(f"[memory] {kind}: {size} determinants, {stored} stored, logs {logs} bytes", flush=True)
+    ctx.close()
+    logged = gates if kind.startswith("lds") else -(-gates // seg) * seg
+    for room in (logs // 2, logs // 3, logs // logged * seg):  # the last: of one segment
+        ctx, mem = _context(swcs, n, na, nb)
+        apply(ctx)
+        ctx.energy()
+        mem.rule(lambda nbytes, k: nbytes > room)
+        print(f"[memory] {kind}: blocks up to {room} bytes", flush=True)
+        dE2, E2 = ctx.param_gradients(M)
+        assert mem.refused > 0 and max(s for s in mem.held.values()) <= logs
+        assert abs(E2 - E) < 1e-12 * abs(E)
+        assert np.abs(dE2 - dE).max() < 1e-12 * max(1.0, np.abs(dE).max())
+        ctx.close()
+    assert np.abs(dE).max() > 1e-3
