@@ -1695,20 +1695,26 @@ static bool rdm_pays_screened(int n, double records, double join_records, double
   return rdm_seconds(n, records, 1.5e-10) + 0.3e-3 < (1.5e-11 + 3.5e-10 * share) * join_records;
 }
 
-// Pool gradients of the `count` operators d_subset (NULL: the whole pool) into
-// d_out from the three-body density matrix (k_rdm.hip).  Returns 1 when the
-// pass does not apply: another method or a table budget is set, fewer than
-// three electrons, a small state, too little memory, or so many pairs of
-// determinants within a triple excitation that the join or the table does
-// less work.  Synchronizes (the pair count decides).
-static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, int64_t count, const double* norm2,
-                         double* d_out) {
-  if (c->pool_method != SWCS_POOL_AUTO || c->table_budget > 0) return 1;
+// A density-matrix pass: record format, sort, hash classes, and what the sample
+// found.
+struct RdmPlan {
+  RdmFmt fm;
+  int nbatch, sort_bits;
+  u64 ntri, total, cap;  // triples of a determinant; records in all and a class's room
+  double join_records, need, have;
+  bool rows, crowded;
+};
+
+// Whether the pass can be taken at all; fills everything of the plan but the
+// sample's findings.
+static bool rdm_plan(swcs_ctx* c, const Counters& h, RdmPlan* p) {
+  if (c->pool_method != SWCS_POOL_AUTO || c->table_budget > 0) return false;
   const int ne = c->na + c->nb;
-  if (ne < 3 || ne > kRdmMaxElectrons) return 1;
-  const double R_join = (double)h.alive * (double)(c->exc.total + 1);
-  const u64 n = h.n, ntri = (u64)ne * (u64)(ne - 1) * (u64)(ne - 2) / 6, total = h.alive * ntri;
-  if (!rdm_pays(c->n, (double)total, R_join)) return 1;
+  if (ne < 3 || ne > kRdmMaxElectrons) return false;
+  p->join_records = (double)h.alive * (double)(c->exc.total + 1);
+  p->ntri = (u64)ne * (u64)(ne - 1) * (u64)(ne - 2) / 6;
+  p->total = h.alive * p->ntri;
+  if (!rdm_pays(c->n, (double)p->total, p->join_records)) return false;
   // pairs of a state that is spread evenly over its sector: a state is at least
   // this crowded, so a full sector needs no sample
   {
@@ -1719,88 +1725,109 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
     const double t3 = c3(a) * c3(va) + c3(b) * c3(vb) + c2(a) * c2(va) * b * vb + c2(b) * c2(vb) * a * va;
     const double share = (double)h.alive / (double)c->sector;
     const double pairs = 0.5 * (double)h.alive * share * (t3 + (ne - 2.0) * t2 + c2(ne - 1.0) * t1);
-    if (pairs > kRdmPairLimit * R_join && !rdm_rows_pay((double)total, pairs, R_join)) return 1;
+    if (pairs > kRdmPairLimit * p->join_records && !rdm_rows_pay((double)p->total, pairs, p->join_records)) return false;
   }
   auto bits_for = [](u64 v) {
     int b = 1;
     while (b < 64 && (v >> b) != 0) ++b;
     return b;
   };
-  RdmFmt fm;
-  fm.bt = bits_for(ntri - 1);
-  fm.hb = std::min(48, 64 - fm.bt - bits_for(n - 1));
-  int nbatch = 1;
-  while (nbatch < 256 && total / (u64)nbatch > kRdmMaxRecords) nbatch *= 2;
+  p->fm.bt = bits_for(p->ntri - 1);
+  p->fm.hb = std::min(48, 64 - p->fm.bt - bits_for(h.n - 1));
+  p->nbatch = 1;
+  while (p->nbatch < 256 && p->total / (u64)p->nbatch > kRdmMaxRecords) p->nbatch *= 2;
   // room for an uneven split of the subsets over the hash classes
-  const u64 cap = nbatch == 1 ? total : total / (u64)nbatch + total / (u64)nbatch / 8 + 65536;
-  const int sort_bits = cap < (1ULL << 19) ? 16 : 24;
-  if (fm.hb < sort_bits + 8 || total / (u64)nbatch > kRdmMaxRecords) return 1;
-  const u64 scr = radix_sort_scratch_elems(cap);
-  const size_t g3 = rdm_gamma_elems(c->n), part = rdm_part_elems(c->n), two = rdm_two_elems(c->n),
-               vt = rdm_vtab_elems(c->n);
-  const double need = 8.0 * ((double)g3 + (double)part + (double)two + (double)vt + 2.0 * (double)cap + (double)scr);
-  const double have = (double)(avail_bytes(c) + c->hp_key.bytes + c->hp_tk.bytes + c->sort_scratch.bytes +
-                               c->rdm_g3.bytes + c->rdm_part.bytes + c->rdm_g2.bytes + c->rdm_vtab.bytes +
-                               c->rdm_mem.bytes);
-  if (need > 0.5 * have) return 1;
-  HIP_TRY(c, c->rdm_g3.ensure(g3 * 8), "alloc density matrix");
-  HIP_TRY(c, c->rdm_part.ensure(part * 8), "alloc density matrix");
-  HIP_TRY(c, c->rdm_g2.ensure(two * 8), "alloc density matrix");
-  HIP_TRY(c, c->rdm_vtab.ensure(vt * 8), "alloc density matrix");
+  const u64 even = p->total / (u64)p->nbatch;
+  p->cap = p->nbatch == 1 ? p->total : even + even / 8 + 65536;
+  p->sort_bits = p->cap < (1ULL << 19) ? 16 : 24;
+  if (p->fm.hb < p->sort_bits + 8 || even > kRdmMaxRecords) return false;
+  p->need = 8.0 * ((double)rdm_gamma_elems(c->n) + (double)rdm_part_elems(c->n) + (double)rdm_two_elems(c->n) +
+                   (double)rdm_vtab_elems(c->n) + 2.0 * (double)p->cap + (double)radix_sort_scratch_elems(p->cap));
+  p->have = (double)(avail_bytes(c) + c->hp_key.bytes + c->hp_tk.bytes + c->sort_scratch.bytes + c->rdm_g3.bytes +
+                     c->rdm_part.bytes + c->rdm_g2.bytes + c->rdm_vtab.bytes + c->rdm_mem.bytes);
+  return p->need <= 0.5 * p->have;
+}
+
+// Record buffers of r records.
+static int rdm_records(swcs_ctx* c, u64 r) {
+  HIP_TRY(c, c->hp_key.ensure(r * 8), "alloc subset records");
+  HIP_TRY(c, c->hp_tk.ensure(r * 8), "alloc subset records");
+  HIP_TRY(c, c->sort_scratch.ensure(radix_sort_scratch_elems(r) * 8), "alloc sort scratch");
+  return SWCS_OK;
+}
+
+// Decides by the pairs among a sample of the determinants, one in `share`: sets
+// rows and crowded, and returns 1 for a state that is left to the join or the
+// table.  Nothing but the sample's records is allocated before.
+static int rdm_sample(swcs_ctx* c, const Counters& h, RdmPlan* p) {
+  u64* cursor = c->scalars.as<u64>() + 32;
+  double share = 8.0;
+  while (share < 1024.0 && ((double)h.alive / share > 2.0 * (double)kRdmSample ||
+                            (double)p->total / share > 0.5 * (double)p->cap)) share *= 2.0;
+  const u64 room = std::min(p->cap, (u64)(2.0 * (double)p->total / share) + 64 * p->ntri);
+  int r = rdm_records(c, room);
+  if (r) return r;
+  HIP_TRY(c, launch_fill_u32(cursor, 0u, 2, c->stream), "zero cursor");
+  HIP_TRY(c, launch_rdm_emit(c->st, h.n, c->na + c->nb, p->fm, 1, 0, (u64)share - 1, c->hp_key.as<u64>(), room, cursor,
+                             grid_blocks(c, h.n, 32), c->stream), "subset records");
+  u64 R = 0;
+  HIP_TRY(c, hipMemcpyAsync(&R, cursor, 8, hipMemcpyDeviceToHost, c->stream), "copy");
+  HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+  if (R > room) {
+    HIP_TRY(c, launch_clear_flag(c->st.ctr, kFlagOverflow, c->stream), "clear flag");
+    return 1;
+  }
+  double pairs = 0.0;
+  if (R > 0) {
+    // records that share a bucket's sort bits by chance are no pairs; their
+    // expected number is taken off (16 bits keep it known to a percent of
+    // the limit for up to 2^22 records)
+    const int bits = R < (1ULL << 22) ? 16 : 24;
+    u64* sorted = c->hp_key.as<u64>();
+    HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, bits, c->sort_scratch.as<u64>(),
+                               radix_sort_scratch_elems(room), c->stream, &sorted), "subset sort");
+    const int cgrid = grid_blocks(c, R, 256);
+    HIP_TRY(c, c->partial2.ensure((size_t)cgrid * 8), "alloc partials");
+    HIP_TRY(c, launch_rdm_count(sorted, R, bits, c->partial2.as<double>(), cgrid, c->stream), "pair count");
+    HIP_TRY(c, launch_reduce_partials(c->partial2.as<double>(), cgrid, cgrid, 1, c->scalars.as<double>() + 26,
+                                      c->stream), "pair count");
+    HIP_TRY(c, hipMemcpyAsync(&pairs, c->scalars.as<double>() + 26, 8, hipMemcpyDeviceToHost, c->stream), "copy");
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
+    pairs = std::max(0.0, pairs - 0.5 * (double)R * (double)R / (double)(1ULL << bits));
+  }
+  pairs *= share * share;
+  const double mem = (double)p->cap * (double)rdm_member_bytes() + (double)((size_t)4 << rdm_row_bits());
+  p->rows = pairs > kRdmRowPairs * (double)p->total && p->need + mem <= 0.5 * p->have;
+  p->crowded = pairs > kRdmPairLimit * p->join_records;
+  if (p->crowded && !(p->rows && rdm_rows_pay((double)p->total, pairs, p->join_records))) return 1;
+  return SWCS_OK;
+}
+
+// The pass itself; returns 1 where a class of a crowded state or the records of a
+// class turn out to be more than it takes.
+static int rdm_pass(swcs_ctx* c, const Counters& h, const RdmPlan& p, const int* d_subset, int64_t count,
+                    const double* norm2, double* d_out) {
+  const int ne = c->na + c->nb;
+  const u64 n = h.n, cap = p.cap;
+  HIP_TRY(c, c->rdm_g3.ensure(rdm_gamma_elems(c->n) * 8), "alloc density matrix");
+  HIP_TRY(c, c->rdm_part.ensure(rdm_part_elems(c->n) * 8), "alloc density matrix");
+  HIP_TRY(c, c->rdm_g2.ensure(rdm_two_elems(c->n) * 8), "alloc density matrix");
+  HIP_TRY(c, c->rdm_vtab.ensure(rdm_vtab_elems(c->n) * 8), "alloc density matrix");
   HIP_TRY(c, c->rdm_bs.ensure((size_t)2 * c->n * c->n * 8), "alloc density matrix");
-  HIP_TRY(c, c->hp_key.ensure(cap * 8), "alloc subset records");
-  HIP_TRY(c, c->hp_tk.ensure(cap * 8), "alloc subset records");
-  HIP_TRY(c, c->sort_scratch.ensure(scr * 8), "alloc sort scratch");
+  if (p.rows)
+    HIP_TRY(c, c->rdm_mem.ensure(cap * rdm_member_bytes() + ((size_t)4 << rdm_row_bits())), "alloc subset members");
+  int r = rdm_records(c, cap);
+  if (r) return r;
+  const u64 scr = radix_sort_scratch_elems(cap);
   double* gam = c->rdm_g3.as<double>();
   u64* cursor = c->scalars.as<u64>() + 32;
-  // Decide by the pairs among a sample of the determinants, one in `share`.
-  bool rows = false, crowded = false;
-  {
-    double share = 8.0;
-    while (share < 1024.0 && ((double)h.alive / share > 2.0 * (double)kRdmSample ||
-                              (double)total / share > 0.5 * (double)cap)) share *= 2.0;
-    HIP_TRY(c, launch_fill_u32(cursor, 0u, 2, c->stream), "zero cursor");
-    HIP_TRY(c, launch_rdm_emit(c->st, n, ne, fm, 1, 0, (u64)share - 1, c->hp_key.as<u64>(), cap, cursor,
-                               grid_blocks(c, n, 32), c->stream), "subset records");
-    u64 R = 0;
-    HIP_TRY(c, hipMemcpyAsync(&R, cursor, 8, hipMemcpyDeviceToHost, c->stream), "copy");
-    HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
-    if (R > cap) {
-      HIP_TRY(c, launch_clear_flag(c->st.ctr, kFlagOverflow, c->stream), "clear flag");
-      return 1;
-    }
-    double pairs = 0.0;
-    if (R > 0) {
-      // records that share a bucket's sort bits by chance are no pairs; their
-      // expected number is taken off (16 bits keep it known to a percent of
-      // the limit for up to 2^22 records)
-      const int bits = R < (1ULL << 22) ? 16 : 24;
-      u64* sorted = c->hp_key.as<u64>();
-      HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, bits, c->sort_scratch.as<u64>(), scr, c->stream,
-                                 &sorted), "subset sort");
-      const int cgrid = grid_blocks(c, R, 256);
-      HIP_TRY(c, c->partial2.ensure((size_t)cgrid * 8), "alloc partials");
-      HIP_TRY(c, launch_rdm_count(sorted, R, bits, c->partial2.as<double>(), cgrid, c->stream), "pair count");
-      HIP_TRY(c, launch_reduce_partials(c->partial2.as<double>(), cgrid, cgrid, 1, c->scalars.as<double>() + 26,
-                                        c->stream), "pair count");
-      HIP_TRY(c, hipMemcpyAsync(&pairs, c->scalars.as<double>() + 26, 8, hipMemcpyDeviceToHost, c->stream), "copy");
-      HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
-      pairs = std::max(0.0, pairs - 0.5 * (double)R * (double)R / (double)(1ULL << bits));
-    }
-    pairs *= share * share;
-    const size_t mem = cap * rdm_member_bytes() + ((size_t)4 << rdm_row_bits());
-    rows = pairs > kRdmRowPairs * (double)total && need + (double)mem <= 0.5 * have;
-    crowded = pairs > kRdmPairLimit * R_join;
-    if (crowded && !(rows && rdm_rows_pay((double)total, pairs, R_join))) return 1;
-    if (rows) HIP_TRY(c, c->rdm_mem.ensure(mem), "alloc subset members");
-  }
   HIP_TRY(c, launch_rdm_clear(c->n, gam, c->stream), "zero density matrix");
-  for (int b = 0; b < nbatch; ++b) {
+  for (int b = 0; b < p.nbatch; ++b) {
     HIP_TRY(c, launch_fill_u32(cursor, 0u, 2, c->stream), "zero cursor");
-    HIP_TRY(c, launch_rdm_emit(c->st, n, ne, fm, nbatch, b, 0, c->hp_key.as<u64>(), cap, cursor,
-                               grid_blocks(c, n, nbatch > 1 ? 4 : 32), c->stream), "subset records");
-    u64 R = total;
-    if (nbatch > 1) {
+    HIP_TRY(c, launch_rdm_emit(c->st, n, ne, p.fm, p.nbatch, b, 0, c->hp_key.as<u64>(), cap, cursor,
+                               grid_blocks(c, n, p.nbatch > 1 ? 4 : 32), c->stream), "subset records");
+    u64 R = p.total;
+    if (p.nbatch > 1) {
       HIP_TRY(c, hipMemcpyAsync(&R, cursor, 8, hipMemcpyDeviceToHost, c->stream), "copy");
       HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
       if (R > cap) {  // a class far above its share (many entries on few subsets)
@@ -1809,12 +1836,12 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
       }
     }
     u64* sorted = c->hp_key.as<u64>();
-    HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, sort_bits, c->sort_scratch.as<u64>(), scr, c->stream,
+    HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, p.sort_bits, c->sort_scratch.as<u64>(), scr, c->stream,
                                &sorted), "subset sort");
     const int tiles = (int)std::min<u64>(std::max<u64>((R + 1023) / 1024, 1), (u64)c->num_cu * 16);
-    if (rows && R > 0) {
+    if (p.rows && R > 0) {
       u64* list = sorted == c->hp_key.as<u64>() ? c->hp_tk.as<u64>() : c->hp_key.as<u64>();
-      HIP_TRY(c, launch_rdm_members(c->st, n, c->n, ne, fm, sort_bits, sorted, R, c->rdm_mem.p, list, cursor, tiles,
+      HIP_TRY(c, launch_rdm_members(c->st, n, c->n, ne, p.fm, p.sort_bits, sorted, R, c->rdm_mem.p, list, cursor, tiles,
                                     c->stream), "subset members");
       u64 got[2] = {0, 0};  // records of the list; a bucket longer than the pass takes
       HIP_TRY(c, hipMemcpyAsync(got, cursor, sizeof(got), hipMemcpyDeviceToHost, c->stream), "copy");
@@ -1826,20 +1853,41 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
                                    c->rdm_mem.p, R, gam, c->stream), "rows");
         continue;
       }
-      if (crowded) return 1;
+      if (p.crowded) return 1;
     }
-    HIP_TRY(c, launch_rdm_pairs(c->st, n, c->n, ne, fm, sort_bits, sorted, R, gam, tiles, c->stream), "pairs");
+    HIP_TRY(c, launch_rdm_pairs(c->st, n, c->n, ne, p.fm, p.sort_bits, sorted, R, gam, tiles, c->stream), "pairs");
   }
   HIP_TRY(c, launch_rdm_diag(c->st, n, c->n, gam, (int)std::min<u64>((n + 7) / 8, (u64)c->num_cu), c->stream),
           "diagonal");
   HIP_TRY(c, launch_rdm_gradients(ints_view(c), c->eri.as<double>(), c->na, c->nb, gam, c->rdm_g2.as<double>(), c->rdm_vtab.as<double>(),
                                   c->rdm_part.as<double>(), c->rdm_bs.as<double>(), c->ops.as<OpDesc>(), d_subset,
                                   count, norm2, d_out, c->stream), "contraction");
-  c->ps_keys = (double)total;
+  c->ps_keys = (double)p.total;
   c->ps_slots = 0;
-  c->ps_batches = nbatch;
+  c->ps_batches = p.nbatch;
   c->ps_passes = 1;
   return SWCS_OK;
+}
+
+// Pool gradients of the `count` operators d_subset (NULL: the whole pool) into
+// d_out from the three-body density matrix (k_rdm.hip).  Returns 1 when the
+// pass does not apply: another method or a table budget is set, fewer than
+// three electrons, a small state, too little memory, or so many pairs of
+// determinants within a triple excitation that the join or the table does
+// less work.  Synchronizes (the pair count decides).
+static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, int64_t count, const double* norm2,
+                         double* d_out) {
+  RdmPlan p;
+  if (!rdm_plan(c, h, &p)) return 1;
+  int r = rdm_sample(c, h, &p);
+  if (r == SWCS_OK) {
+    r = rdm_pass(c, h, p, d_subset, count, norm2, d_out);
+    if (r == 1 || r == SWCS_E_OOM) {  // the matrix holds nothing; the join or the table may need the room
+      DevBuf* bufs[] = {&c->rdm_g3, &c->rdm_part, &c->rdm_mem};
+      for (DevBuf* b : bufs) b->release();
+    }
+  }
+  return r == SWCS_E_OOM ? 1 : r;
 }
 
 // The screened query table is sized from a bound on its key count (no host

@@ -1,6 +1,8 @@
 """Device memory that runs out part way: an allocator that refuses chosen blocks.
 A call either finds its way with less scratch, with the same results, or fails
 with SWCS_E_OOM and leaves no state that is neither the old nor the new one."""
+import math
+
 import numpy as np
 import pytest
 
@@ -217,3 +219,71 @@ def test_adjoint_in_groups_of_segments(swcs, kind):
         assert np.abs(dE2 - dE).max() < 1e-12 * max(1.0, np.abs(dE).max())
         ctx.close()
     assert np.abs(dE).max() > 1e-3
+
+
+def _state(n, na, nb, count, width, seed):
+    """Distinct determinants around the reference: each spin occupies the
+    orbitals of smallest orbital number plus exponential noise of mean width."""
+    rng = np.random.default_rng(seed)
+    got = np.zeros(0, dtype=np.uint64)
+    while len(got) < count:
+        key = np.zeros(2 * count, dtype=np.uint64)
+        for spin, occ in ((0, na), (1, nb)):
+            o = np.argsort(rng.exponential(width, (2 * count, n)) + np.arange(n), axis=1)[:, :occ]
+            for c in range(occ):
+                key |= np.uint64(1) << (2 * o[:, c] + spin).astype(np.uint64)
+        got = np.unique(np.concatenate([got, key]))
+    keys = rng.permutation(got)[:count]
+    return keys, rng.standard_normal(count) * 10.0 ** rng.uniform(-4, 0, count)
+
+
+def _matrix_bytes(n):
+    """The three-body density matrix: four square blocks of C(n, 3) or n C(n, 2)
+    rows, one more row, rows of a multiple of eight."""
+    total = 0
+    for rows in (math.comb(n, 3), n * math.comb(n, 2)):
+        total += 2 * 8 * (rows + 1) * ((rows + 8) // 8 * 8)
+    return total
+
+
+def test_density_matrix_refused(swcs):
+    """The density matrix (1.25 GB at 26 orbitals) is refused, everything smaller
+    granted: the join takes the pool, the screened pass the subset."""
+    n, na, nb = 26, 8, 8
+    ctx, mem = _context(swcs, n, na, nb)
+    ctx.set_state(*_state(n, na, nb, 2500, 6.0, 1))
+    size = _matrix_bytes(n)
+    mem.rule(lambda nbytes, k: nbytes >= size)
+    g = ctx.pool_gradients()
+    assert mem.refused > 0
+    some = np.arange(0, ctx.K, 4).astype(np.int32)
+    g_some = ctx.pool_gradients(some)
+    auto = ctx.pool_stats()
+    ctx.set_pool_method("join")
+    want = ctx.pool_gradients()
+    assert auto["screened"] and auto["table_slots"] > 0
+    top = np.abs(want).max()
+    assert top > 1e-3 and np.abs(g - want).max() < 1e-12 * top and np.abs(g_some - want[some]).max() < 1e-12 * top
+    ctx.set_pool_method("auto")
+    mem.rule(lambda nbytes, k: False)
+    g = ctx.pool_gradients()
+    assert size in mem.held.values() and ctx.pool_stats()["keys"] == 2500 * math.comb(16, 3)
+    assert np.abs(g - want).max() < 1e-12 * top
+    ctx.close()
+
+
+def test_turned_away_state_holds_no_matrix(swcs):
+    """100,000 determinants of 32 orbitals and 2 + 2 electrons share subsets by more
+    than a thousand, which only the density-matrix pass itself finds: the matrix
+    (4.4 GB) is given back before the join."""
+    n, na, nb = 32, 2, 2
+    ctx, mem = _context(swcs, n, na, nb)
+    ctx.set_state(*_state(n, na, nb, 100000, 1e6, 2))
+    mem.rule(lambda nbytes, k: False)
+    g = ctx.pool_gradients()
+    assert _matrix_bytes(n) in mem.sizes and _matrix_bytes(n) not in mem.held.values()
+    assert ctx.pool_stats()["keys"] != 100000 * math.comb(4, 3)
+    ctx.set_pool_method("join")
+    want = ctx.pool_gradients()
+    assert np.abs(g - want).max() < 1e-12 * np.abs(want).max()
+    ctx.close()
