@@ -351,6 +351,18 @@ void release_join_scratch(swcs_ctx* c) {
   for (DevBuf* b : bufs) b->release();
 }
 
+// What the density-matrix and spin-string passes keep between calls (it holds
+// nothing): given back where another pass needs the room.  Returns its size.
+size_t matrix_scratch(swcs_ctx* c, bool release) {
+  DevBuf* bufs[] = {&c->rdm_g3, &c->rdm_part, &c->rdm_mem, &c->str_rec, &c->str_key, &c->str_val, &c->str_oth, &c->str_tab};
+  size_t held = 0;
+  for (DevBuf* b : bufs) {
+    held += b->bytes;
+    if (release) b->release();
+  }
+  return held;
+}
+
 // Whether the whole-pool join is taken for a state of `alive` entries: a
 // forced join always, AUTO up to kJoinAutoMaxRecords records.
 bool join_fits_state(swcs_ctx* c, u64 alive) {
@@ -362,8 +374,10 @@ bool join_fits_state(swcs_ctx* c, u64 alive) {
 // Budget for a table sized from free memory: 40 % of what is free (blocks
 // cached by the allocator included) plus the table's own allocation.  The
 // join's scratch is given back first only when a table of `need` bytes would
-// not fit that budget otherwise: giving it back on every call makes a caching
-// allocator split and regrow its blocks from one call to the next.
+// not fit that budget otherwise, and the density matrix's and the strings' when
+// it still does not and they are an eighth of the rest: giving them back on every
+// call makes a caching allocator split and regrow its blocks from one call to the
+// next.
 double free_table_budget(swcs_ctx* c, double need) {
   auto budget = [&]() {
     return std::max<double>(64.0 * 1024 * 1024, 0.4 * (double)(avail_bytes(c) + c->acc_tab.bytes));
@@ -371,6 +385,10 @@ double free_table_budget(swcs_ctx* c, double need) {
   double b = budget();
   if (need > b) {
     release_join_scratch(c);
+    b = budget();
+  }
+  if (need > b && 8 * matrix_scratch(c, false) >= avail_bytes(c)) {
+    (void)matrix_scratch(c, true);
     b = budget();
   }
   return b;
@@ -1882,10 +1900,7 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
   int r = rdm_sample(c, h, &p);
   if (r == SWCS_OK) {
     r = rdm_pass(c, h, p, d_subset, count, norm2, d_out);
-    if (r == 1 || r == SWCS_E_OOM) {  // the matrix holds nothing; the join or the table may need the room
-      DevBuf* bufs[] = {&c->rdm_g3, &c->rdm_part, &c->rdm_mem};
-      for (DevBuf* b : bufs) b->release();
-    }
+    if (r == 1 || r == SWCS_E_OOM) (void)matrix_scratch(c, true);  // the join or the table may need the room
   }
   return r == SWCS_E_OOM ? 1 : r;
 }
@@ -2157,32 +2172,39 @@ static int join_gradients(swcs_ctx* c, const Counters& h, const unsigned char* d
   const u64 scr = radix_sort_scratch_elems(R);
   const u64 list_bytes = n * 16;  // (key, psi) of every stored entry
   const double need = 16.0 * (double)R + 8.0 * (double)scr + (double)list_bytes;
-  const double have = (double)(avail_bytes(c) + c->hp_key.bytes + c->hp_tk.bytes + c->sort_scratch.bytes +
-                               c->join_src.bytes + c->join_w.bytes);
-  if (need > 0.5 * have) {
-    if (forced) return fail(c, SWCS_E_CAPACITY, "join records exceed half of the free device memory");
-    return 1;
-  }
   // Gradient terms by operator bin (2^lb bins of at most kJoinTermSlots
   // operators, k mod 2^lb), each with room for 1.25 times an even share of
   // the records: the device-scope adds into g[K] then number about 8192 per
   // bin and chunk instead of one per record.  Terms past a full bin, and
   // every term when the bins do not fit, take the direct adds.
+  int lb = 0;
+  while (lb < kJoinBinsLog && (u64)c->K_pool > (256ULL << lb)) ++lb;
+  while (lb <= kJoinMaxBinsLog && (u64)c->K_pool > ((u64)kJoinTermSlots << lb)) ++lb;
+  const bool bins = lb <= kJoinMaxBinsLog;
+  const u64 cap = ((u64)(1.25 * (double)R / (double)(1ULL << lb)) + 4096 + 7) & ~7ULL;
+  const double bin_bytes = 10.0 * (double)cap * (double)(1ULL << lb);
+  auto room = [&]() {
+    return 0.5 * (double)(avail_bytes(c) + c->hp_key.bytes + c->hp_tk.bytes + c->sort_scratch.bytes +
+                          c->join_src.bytes + c->join_w.bytes);
+  };
+  double half = room();
+  const double gain = 0.5 * (double)matrix_scratch(c, false);
+  if ((need > half && need <= half + gain) || (bins && need + bin_bytes > half && need + bin_bytes <= half + gain)) {
+    (void)matrix_scratch(c, true);
+    half = room();
+  }
+  if (need > half) {
+    if (forced) return fail(c, SWCS_E_CAPACITY, "join records exceed half of the free device memory");
+    return 1;
+  }
   JoinTerms terms{-1, 0, nullptr, nullptr, nullptr};
-  {
-    int lb = 0;
-    while (lb < kJoinBinsLog && (u64)c->K_pool > (256ULL << lb)) ++lb;
-    while (lb <= kJoinMaxBinsLog && (u64)c->K_pool > ((u64)kJoinTermSlots << lb)) ++lb;
-    const u64 cap = ((u64)(1.25 * (double)R / (double)(1ULL << lb)) + 4096 + 7) & ~7ULL;
-    const double bin_bytes = 10.0 * (double)cap * (double)(1ULL << lb);
-    if (lb <= kJoinMaxBinsLog && need + bin_bytes <= 0.5 * have) {
-      // one buffer: the bins' cursors (2 KB kept for them), values, operators
-      const size_t head = (size_t)8 << kJoinMaxBinsLog;
-      HIP_TRY(c, c->join_w.ensure(head + (size_t)(cap << lb) * 10), "alloc join terms");
-      HIP_TRY(c, launch_fill_u32(c->join_w.p, 0u, (u64)2 << lb, c->stream), "zero bins");
-      double* w = (double*)((char*)c->join_w.p + head);
-      terms = JoinTerms{lb, cap, c->join_w.as<u64>(), w, (unsigned short*)(w + (cap << lb))};
-    }
+  if (bins && need + bin_bytes <= half) {
+    // one buffer: the bins' cursors (2 KB kept for them), values, operators
+    const size_t head = (size_t)8 << kJoinMaxBinsLog;
+    HIP_TRY(c, c->join_w.ensure(head + (size_t)(cap << lb) * 10), "alloc join terms");
+    HIP_TRY(c, launch_fill_u32(c->join_w.p, 0u, (u64)2 << lb, c->stream), "zero bins");
+    double* w = (double*)((char*)c->join_w.p + head);
+    terms = JoinTerms{lb, cap, c->join_w.as<u64>(), w, (unsigned short*)(w + (cap << lb))};
   }
   HIP_TRY(c, c->hp_key.ensure(R * 8), "alloc join records");
   HIP_TRY(c, c->hp_tk.ensure(R * 8), "alloc join records");

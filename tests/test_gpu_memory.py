@@ -287,3 +287,29 @@ def test_turned_away_state_holds_no_matrix(swcs):
     want = ctx.pool_gradients()
     assert np.abs(g - want).max() < 1e-12 * np.abs(want).max()
     ctx.close()
+
+
+@pytest.mark.parametrize("method", ["join", "table"])
+def test_matrix_given_back_to_other_passes(swcs, method):
+    """With 1.8 GB of the device free beside a density matrix of 1.25 GB from an
+    earlier call: 73,982,500 join records take 1.2 GB, half of 2.5; a table of their
+    keys takes 0.4 of what is free at once, so both get the matrix's room."""
+    import torch
+    n, na, nb, count = 26, 8, 8, 2500
+    ctx, mem = _context(swcs, n, na, nb)
+    ctx.set_state(*_state(n, na, nb, count, 6.0, 1))
+    want = ctx.pool_gradients()
+    size = _matrix_bytes(n)
+    assert ctx.pool_stats()["keys"] == count * math.comb(16, 3) and size in mem.held.values()
+    torch.cuda.empty_cache()
+    torch.cuda.synchronize()
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - 1_800_000_000, dtype=torch.uint8, device="cuda")
+    try:
+        ctx.set_pool_method(method)
+        g = ctx.pool_gradients()
+        assert size not in mem.held.values()
+        assert np.abs(g - want).max() < 1e-12 * np.abs(want).max()
+    finally:
+        ctx.close()
+        del rest
+        torch.cuda.empty_cache()
