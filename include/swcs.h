@@ -101,8 +101,10 @@ int swcs_set_stream(swcs_ctx* ctx, void* hip_stream);
  * and may free a block while work it enqueued earlier on the context stream
  * still reads it: the allocator must keep a freed block from other use until
  * that stream has passed the free (a caching allocator bound to the context
- * stream does; otherwise synchronize in free_fn).  An alloc_fn failure
- * returns SWCS_E_OOM from the call that needed the memory.  Budgets the
+ * stream does; otherwise synchronize in free_fn).  When alloc_fn fails the
+ * library gives back scratch that earlier calls left, asks again, and takes a
+ * form that needs less where there is one (adjoint, density matrix);
+ * then SWCS_E_OOM from the call that needed the memory.  Budgets the
  * library derives from free device memory (state capacity, pool-gradient
  * tables) count hipMemGetInfo's free bytes plus the bytes the library has
  * handed back to free_fn; memory the allocator caches for others is not

@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -31,6 +32,10 @@ struct Allocator {
   swcs_free_fn free = nullptr;
   void* user = nullptr;
   size_t cached = 0;
+  // before an allocation fails: gives back what holds nothing, false if there is
+  // nothing of the kind
+  bool (*reclaim)(swcs_ctx*) = nullptr;
+  swcs_ctx* ctx = nullptr;
 };
 
 // Device buffer that grows on demand (contents are not preserved on growth).
@@ -47,6 +52,11 @@ struct DevBuf {
     if (want <= bytes && p) return hipSuccess;
     release();
     if (want == 0) want = 8;
+    hipError_t e = take(want);
+    if (e == hipErrorOutOfMemory && cur && cur->reclaim && cur->reclaim(cur->ctx)) e = take(want);
+    return e;
+  }
+  hipError_t take(size_t want) {
     if (cur && cur->alloc) {
       p = cur->alloc(want, cur->user);
       if (!p) return hipErrorOutOfMemory;
@@ -202,6 +212,10 @@ struct swcs_ctx {
     for (DevBuf* b : all) f(*b);
     for (auto& b : ckpt) f(b);
   }
+  // A pass that uses the density matrix's, the strings' or the adjoint's scratch is
+  // under way; between passes this scratch holds nothing.
+  bool matrix_busy = false, strings_busy = false, adjoint_busy = false;
+
   // Point every buffer's next allocation at the context's allocator.
   void bind_buffers() {
     for_each_buf([this](DevBuf& b) { b.cur = &alloc; });
@@ -361,6 +375,30 @@ size_t matrix_scratch(swcs_ctx* c, bool release) {
     if (release) b->release();
   }
   return held;
+}
+
+// Marks a pass that is under way (swcs_ctx::*_busy).
+struct Busy {
+  bool& flag;
+  explicit Busy(bool& f) : flag(f) { flag = true; }
+  ~Busy() { flag = false; }
+};
+
+// Last resort of an allocation: the scratch of passes that are not under way.  A
+// call fits where it did before such a pass had run.
+bool reclaim_idle(swcs_ctx* c) {
+  size_t held = 0;
+  auto give = [&](bool busy, std::initializer_list<DevBuf*> bufs) {
+    for (DevBuf* b : bufs) {
+      if (busy) continue;
+      held += b->bytes;
+      b->release();
+    }
+  };
+  give(c->matrix_busy, {&c->rdm_g3, &c->rdm_part, &c->rdm_mem});
+  give(c->strings_busy, {&c->str_rec, &c->str_key, &c->str_val, &c->str_oth, &c->str_tab});
+  give(c->adjoint_busy, {&c->seg_states, &c->work});
+  return held > 0;
 }
 
 // Whether the whole-pool join is taken for a state of `alive` entries: a
@@ -858,6 +896,8 @@ int swcs_create(int n_spatial, int n_alpha, int n_beta, int device, swcs_ctx** o
   double sec = binom(n_spatial, n_alpha) * binom(n_spatial, n_beta);
   c->sector = sec > 1e18 ? (u64)1e18 : (u64)sec;
   c->exc = make_exc_space(n_spatial, n_alpha, n_beta);
+  c->alloc.reclaim = reclaim_idle;
+  c->alloc.ctx = c;
   c->bind_buffers();
   if (c->ctr.ensure(sizeof(Counters)) != hipSuccess || c->scalars.ensure(64 * sizeof(double)) != hipSuccess) {
     g_create_error = "device allocation failed";
@@ -1394,6 +1434,7 @@ static int string_sigma(swcs_ctx* c, const Counters& h) {
   const int occ[2] = {c->na, c->nb};
   const int shift = (c->n + 1 + 7) / 8 * 8;  // whole digits: the sort never reads the index
   if (shift < 64 && ((n - 1) >> (64 - shift)) != 0) return 1;
+  const Busy busy(c->strings_busy);
   // Tests per determinant, from the sampled chance that two share a string.
   // The spin whose strings lead the (1, 1) pass is the one with fewer tests: a
   // string's neighbours are at most nocc nvir groups of about its own size.
@@ -1897,6 +1938,7 @@ static int rdm_gradients(swcs_ctx* c, const Counters& h, const int* d_subset, in
                          double* d_out) {
   RdmPlan p;
   if (!rdm_plan(c, h, &p)) return 1;
+  const Busy busy(c->matrix_busy);
   int r = rdm_sample(c, h, &p);
   if (r == SWCS_OK) {
     r = rdm_pass(c, h, p, d_subset, count, norm2, d_out);
@@ -2453,6 +2495,7 @@ int swcs_param_gradients(swcs_ctx* c, double* dE, double* E_out) {
   // slot also holds up to one star record per stored entry.
   const size_t gate_log_bytes = n * (sizeof(PairRec) + (c->a_has_star ? sizeof(StarRec) : 0));
   HIP_TRY(c, launch_mu_init(c->st, c->sigma.as<double>(), n, nn, c->mu.as<double>(), c->stream), "mu init");
+  const Busy busy(c->adjoint_busy);
   if (lds) {
     const hipError_t el = c->seg_states.ensure((size_t)M * gate_log_bytes);
     if (el != hipSuccess && el != hipErrorOutOfMemory) return hip_fail(c, el, "alloc pair logs");

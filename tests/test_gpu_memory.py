@@ -313,3 +313,36 @@ def test_matrix_given_back_to_other_passes(swcs, method):
         ctx.close()
         del rest
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("kept", ["density matrix", "strings", "adjoint"])
+def test_idle_scratch_makes_room(swcs, kept):
+    """A pool of memory that is nearly full after a pass: a later call gets the room
+    of the scratch which that pass left behind."""
+    n, na, nb = (11, 5, 4) if kept == "adjoint" else (26, 8, 8)
+    ctx, mem = _context(swcs, n, na, nb)
+    if kept == "adjoint":
+        _, _, _, ops, theta = _chain()
+        ctx.apply_ansatz(ops, theta)
+        ctx.param_gradients(len(ops))
+        ctx.set_sigma_method("hole_pairs")
+        call = ctx.energy
+    elif kept == "density matrix":
+        ctx.set_state(*_state(n, na, nb, 2500, 6.0, 1))
+        ctx.pool_gradients()
+        assert _matrix_bytes(n) in mem.held.values()
+        big = _state(n, na, nb, 300000, 1e6, 3)
+        call = lambda: ctx.set_state(*big)
+    else:
+        ctx.set_state(*_state(n, na, nb, 300000, 1e6, 3))
+        ctx.energy()
+        call = ctx.get_state
+    before = dict(mem.held)
+    limit = sum(before.values()) + (1 << 20)
+    mem.rule(lambda nbytes, k: sum(mem.held.values()) + nbytes > limit)
+    call()
+    gone = [s for p, s in before.items() if p not in mem.held]
+    print(f"[memory] {kept}: {mem.refused} refused, {sum(gone)} bytes given back", flush=True)
+    assert mem.refused > 0 and sum(mem.held.values()) <= limit
+    assert abs(np.sum(ctx.get_state()[1] ** 2) / ctx.energy_noalloc()[2] - 1.0) < 1e-12
+    ctx.close()
