@@ -103,7 +103,7 @@ int swcs_set_stream(swcs_ctx* ctx, void* hip_stream);
  * that stream has passed the free (a caching allocator bound to the context
  * stream does; otherwise synchronize in free_fn).  When alloc_fn fails the
  * library gives back scratch that earlier calls left, asks again, and takes a
- * form that needs less where there is one (adjoint, density matrix);
+ * form that needs less where there is one (adjoint, density matrix, strings);
  * then SWCS_E_OOM from the call that needed the memory.  Budgets the
  * library derives from free device memory (state capacity, pool-gradient
  * tables) count hipMemGetInfo's free bytes plus the bytes the library has

@@ -1427,14 +1427,13 @@ static int diag_enqueue(swcs_ctx* c, u64 n) {
 // the groups' pair tests outweigh its sort.  Synchronizes for that decision,
 // which rests on a sample (20 us; deciding after the sorts cost a state that is
 // turned away 200).
-static int string_sigma(swcs_ctx* c, const Counters& h) {
+static int string_sigma_enqueue(swcs_ctx* c, const Counters& h) {
   const u64 n = h.n, alive = h.alive;
   if (c->sigma_method != SWCS_SIGMA_AUTO || alive == 0 || n >= (1ULL << 31)) return 1;
   const int ne = c->na + c->nb;
   const int occ[2] = {c->na, c->nb};
   const int shift = (c->n + 1 + 7) / 8 * 8;  // whole digits: the sort never reads the index
   if (shift < 64 && ((n - 1) >> (64 - shift)) != 0) return 1;
-  const Busy busy(c->strings_busy);
   // Tests per determinant, from the sampled chance that two share a string.
   // The spin whose strings lead the (1, 1) pass is the one with fewer tests: a
   // string's neighbours are at most nocc nvir groups of about its own size.
@@ -1489,6 +1488,17 @@ static int string_sigma(swcs_ctx* c, const Counters& h) {
                            c->str_val.as<double>() + s * alive, c->str_oth.as<unsigned>() + s * alive, tab[s], slots[s],
                            s == lead, c->sigma.as<double>(), grid_blocks(c, alive, 32), c->stream), "string pairs");
   return SWCS_OK;
+}
+
+// Same; a state without room for the strings is left to hole pairs, which may
+// find their records' buffers in place.
+static int string_sigma(swcs_ctx* c, const Counters& h) {
+  const Busy busy(c->strings_busy);
+  const int r = string_sigma_enqueue(c, h);
+  if (r != SWCS_E_OOM) return r;
+  DevBuf* bufs[] = {&c->str_rec, &c->str_key, &c->str_val, &c->str_oth, &c->str_tab};
+  for (DevBuf* b : bufs) b->release();
+  return 1;
 }
 
 // sigma_P over the stored entries; (numer, norm2) land in scalars[0..1] on

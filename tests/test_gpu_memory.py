@@ -346,3 +346,21 @@ def test_idle_scratch_makes_room(swcs, kept):
     assert mem.refused > 0 and sum(mem.held.values()) <= limit
     assert abs(np.sum(ctx.get_state()[1] ** 2) / ctx.energy_noalloc()[2] - 1.0) < 1e-12
     ctx.close()
+
+
+def test_strings_refused(swcs):
+    """The records of the spin strings (32 bytes a determinant) are refused: sigma_P
+    by hole pairs."""
+    ctx, mem = _context(swcs, 26, 8, 8)
+    ctx.set_state(*_state(26, 8, 8, 40000, 1e6, 5))
+    mem.rule(lambda nbytes, k: nbytes == 32 * 40000)
+    e, nu, norm2 = ctx.energy()
+    keys, sigma = ctx.sigma_projected()
+    assert mem.refused == 2
+    ctx.set_sigma_method("hole_pairs")
+    e2 = ctx.energy()[0]
+    keys2, sigma2 = ctx.sigma_projected()
+    scale = np.linalg.norm(sigma2)
+    assert np.array_equal(keys, keys2) and np.linalg.norm(sigma - sigma2) < 1e-12 * scale
+    assert abs(e - e2) < 1e-12 * scale / np.sqrt(norm2)
+    ctx.close()
