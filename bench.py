@@ -258,7 +258,7 @@ def gpu_bench(args, wl):
     reps = 3
     for kname in ("chain_lds", "gate", "adjoint_lds", "adjoint_replay_lds", "gate_replay", "adjoint_rec", "sigma_proj",
                   "holepair", "sigma_push", "sigma_push_into", "pool_contract", "contract_ops", "select",
-                  "join_emit", "join_sort", "join_reduce", "join_terms"):
+                  "join_emit", "join_sort", "join_reduce", "join_terms", "strings"):
         if not args.kernel_times:
             break
         ctx.timer_start(kname)

@@ -370,7 +370,8 @@ enum {
   SWCS_K_JOIN_EMIT = 14,     /* full-pool gradients: one record per connection   */
   SWCS_K_JOIN_SORT = 15,     /* full-pool gradients: radix sort of the records   */
   SWCS_K_JOIN_REDUCE = 16,   /* full-pool gradients: sigma and g per bucket run  */
-  SWCS_K_JOIN_TERMS = 17     /* full-pool gradients: sums of the binned g terms  */
+  SWCS_K_JOIN_TERMS = 17,    /* full-pool gradients: sums of the binned g terms  */
+  SWCS_K_STRINGS = 18        /* sigma_P pair evaluation inside spin-string groups, one launch a spin */
 };
 
 /* From now on record HIP events on the context stream around every launch

@@ -1483,7 +1483,7 @@ static int string_sigma_enqueue(swcs_ctx* c, const Counters& h) {
   const Ints I = ints_view(c);
   HIP_TRY(c, launch_sigma_diag(c->st, I, n, c->sigma.as<double>(), grid_blocks(c, n, 256), c->stream), "diagonal sigma");
   for (int s = 0; s < 2; ++s)
-    TIMED(c, SWCS_K_HOLEPAIR,
+    TIMED(c, SWCS_K_STRINGS,
           launch_str_sigma(I, rec[s], alive, shift, occ[s], c->str_key.as<u64>() + s * alive,
                            c->str_val.as<double>() + s * alive, c->str_oth.as<unsigned>() + s * alive, tab[s], slots[s],
                            s == lead, c->sigma.as<double>(), grid_blocks(c, alive, 32), c->stream), "string pairs");
@@ -2707,7 +2707,7 @@ int swcs_occupations(swcs_ctx* c, double* n_out) {
 
 int swcs_timer_start(swcs_ctx* c, int kernel_id) {
   if (!c) return SWCS_E_INVALID;
-  if (kernel_id < SWCS_K_CHAIN_LDS || kernel_id > SWCS_K_JOIN_TERMS)
+  if (kernel_id < SWCS_K_CHAIN_LDS || kernel_id > SWCS_K_STRINGS)
     return fail(c, SWCS_E_INVALID, "unknown kernel id");
   c->timer_kernel = kernel_id;
   c->ev_used = 0;
