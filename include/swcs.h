@@ -305,8 +305,9 @@ int swcs_gate_sizes(swcs_ctx* ctx, int64_t* n_in, int64_t M);
 
 /* Per-gate active counts of the last apply call: n_act[M] receives the number
  * of stored entries the gate's operator (or its adjoint) acts on, counted by
- * the multi-block gate kernels (0 for gates run in the single-workgroup chain
- * of small states).  Returns SWCS_E_INVALID if M differs. */
+ * the multi-block gate kernels and by the single-workgroup chain for sectors
+ * smaller than its capacity and for overlapping generators (0 for the other
+ * gates it runs).  Returns SWCS_E_INVALID if M differs. */
 int swcs_gate_active(swcs_ctx* ctx, int64_t* n_act, int64_t M);
 
 /* Stored entries (alive or pruned; every gate scans them) and alive

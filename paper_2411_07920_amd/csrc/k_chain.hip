@@ -178,22 +178,24 @@ static_assert(kLdsCap <= 4 * kChainThreads, "lds_ncut holds four entries a threa
 // for g % seg == 0) and the per-gate input sizes are written to HBM.  If a
 // gate might not fit, the kernel stops before it: the state is written back
 // and ctr->stop_gate / kFlagStopped tell the host where to continue.  STAR:
-// gates with kinds[g] set are overlapping generators gens[g].
+// gates with kinds[g] set are overlapping generators gens[g].  gate_n_act (may
+// be NULL) receives the entries that each gate's operator acts on, as the
+// multi-block kernels count them.
 template <int CAP, bool STAR>
 __global__ void __launch_bounds__(kChainThreads)
 k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restrict__ ctr,
             const GateDesc* __restrict__ gates, const int* __restrict__ kinds, const GenGate* __restrict__ gens,
             int g0, int M, double eps, int prune_first, double* const* __restrict__ ckpt, u64* __restrict__ ckpt_n, int seg,
-            u64* __restrict__ gate_n_in, u64 max_keys, unsigned ncut) {
+            u64* __restrict__ gate_n_in, u64* __restrict__ gate_n_act, u64 max_keys, unsigned ncut) {
   __shared__ NcutState nst;
   __shared__ u64 skeys[CAP];
   __shared__ double samps[CAP];
   __shared__ int sslots[2 * CAP];
-  // Per-gate append and alive-change counters, three in rotation: gate g
-  // uses slot g % 3; after the gate's barrier every thread reads it, and
+  // Per-gate append, activity and alive-change counters, three in rotation: gate
+  // g uses slot g % 3; after the gate's barrier every thread reads it, and
   // thread 0 clears slot (g + 2) % 3, last read before the previous barrier
   // and next used after the following one.
-  __shared__ unsigned s_app[3];
+  __shared__ unsigned s_app[3], s_act[3];
   __shared__ int s_dal[3];
   __shared__ unsigned s_n0, s_alive0;
   __shared__ GateDesc sg[kGateChunk];
@@ -205,6 +207,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
   }
   if (tid < 3) {
     s_app[tid] = 0;
+    s_act[tid] = 0;
     s_dal[tid] = 0;
   }
   for (int t = tid; t < 2 * CAP; t += kChainThreads) sslots[t] = 0;
@@ -250,6 +253,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
     }
     const int slot = g % 3;
     int dal = 0;
+    unsigned act = 0;
     auto append = [&](u64 key, double val) {
       const unsigned idx = n + atomicAdd(&s_app[slot], 1u);
       skeys[idx] = key;
@@ -262,6 +266,7 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
       for (unsigned i = tid; i < n; i += kChainThreads) {
         const GenOut o = gen_entry(S, i, gg, eps);
         dal += (int)o.dalive;
+        act += (op_acts(gg.op1, skeys[i]) || op_acts(gg.op2, skeys[i])) ? 1u : 0u;
         if (o.napp > 0) append(o.key[0], o.val[0]);
         if (o.napp > 1) append(o.key[1], o.val[1]);
       }
@@ -270,14 +275,18 @@ k_chain_lds(u64* __restrict__ keys, double* __restrict__ amps, Counters* __restr
       for (unsigned i = tid; i < n; i += kChainThreads) {
         const GateOut o = gate_entry(S, i, gd.op, gd.c, gd.s, eps);
         dal += (int)o.dalive;
+        act += o.acts ? 1u : 0u;
         if (o.append) append(o.key, o.val);
       }
     }
     if (dal) atomicAdd(&s_dal[slot], dal);
+    if (gate_n_act && act) atomicAdd(&s_act[slot], act);
     lds_barrier();
     if (tid == 0) {
       if (gate_n_in) gate_n_in[g] = alive;
+      if (gate_n_act) gate_n_act[g] = s_act[slot];
       s_app[(g + 2) % 3] = 0;
+      s_act[(g + 2) % 3] = 0;
       s_dal[(g + 2) % 3] = 0;
     }
     n += s_app[slot];
@@ -480,13 +489,13 @@ int lds_chain_capacity() { return kLdsCap; }
 
 hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, const int* kinds, const GenGate* gens,
                             int g0, int M, double eps, int prune_first, double* const* ckpt, u64* ckpt_n, int seg,
-                            u64* gate_n_in, u64 max_keys, unsigned ncut, hipStream_t stream) {
+                            u64* gate_n_in, u64* gate_n_act, u64 max_keys, unsigned ncut, hipStream_t stream) {
   if (kinds)
     hipLaunchKernelGGL((k_chain_lds<kLdsCap, true>), dim3(1), dim3(kChainThreads), 0, stream, st.keys, st.amps, st.ctr,
-                       gates, kinds, gens, g0, M, eps, prune_first, ckpt, ckpt_n, seg, gate_n_in, max_keys, ncut);
+                       gates, kinds, gens, g0, M, eps, prune_first, ckpt, ckpt_n, seg, gate_n_in, gate_n_act, max_keys, ncut);
   else
     hipLaunchKernelGGL((k_chain_lds<kLdsCap, false>), dim3(1), dim3(kChainThreads), 0, stream, st.keys, st.amps, st.ctr,
-                       gates, kinds, gens, g0, M, eps, prune_first, ckpt, ckpt_n, seg, gate_n_in, max_keys, ncut);
+                       gates, kinds, gens, g0, M, eps, prune_first, ckpt, ckpt_n, seg, gate_n_in, gate_n_act, max_keys, ncut);
   return hipGetLastError();
 }
 

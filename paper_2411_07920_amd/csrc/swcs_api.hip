@@ -697,9 +697,13 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     if (r) return r;
   }
   if (chain_in_lds(c, n_start, M)) {
+    // counted where the chain would run in HBM but for its small sector or its
+    // overlapping generators
+    const bool count = has_star || c->st.cap < (u64)lds_chain_capacity();
     TIMED(c, SWCS_K_CHAIN_LDS, launch_chain_lds(c->st, c->gate_tab.as<GateDesc>(), kinds, gens, 0, (int)M, eps, eps > 0.0 ? 1 : 0,
                                 ckpt ? c->ckpt_ptrs.as<double*>() : nullptr, c->ckpt_n.as<u64>(),
-                                c->seg, c->gate_n_in.as<u64>(), c->sector, ncut, c->stream), "chain");
+                                c->seg, c->gate_n_in.as<u64>(), count ? c->gate_n_act.as<u64>() : nullptr, c->sector, ncut,
+                                c->stream), "chain");
     HIP_TRY(c, launch_hash_clear(c->st.hash, c->st.hmask + 1, c->stream), "hash clear");
     HIP_TRY(c, launch_hash_build_dev(c->st, grid_blocks(c, lds_chain_capacity(), 256), c->stream), "hash build");
     hipError_t e;

@@ -466,7 +466,7 @@ hipError_t launch_ncut(double* amps, u64 stride, const u64* keys, u64 n_host, Co
 int lds_chain_capacity();
 hipError_t launch_chain_lds(const DeviceState& st, const GateDesc* gates, const int* kinds, const GenGate* gens,
                             int g0, int M, double eps, int prune_first, double* const* ckpt, u64* ckpt_n, int seg,
-                            u64* gate_n_in, u64 max_keys, unsigned ncut, hipStream_t stream);
+                            u64* gate_n_in, u64* gate_n_act, u64 max_keys, unsigned ncut, hipStream_t stream);
 hipError_t launch_adjoint_replay_lds(const u64* keys, unsigned n, const GateDesc* gates, const int* kinds,
                                      const GenGate* gens, int M, int seg, double eps, const double* const* ckpt,
                                      const u64* ckpt_n, char* logbuf, size_t log_bytes, unsigned* logcnt,

@@ -410,7 +410,8 @@ class Context:
         return out[:M]
 
     def gate_active(self, M: int):
-        """Entries each gate's operator acted on (multi-block gates; 0 in the LDS chain)."""
+        """Entries each gate's operator acted on (0 where the LDS chain does not count
+        them: include/swcs.h, swcs_gate_active)."""
         out = np.zeros(max(M, 1), dtype=np.int64)
         self._check(self._lib.swcs_gate_active(self._h, _ptr(out, ctypes.c_int64), M))
         return out[:M]
