@@ -727,24 +727,22 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     if (begun) c->have_state = false;
     return r;
   };
-  // Buffers of the gates from g0 on, allocated before the first is enqueued.
-  auto reserve = [&]() -> int {
+  // A checkpoint is allocated ahead of its gate, while the gates before it run
+  // (in a new context these allocations are a tenth of the chain's time).
+  auto enqueue = [&]() -> int {
     if (ncut) {
       int r = ncut_reserve(c, 1, c->st.cap);
       if (r) return r;
     }
-    for (int64_t j = ckpt ? (g0 + c->seg - 1) / c->seg : M; j * c->seg < M; ++j)
-      HIP_TRY(c, c->ckpt[(size_t)j].ensure(c->st.cap * sizeof(double)), "alloc checkpoint");
-    return SWCS_OK;
-  };
-  auto enqueue = [&]() -> int {
     HIP_TRY(c, launch_live_begin(c->st, (unsigned)g0, c->stream), "counters");
     for (int64_t g = g0; g < M; ++g) {
       if (ckpt && g % c->seg == 0) {
         const int j = (int)(g / c->seg);
+        HIP_TRY(c, c->ckpt[j].ensure(c->st.cap * sizeof(double)), "alloc checkpoint");
         HIP_TRY(c, launch_ckpt_save(c->st, (unsigned)g, c->ckpt[j].as<double>(), c->ckpt_n.as<u64>() + j,
                                     grid_blocks(c, c->st.cap / 4, 256), c->stream), "checkpoint");
       }
+      begun = true;
       const OpDesc& op = c->ops_host[op_idx[g]];
       if (kind && kind[g])
         HIP_TRY(c, launch_gen_gate(c->st, gen[g], eps, c->gate_n_in.as<u64>() + g, (unsigned)g, c->sector,
@@ -768,10 +766,7 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     return SWCS_OK;
   };
   for (int attempt = 0; attempt < 64; ++attempt) {
-    int r = reserve();
-    if (r) return part_way(r);
-    begun = true;
-    r = enqueue();
+    int r = enqueue();
     if (r) return part_way(r);
     hipError_t e;
     Counters h = read_counters(c, &e);
@@ -1836,22 +1831,22 @@ static int rdm_records(swcs_ctx* c, u64 r) {
 
 // Decides by the pairs among a sample of the determinants, one in `share`: sets
 // rows and crowded, and returns 1 for a state that is left to the join or the
-// table.  Nothing but the sample's records is allocated before.
+// table.  Nothing but the record buffers, which the join uses as well, is allocated
+// before.
 static int rdm_sample(swcs_ctx* c, const Counters& h, RdmPlan* p) {
   u64* cursor = c->scalars.as<u64>() + 32;
   double share = 8.0;
   while (share < 1024.0 && ((double)h.alive / share > 2.0 * (double)kRdmSample ||
                             (double)p->total / share > 0.5 * (double)p->cap)) share *= 2.0;
-  const u64 room = std::min(p->cap, (u64)(2.0 * (double)p->total / share) + 64 * p->ntri);
-  int r = rdm_records(c, room);
+  int r = rdm_records(c, p->cap);
   if (r) return r;
   HIP_TRY(c, launch_fill_u32(cursor, 0u, 2, c->stream), "zero cursor");
-  HIP_TRY(c, launch_rdm_emit(c->st, h.n, c->na + c->nb, p->fm, 1, 0, (u64)share - 1, c->hp_key.as<u64>(), room, cursor,
+  HIP_TRY(c, launch_rdm_emit(c->st, h.n, c->na + c->nb, p->fm, 1, 0, (u64)share - 1, c->hp_key.as<u64>(), p->cap, cursor,
                              grid_blocks(c, h.n, 32), c->stream), "subset records");
   u64 R = 0;
   HIP_TRY(c, hipMemcpyAsync(&R, cursor, 8, hipMemcpyDeviceToHost, c->stream), "copy");
   HIP_TRY(c, hipStreamSynchronize(c->stream), "sync");
-  if (R > room) {
+  if (R > p->cap) {
     HIP_TRY(c, launch_clear_flag(c->st.ctr, kFlagOverflow, c->stream), "clear flag");
     return 1;
   }
@@ -1863,7 +1858,7 @@ static int rdm_sample(swcs_ctx* c, const Counters& h, RdmPlan* p) {
     const int bits = R < (1ULL << 22) ? 16 : 24;
     u64* sorted = c->hp_key.as<u64>();
     HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, bits, c->sort_scratch.as<u64>(),
-                               radix_sort_scratch_elems(room), c->stream, &sorted), "subset sort");
+                               radix_sort_scratch_elems(p->cap), c->stream, &sorted), "subset sort");
     const int cgrid = grid_blocks(c, R, 256);
     HIP_TRY(c, c->partial2.ensure((size_t)cgrid * 8), "alloc partials");
     HIP_TRY(c, launch_rdm_count(sorted, R, bits, c->partial2.as<double>(), cgrid, c->stream), "pair count");
@@ -1898,8 +1893,6 @@ static int rdm_pass(swcs_ctx* c, const Counters& h, const RdmPlan& p, const int*
   HIP_TRY(c, c->rdm_bs.ensure((size_t)2 * c->n * c->n * 8), "alloc density matrix");
   if (p.rows)
     HIP_TRY(c, c->rdm_mem.ensure(cap * rdm_member_bytes() + ((size_t)4 << rdm_row_bits())), "alloc subset members");
-  int r = rdm_records(c, cap);
-  if (r) return r;
   const u64 scr = radix_sort_scratch_elems(cap);
   double* gam = c->rdm_g3.as<double>();
   u64* cursor = c->scalars.as<u64>() + 32;
@@ -2453,16 +2446,17 @@ constexpr size_t kReplayGroupBytes = (size_t)4 << 30;
 // there a launch of many blocks is faster.
 constexpr u64 kWalkMaxRecords = 8192;
 
-// Buffers for replaying *segs segments of n entries side by side.  Where a block
-// is refused it is tried with half as many segments, and one segment once more
-// after everything that holds nothing has been given back.
+// Buffers for replaying *segs segments of n entries side by side.  Groups of up to
+// 512 MB need no look at free memory (0.1 ms).  Where a block is refused it is tried
+// with half as many segments, and one segment once more after everything that
+// holds nothing has been given back.
 static int replay_reserve(swcs_ctx* c, u64 n, int nseg, size_t gate_log_bytes, int* segs) {
   DevBuf* bufs[] = {&c->seg_states, &c->work, &c->ncut_cand, &c->ncut_state};
   const size_t seg_bytes = (size_t)c->seg * gate_log_bytes + n * 8 + (c->a_ncut ? n * 4 + ncut_select_bytes() : 0);
   size_t s = std::min<size_t>((size_t)nseg, std::max<size_t>(1, kReplayGroupBytes / seg_bytes));
   size_t held = 0;
   for (DevBuf* b : bufs) held += b->bytes;
-  if (s * seg_bytes > held) s = std::min(s, std::max<size_t>(1, (held + avail_bytes(c)) / 2 / seg_bytes));
+  if (s * seg_bytes > std::max<size_t>(held, (size_t)512 << 20)) s = std::min(s, std::max<size_t>(1, (held + avail_bytes(c)) / 2 / seg_bytes));
   auto take = [&]() -> int {
     HIP_TRY(c, c->seg_states.ensure(s * c->seg * gate_log_bytes), "alloc pair logs");
     HIP_TRY(c, c->work.ensure(s * n * 8), "alloc working amplitudes");
