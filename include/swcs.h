@@ -142,9 +142,11 @@ int swcs_set_table_budget(swcs_ctx* ctx, int64_t bytes);
  * LDS by popcount.  AUTO (default) takes PAIRS when the state
  * fits and n <= 8 C, otherwise ENUMERATE up to 3e7 probes, otherwise one sort
  * of the determinants by each spin's occupation and pair tests within these
- * groups (40 bytes per determinant and spin of device memory), or HOLE_PAIRS
- * where a sample finds the groups large.  All give the same sigma up to
- * summation order.
+ * groups (up to 2^31 stored entries), or HOLE_PAIRS where a sample finds the
+ * groups large or the memory is refused.  The spin groups take 36 bytes per
+ * determinant and spin, and per spin a table of 16-byte slots, the next power
+ * of two from twice the determinants or, if fewer, the strings of that spin.
+ * All give the same sigma up to summation order.
  * Returns SWCS_E_INVALID for an unknown method. */
 enum { SWCS_SIGMA_AUTO = 0, SWCS_SIGMA_ENUMERATE = 1, SWCS_SIGMA_HOLE_PAIRS = 2, SWCS_SIGMA_PAIRS = 3 };
 int swcs_set_sigma_method(swcs_ctx* ctx, int method);
@@ -165,18 +167,22 @@ int swcs_set_sigma_method(swcs_ctx* ctx, int method);
  * (default), with no table budget set, forms large states' gradients from the
  * three-body density matrix of the stored determinants instead: pairs that
  * share N_e - 3 electrons, found by a sort of alive * C(N_e, 3) records, then
- * a dense contraction with the integrals (3 to 32 electrons; from 3e7 join
- * records, more beyond 20 orbitals; not where a sample of the state shows so
- * many such pairs -- more than join records, or some ten times as many where
- * another 16 bytes a record fit -- that the join does less work; up to 1.3 GB at
- * 26 orbitals plus 16 bytes a record, within half of the free device memory).
- * It serves screened subsets
- * that would otherwise count their query keys as well.  Where it does not
- * apply, AUTO takes JOIN when there are at most 2^31 records (beyond that the
- * table was faster at 52 spin-orbitals) and they fit within half of the free
- * device memory and the word, else TABLE; a JOIN pass whose hash group
- * overflows its LDS table is redone by TABLE.  Forced JOIN that does not fit
- * returns SWCS_E_CAPACITY.  All agree up to summation order.
+ * a dense contraction with the integrals (3 to 32 electrons).  A cost model
+ * takes it: for a whole pool from 9e6 join records where 0.6 ms, 0.4 ps times
+ * n^7 and 55 ps per record of its own are below 65 ps per join record; for a
+ * subset where, besides, 0.9 ms, the n^7 term and 150 ps per record are below
+ * 15 ps per join record and 350 more times the share of the pool (in the device
+ * entry point only where its query keys would be counted).  Not
+ * where a sample of the state shows so many such pairs -- more than join
+ * records, or some ten times as many where another 16 bytes a record fit --
+ * that the join does less work, nor where it would take more than half of the
+ * free device memory: the matrix (1.25 GB at 26 orbitals, 4.4 at 32), 0.13 and
+ * 0.3 GB of partial sums, and 16 bytes a record.  Where it does not apply or
+ * its memory is refused, AUTO takes JOIN when there are at most 2^31 records
+ * (beyond that the table was faster at 52 spin-orbitals) and they fit within
+ * half of the free device memory and the word, else TABLE; a JOIN pass whose
+ * hash group overflows its LDS table is redone by TABLE.  Forced JOIN that does
+ * not fit returns SWCS_E_CAPACITY.  All agree up to summation order.
  * Returns SWCS_E_INVALID for an unknown method. */
 enum { SWCS_POOL_AUTO = 0, SWCS_POOL_TABLE = 1, SWCS_POOL_JOIN = 2 };
 int swcs_set_pool_method(swcs_ctx* ctx, int method);
@@ -285,7 +291,8 @@ int swcs_pool_gradients(swcs_ctx* ctx, const int32_t* subset, int64_t n_subset, 
  * synchronization) and restarts with fewer batches when the query set is
  * under half the estimate.
  * A call that would count takes the density matrix instead where AUTO does
- * (swcs_set_pool_method), with two synchronizations.
+ * (swcs_set_pool_method), with two synchronizations, a third on crowded states,
+ * and two or three per hash class above 2^28 subset records.
  * A bound-sized table is not checked on the host: if an insert found it full
  * (more than 4,096 probes at load <= 1/2), every entry of d_g is NaN.
  * Returns SWCS_E_OOM if even 4,096 batches do not fit the table memory. */
