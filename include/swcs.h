@@ -114,7 +114,8 @@ int swcs_set_allocator(swcs_ctx* ctx, swcs_alloc_fn alloc_fn, swcs_free_fn free_
 
 /* Upper bound on stored determinants (0 = library default, sized from free
  * device memory).  With allow_regrow != 0 the state arrays grow on demand up
- * to that bound; growth past it fails with SWCS_E_CAPACITY.  With
+ * to that bound; a chain that would grow past it fails with SWCS_E_CAPACITY and
+ * leaves the state in front of the gate that did not fit.  With
  * allow_regrow == 0 (max_dets > 0 required, else SWCS_E_INVALID) the arrays
  * are reserved once at max_dets on the next apply or set_state and then kept:
  * no state allocation happens inside later applies, and a chain that would

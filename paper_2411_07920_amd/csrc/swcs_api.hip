@@ -775,7 +775,7 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
       h.flags &= ~(kFlagOverflow | kFlagStopped);
       HIP_TRY(c, launch_store_counters(c->st.ctr, h, c->stream), "counters");
       c->hc_valid = false;
-      return fail(c, SWCS_E_DEVICE, "internal overflow in gate chain");
+      return part_way(fail(c, SWCS_E_DEVICE, "internal overflow in gate chain"));
     }
     if (!(h.flags & kFlagStopped)) {
       // a chain without checkpoints leaves no record of storage positions
@@ -822,7 +822,7 @@ int run_chain(swcs_ctx* c, const int32_t* op_idx, const double* cs, const double
     // Checkpoint of the gate where the chain resumes was skipped if it lies
     // on a segment boundary: the loop above re-enqueues it.
   }
-  return fail(c, SWCS_E_CAPACITY, "capacity growth did not converge");
+  return part_way(fail(c, SWCS_E_CAPACITY, "capacity growth did not converge"));
 }
 
 }  // namespace
@@ -1178,10 +1178,19 @@ static int apply_common(swcs_ctx* c, ChainSpec& sp, double eps, int64_t ncut, in
   }
   int r = run_chain(c, sp.ops.data(), sp.cs.data(), sp.sn.data(), M, eps, (unsigned)ncut, from_reference,
                     n_start, &h, sp.kind.data(), sp.gen.data());
-  if (r && from_reference && c->have_state && chain_in_lds(c, 1, M)) {
-    // the chain may have failed before the index it would have left was built
-    (void)launch_hash_clear(c->st.hash, c->st.hmask + 1, c->stream);
-    (void)launch_hash_build_dev(c->st, grid_blocks(c, c->st.cap, 256), c->stream);
+  if (r && c->have_state) {
+    // the state in front of the gate that did not fit, or the one before the first:
+    // its index, where the chain failed before the one it would have left was
+    // built, and its filter
+    const std::string err = c->err;
+    hipError_t e;
+    const Counters h1 = read_counters(c, &e);
+    if (e == hipSuccess && from_reference && chain_in_lds(c, 1, M)) {
+      e = launch_hash_clear(c->st.hash, c->st.hmask + 1, c->stream);
+      if (e == hipSuccess) e = launch_hash_build_dev(c->st, grid_blocks(c, c->st.cap, 256), c->stream);
+    }
+    if (e != hipSuccess || build_filter(c, h1.n, h1.alive) != SWCS_OK) c->have_state = false;
+    c->err = err;
   }
   if (r) return r;
   r = build_filter(c, h.n, h.alive);

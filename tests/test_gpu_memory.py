@@ -364,3 +364,29 @@ def test_strings_refused(swcs):
     assert np.array_equal(keys, keys2) and np.linalg.norm(sigma - sigma2) < 1e-12 * scale
     assert abs(e - e2) < 1e-12 * scale / np.sqrt(norm2)
     ctx.close()
+
+
+@pytest.mark.parametrize("start", ["reference", "set_state"])
+def test_state_of_a_chain_past_the_maximum(swcs, start):
+    """A chain that would grow past the largest capacity stops in front of a gate
+    and keeps the state there: its energy (through the index and the filter) is that
+    of the exported state."""
+    n, na, nb, ops, theta = _chain()
+    ctx, mem = _context(swcs, n, na, nb)
+    ctx.set_capacity(20000)
+    with pytest.raises(swcs.SwcsError) as ei:
+        if start == "reference":
+            ctx.apply_ansatz(ops, theta)
+        else:
+            ctx.apply_ansatz(ops[:8], theta[:8])
+            ctx.apply_gates(ops[8:], theta[8:])
+    assert ei.value.code == swcs.SWCS_E_CAPACITY
+    keys, amps = ctx.get_state()
+    assert len(keys) > 4096 and abs(np.sum(amps ** 2) - 1.0) < 1e-12
+    e = ctx.energy()[0]
+    ctx.set_capacity(0)
+    ctx.set_state(keys, amps)
+    want = ctx.energy()[0]
+    print(f"[memory] {len(keys)} determinants: {e} {want}", flush=True)
+    assert abs(e - want) < 1e-12 * abs(want)
+    ctx.close()
