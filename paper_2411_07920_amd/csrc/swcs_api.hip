@@ -1895,17 +1895,28 @@ static int rdm_pass(swcs_ctx* c, const Counters& h, const RdmPlan& p, const int*
                     const double* norm2, double* d_out) {
   const int ne = c->na + c->nb;
   const u64 n = h.n, cap = p.cap;
-  HIP_TRY(c, c->rdm_g3.ensure(rdm_gamma_elems(c->n) * 8), "alloc density matrix");
-  HIP_TRY(c, c->rdm_part.ensure(rdm_part_elems(c->n) * 8), "alloc density matrix");
-  HIP_TRY(c, c->rdm_g2.ensure(rdm_two_elems(c->n) * 8), "alloc density matrix");
-  HIP_TRY(c, c->rdm_vtab.ensure(rdm_vtab_elems(c->n) * 8), "alloc density matrix");
-  HIP_TRY(c, c->rdm_bs.ensure((size_t)2 * c->n * c->n * 8), "alloc density matrix");
-  if (p.rows)
-    HIP_TRY(c, c->rdm_mem.ensure(cap * rdm_member_bytes() + ((size_t)4 << rdm_row_bits())), "alloc subset members");
   const u64 scr = radix_sort_scratch_elems(cap);
-  double* gam = c->rdm_g3.as<double>();
   u64* cursor = c->scalars.as<u64>() + 32;
-  HIP_TRY(c, launch_rdm_clear(c->n, gam, c->stream), "zero density matrix");
+  // In a new context the matrix is allocated while the first records are written and
+  // sorted (0.2 ms); one in place is cleared before them, so that the sorted records
+  // are still in the caches when the pairs read them (0.05 ms at 26 orbitals).
+  double* gam = nullptr;
+  auto matrix = [&]() -> int {
+    HIP_TRY(c, c->rdm_g3.ensure(rdm_gamma_elems(c->n) * 8), "alloc density matrix");
+    HIP_TRY(c, c->rdm_part.ensure(rdm_part_elems(c->n) * 8), "alloc density matrix");
+    HIP_TRY(c, c->rdm_g2.ensure(rdm_two_elems(c->n) * 8), "alloc density matrix");
+    HIP_TRY(c, c->rdm_vtab.ensure(rdm_vtab_elems(c->n) * 8), "alloc density matrix");
+    HIP_TRY(c, c->rdm_bs.ensure((size_t)2 * c->n * c->n * 8), "alloc density matrix");
+    if (p.rows)
+      HIP_TRY(c, c->rdm_mem.ensure(cap * rdm_member_bytes() + ((size_t)4 << rdm_row_bits())), "alloc subset members");
+    gam = c->rdm_g3.as<double>();
+    HIP_TRY(c, launch_rdm_clear(c->n, gam, c->stream), "zero density matrix");
+    return SWCS_OK;
+  };
+  if (c->rdm_g3.bytes >= rdm_gamma_elems(c->n) * 8) {
+    int r = matrix();
+    if (r) return r;
+  }
   for (int b = 0; b < p.nbatch; ++b) {
     HIP_TRY(c, launch_fill_u32(cursor, 0u, 2, c->stream), "zero cursor");
     HIP_TRY(c, launch_rdm_emit(c->st, n, ne, p.fm, p.nbatch, b, 0, c->hp_key.as<u64>(), cap, cursor,
@@ -1922,6 +1933,10 @@ static int rdm_pass(swcs_ctx* c, const Counters& h, const RdmPlan& p, const int*
     u64* sorted = c->hp_key.as<u64>();
     HIP_TRY(c, radix_sort_keys(sorted, c->hp_tk.as<u64>(), R, p.sort_bits, c->sort_scratch.as<u64>(), scr, c->stream,
                                &sorted), "subset sort");
+    if (!gam) {
+      int r = matrix();
+      if (r) return r;
+    }
     const int tiles = (int)std::min<u64>(std::max<u64>((R + 1023) / 1024, 1), (u64)c->num_cu * 16);
     if (p.rows && R > 0) {
       u64* list = sorted == c->hp_key.as<u64>() ? c->hp_tk.as<u64>() : c->hp_key.as<u64>();
